@@ -125,6 +125,10 @@ constexpr int kBlocksPerCU = 8;            // resident 256-thread workgroups per
 // queues, their sizes falling linearly from 1.5x to 0.5x the mean, so that the wavefronts finish
 // together.  Each range start costs a few dependent loads and a pipeline fill.
 constexpr int kRangesPerWave = 6;
+// Calls of at most this many streamlines per wavefront of a full launch give every wavefront one
+// range of (nearly) equally many streamlines instead, without a table: with a handful of streamlines a
+// wavefront, finding, fetching and starting six ranges takes longer than counting them.
+constexpr int kStaticRangeStreamlines = 4;
 constexpr int64_t kLongRangesFrom = int64_t(1) << 21;   // 4-window batches from this many streamlines
 constexpr int64_t kDirectMaxStreamlines = int64_t(1) << 17;   // calls below this many streamlines ...
 constexpr int64_t kDirectMaxEntries = int64_t(1) << 20;       // ... on a C of at most this many entries
@@ -179,8 +183,10 @@ struct CountPlan {
     size_t ovf_bytes = 0, ct_bytes = 0, ends_bytes = 0, fb_bytes = 0, first_bytes = 0, pairs_bytes = 0;
 };
 
-// Scratch regions of one call (device pointers, sized by CountPlan).  `fallback` must be all-zero.
+// Scratch regions of one call (device pointers, sized by CountPlan).  `fallback` must be all-zero,
+// or `zero_fallback` set (compact volumes only).
 struct CountScratch {
+    bool zero_fallback = false;
     void *ovf = nullptr;        // overflow count, range counter (256 B), then the overflow queue
     int32_t *ct = nullptr;      // transposed copy of C
     int32_t *ends = nullptr;    // end labels: last[S] (and first[S])
@@ -239,8 +245,13 @@ int make_count_plan(int64_t S, int32_t N, int32_t M, const fc::CompactVol *cv, c
                                                 4 * (size_t)cv->ncoarse_words);
     if (o.blocks_per_cu > 0 && o.blocks_per_cu < per_cu) per_cu = o.blocks_per_cu;
     cp.blocks = (int64_t)cus * per_cu;
-    cp.nparts = cp.blocks * fc::kWavesPerBlock * kRangesPerWave;
-    cp.first_bytes = 4 * (size_t)(cp.nparts + 1);
+    if (S <= cp.blocks * fc::kWavesPerBlock * kStaticRangeStreamlines) {
+        cp.nparts = std::min<int64_t>(cp.blocks * fc::kWavesPerBlock, S);
+        cp.blocks = (cp.nparts + fc::kWavesPerBlock - 1) / fc::kWavesPerBlock;
+    } else {
+        cp.nparts = cp.blocks * fc::kWavesPerBlock * kRangesPerWave;
+        cp.first_bytes = 4 * (size_t)(cp.nparts + 1);
+    }
     // pair slices: pair_capacity entries in all (default 8 per streamline, between 2^20 and
     // 2^28), split evenly between the wavefronts; a full slice sends the rest of its
     // wavefront's updates to C as atomics
@@ -335,12 +346,20 @@ int enqueue_count(const CountPlan &cp, const CountScratch &sc, int dev, const fl
             z.w32[1] = reinterpret_cast<int32_t *>(pb + cp.off_hist);
             z.n32[1] = fc::pair_hist_cursor_words(cp.ntiles);
         }
+        if (sc.zero_fallback) {
+            z.w32[2] = reinterpret_cast<int32_t *>(sc.fallback);
+            z.n32[2] = (int64_t)(cp.fb_bytes / 4);
+        }
         z.w64 = a.ovf.count;   // overflow count and range queues
         z.n64 = header_words;
-        // tapering ranges (largest first) end the launch evenly
-        FC_HIP(fc::launch_partition(offsets, S, cp.nparts, sc.first, z, true, cus, st));
+        fc::Ranges rg;
+        rg.first = cp.first_bytes ? sc.first : nullptr;
+        rg.nparts = cp.nparts;
+        rg.per = (uint32_t)(S / cp.nparts);
+        rg.extra = (uint32_t)(S % cp.nparts);
+        FC_HIP(fc::launch_partition(offsets, S, cp.nparts, cp.first_bytes ? sc.first : nullptr, z, cus, st));
         if (o.event_begin) FC_HIP(hipEventRecord((hipEvent_t)o.event_begin, st));
-        FC_HIP(fc::launch_count_stream(a, *cv, sc.first, cp.nparts, (int)cp.blocks, cp.batch, po, st));
+        FC_HIP(fc::launch_count_stream(a, *cv, rg, (int)cp.blocks, cp.batch, po, st));
         if (o.event_end) FC_HIP(hipEventRecord((hipEvent_t)o.event_end, st));
         FC_HIP(fc::launch_fallback_compact(a, *cv, fs, st));
         if (cp.append)
@@ -1036,8 +1055,7 @@ int fastcod_volume_count_noalloc(const fastcod_volume *vol, const float *points,
     hipStream_t st = static_cast<hipStream_t>(stream);
     FC_HIP(hipStreamWaitEvent(st, vol->ready, 0));
     // the fallback's bit maps must start all-zero; an earlier call may have left other contents there
-    if (cp.fb_bytes) FC_HIP(fc::launch_fill_i32(reinterpret_cast<int32_t *>(sc.fallback), (int64_t)(cp.fb_bytes / 4), 0,
-                                                cu_count(dev), st));
+    sc.zero_fallback = cp.fb_bytes > 0;
     const fc::Grid g = make_grid(vol->dims);
     return enqueue_count(cp, sc, dev, points, offsets, S, g, vol->N, vol->M, nullptr, &cv, C, o, st);
 }

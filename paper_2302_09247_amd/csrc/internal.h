@@ -152,18 +152,25 @@ hipError_t launch_compact_build(const int32_t *roi, const int32_t *lab, Grid g, 
                                 int64_t W, int cus, hipStream_t st);
 
 // Per-call state zeroed by the partition launch, so that it needs no launches of its own: C when
-// it is not accumulated into, the pair histogram's tile cursors, the overflow and range counters.
-// Each range may be empty.
+// it is not accumulated into, the pair histogram's tile cursors, a fixed scratch area's fallback bit
+// maps, the overflow and range counters.  Each range may be empty.
 struct ZeroRanges {
-    int32_t *w32[2] = {nullptr, nullptr};
-    int64_t n32[2] = {0, 0};
+    int32_t *w32[3] = {nullptr, nullptr, nullptr};
+    int64_t n32[3] = {0, 0, 0};
     unsigned long long *w64 = nullptr;
     int64_t n64 = 0;
 };
-// nparts ranges of whole streamlines, of equal point counts or (taper) of point counts falling
-// linearly from 1.5x to 0.5x the mean in range order: first[nparts + 1]; also zeroes `z`
+// nparts ranges of whole streamlines, their point counts falling linearly from 1.5x to 0.5x the mean
+// in range order: first[nparts + 1] (nullptr: no ranges); also zeroes `z`
 hipError_t launch_partition(const int64_t *offsets, int64_t S, int64_t nparts, int32_t *first, const ZeroRanges &z,
-                            bool taper, int cus, hipStream_t st);
+                            int cus, hipStream_t st);
+// Streamline ranges of a flat-stream launch: a table of nparts ranges handed out by the queues, or
+// (first == nullptr) one range per wavefront, `per` streamlines each and one more in the first `extra`.
+struct Ranges {
+    const int32_t *first;
+    int64_t nparts;
+    uint32_t per, extra;
+};
 // resident 256-thread workgroups per CU of the flat-stream kernel
 int count_stream_blocks_per_cu(bool scaled, bool packed, int batch, bool ends, int up, size_t dyn_lds);
 
@@ -178,10 +185,9 @@ hipError_t launch_parcellate(const int32_t *C, int32_t N, int32_t M, int32_t *la
 // Alg. 1's count: C(row of the first point, label of the last point) += 1 for every streamline
 hipError_t launch_count_seed_end(const CountArgs &a, const RasterVol *rv, const CompactVol *cv, int cus,
                                  hipStream_t st);
-// wavefronts take the nparts ranges of `first` from ovf.work; batch: 64-point windows per
-// pipelined batch (2 or 4)
-hipError_t launch_count_stream(const CountArgs &a, const CompactVol &cv, const int32_t *first, int64_t nparts,
-                               int blocks, int batch, const PairOut &po, hipStream_t st);
+// batch: 64-point windows per pipelined batch (2 or 4)
+hipError_t launch_count_stream(const CountArgs &a, const CompactVol &cv, const Ranges &rg, int blocks, int batch,
+                               const PairOut &po, hipStream_t st);
 // C[NM] += histogram of the updates in the slices (nwaves slices of po.cap entries, lengths in
 // po.counts), ntiles = ceil(NM / 16K).  hist: pair_hist_words(ntiles) words, of which the first
 // pair_hist_cursor_words(ntiles) (the tile cursors) must be zero on entry; sorted: nwaves * po.cap

@@ -1,0 +1,56 @@
+"""GPU parity of the flat-stream kernel's streamline ranges against the oracle, bit-exact.
+
+Up to four streamlines per wavefront of a full launch, every wavefront gets one range of (nearly)
+equally many streamlines; beyond that, ranges come from a table written in one pass over the offsets.
+Both sides of that line, calls smaller than one workgroup, streamlines long enough to begin hundreds
+of ranges at once, and runs of empty streamlines, also at the ends.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2302_09247_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(S, giant, seed):
+    vols = synth.volumes_interleaved64()
+    rng = np.random.default_rng(seed)
+    lens = rng.integers(0, 9, S)
+    lens[rng.random(S) < 0.2] = 0
+    lens[: S // 8] = 0
+    lens[S - S // 8:] = 0
+    if giant:
+        lens[S // 2] = 60 * max(S, 50)
+    off = np.zeros(S + 1, np.int64)
+    off[1:] = np.cumsum(lens)
+    P = int(off[-1])
+    # points near the middle of the grid, in runs that stay close to each other
+    base = np.repeat(rng.uniform(4, 60, (P // 16 + 1, 3)), 16, axis=0)[:P]
+    pts = (base + rng.uniform(-2, 2, (P, 3))).astype(np.float32).reshape(-1, 3)
+    return pts, off, vols
+
+
+@pytest.mark.parametrize("S", [1, 3, 5, 1023, 1025, 4096, 4097, 9001])
+@pytest.mark.parametrize("giant", [False, True])
+def test_ranges(fc, S, giant):
+    pts, off, vols = _case(S, giant, 100 + S)
+    if pts.shape[0] == 0:
+        pts = np.zeros((1, 3), np.float32)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    dev = [torch.from_numpy(a).cuda() for a in (pts, off, vols.roi, vols.lab)]
+    vol = fc.Volume(dev[2], dev[3], vols.N, vols.M)
+    for mode in (0, 2):
+        exp = oracle.count(pts, off, vols.roi, vols.lab, vols.N, vols.M, mode=mode)
+        # one workgroup per CU: with 256 CUs the line lies at 4 * 4 * 256 = 4096 streamlines
+        print(f"ranges S={S} giant={giant} mode={mode} cus={cus}", flush=True)
+        for kw in (dict(blocks_per_cu=1), dict()):
+            C = fc.count(*dev, vols.N, vols.M, mode=mode, variant=2, **kw)
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(C.cpu().numpy().astype(np.int64), exp, err_msg=f"{kw}")
+        out = torch.full((vols.N, vols.M), 7, dtype=torch.int32, device="cuda")
+        vol.count(dev[0], dev[1], mode=mode, out=out, noalloc=True, blocks_per_cu=1)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(out.cpu().numpy().astype(np.int64), exp, err_msg="noalloc")
