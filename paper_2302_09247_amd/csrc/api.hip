@@ -270,12 +270,27 @@ int make_count_plan(int64_t S, int32_t N, int32_t M, const fc::CompactVol *cv, c
     return FASTCOD_OK;
 }
 
-// The counting sequence on one stream, against a raster or a compact volume, with the scratch
-// regions of `sc` (sized by `cp`).
-int enqueue_count(const CountPlan &cp, const CountScratch &sc, int dev, const float *points, const int64_t *offsets,
+// A compact volume that the call builds for itself, from raster volumes into `buf`.
+struct VolumeBuild {
+    const int32_t *roi, *lab;
+    const int32_t *dims;
+    const CompactLayout *L;
+    void *buf;
+};
+
+// The counting sequence on one stream, against a raster or a compact volume (with `vb`: one that is
+// built first), with the scratch regions of `sc` (sized by `cp`).
+int enqueue_count(const CountPlan &cp, const CountScratch &sc, int dev, const VolumeBuild *vb, const float *points, const int64_t *offsets,
                   int64_t S, const fc::Grid &g, int32_t N, int32_t M, const fc::RasterVol *rv,
                   const fc::CompactVol *cv, int32_t *C, const fastcod_opts &o, hipStream_t st) {
     const int cus = cu_count(dev);
+    auto build = [&](bool zeroed) {
+        return enqueue_compact_build(vb->roi, vb->lab, vb->dims, N, M, *vb->L, vb->buf, cus, st, zeroed);
+    };
+    // the partition launch zeroes what the build needs, so the build follows it, unless something
+    // before the partition reads the volume
+    const bool build_late = vb && !cp.seed_end && S > 0 && cp.nl == 0;
+    if (vb && !build_late && S > 0) FC_HIP(build(false));
     if (cp.seed_end) {
         // Alg. 1's count: one update per streamline, straight into C
         if (!(o.flags & FASTCOD_ACCUMULATE)) FC_HIP(fc::launch_fill_i32(C, (int64_t)N * M, 0, cus, st));
@@ -350,6 +365,7 @@ int enqueue_count(const CountPlan &cp, const CountScratch &sc, int dev, const fl
             z.w32[2] = reinterpret_cast<int32_t *>(sc.fallback);
             z.n32[2] = (int64_t)(cp.fb_bytes / 4);
         }
+        if (build_late) z.w32[3] = compact_zero_words(vb->buf, *vb->L, &z.n32[3]);
         z.w64 = a.ovf.count;   // overflow count and range queues
         z.n64 = header_words;
         fc::Ranges rg;
@@ -358,6 +374,7 @@ int enqueue_count(const CountPlan &cp, const CountScratch &sc, int dev, const fl
         rg.per = (uint32_t)(S / cp.nparts);
         rg.extra = (uint32_t)(S % cp.nparts);
         FC_HIP(fc::launch_partition(offsets, S, cp.nparts, cp.first_bytes ? sc.first : nullptr, z, cus, st));
+        if (build_late) FC_HIP(build(true));
         if (o.event_begin) FC_HIP(hipEventRecord((hipEvent_t)o.event_begin, st));
         FC_HIP(fc::launch_count_stream(a, *cv, rg, (int)cp.blocks, cp.batch, po, st));
         if (o.event_end) FC_HIP(hipEventRecord((hipEvent_t)o.event_end, st));
@@ -377,7 +394,7 @@ int enqueue_count(const CountPlan &cp, const CountScratch &sc, int dev, const fl
 }
 
 // The counting sequence with the scratch regions taken from (and grown in) the stream's workspace.
-int enqueue_count_ws(Workspace &ws, int dev, const float *points, const int64_t *offsets, int64_t S,
+int enqueue_count_ws(Workspace &ws, int dev, const VolumeBuild *vb, const float *points, const int64_t *offsets, int64_t S,
                      const fc::Grid &g, int32_t N, int32_t M, const fc::RasterVol *rv, const fc::CompactVol *cv,
                      int32_t *C, const fastcod_opts &o, hipStream_t st) {
     CountPlan cp;
@@ -408,7 +425,7 @@ int enqueue_count_ws(Workspace &ws, int dev, const float *points, const int64_t 
         FC_HIP(ws.pairs.ensure(cp.pairs_bytes, false));
         sc.pairs = static_cast<char *>(ws.pairs.p);
     }
-    return enqueue_count(cp, sc, dev, points, offsets, S, g, N, M, rv, cv, C, o, st);
+    return enqueue_count(cp, sc, dev, vb, points, offsets, S, g, N, M, rv, cv, C, o, st);
 }
 
 // ---- batched plans ----
@@ -933,12 +950,12 @@ int fastcod_count_ex(const float *points, const int64_t *offsets, int64_t S, con
         return fail(FASTCOD_EINVAL, "grid too thin for the compact volume; use FASTCOD_VARIANT_WAVE");
     if (o.variant == FASTCOD_VARIANT_WAVE || !compact_ok) {
         fc::RasterVol rv{roi, lab, dims[0], dims[0] * dims[1], N, M};
-        return enqueue_count_ws(ws, dev, points, offsets, S, g, N, M, &rv, nullptr, C, o, st);
+        return enqueue_count_ws(ws, dev, nullptr, points, offsets, S, g, N, M, &rv, nullptr, C, o, st);
     }
     FC_HIP(ws.compact.ensure(L.bytes, false));
     fc::CompactVol cv = compact_view(ws.compact.p, L, N, M);
-    FC_HIP(enqueue_compact_build(roi, lab, dims, N, M, L, ws.compact.p, cu_count(dev), st));
-    return enqueue_count_ws(ws, dev, points, offsets, S, g, N, M, nullptr, &cv, C, o, st);
+    const VolumeBuild vb{roi, lab, dims, &L, ws.compact.p};
+    return enqueue_count_ws(ws, dev, &vb, points, offsets, S, g, N, M, nullptr, &cv, C, o, st);
 }
 
 int fastcod_count(const float *points, const int64_t *offsets, int64_t S, const int32_t *roi, const int32_t *lab,
@@ -1009,7 +1026,7 @@ int fastcod_volume_count(const fastcod_volume *vol, const float *points, const i
     FC_HIP(hipStreamWaitEvent(st, vol->ready, 0));
     const fc::Grid g = make_grid(vol->dims);
     fc::CompactVol cv = compact_view(vol->buf, vol->L, vol->N, vol->M);
-    return enqueue_count_ws(ws, dev, points, offsets, S, g, vol->N, vol->M, nullptr, &cv, C, o, st);
+    return enqueue_count_ws(ws, dev, nullptr, points, offsets, S, g, vol->N, vol->M, nullptr, &cv, C, o, st);
 }
 
 int fastcod_volume_count_noalloc(const fastcod_volume *vol, const float *points, const int64_t *offsets, int64_t S,
@@ -1057,7 +1074,7 @@ int fastcod_volume_count_noalloc(const fastcod_volume *vol, const float *points,
     // the fallback's bit maps must start all-zero; an earlier call may have left other contents there
     sc.zero_fallback = cp.fb_bytes > 0;
     const fc::Grid g = make_grid(vol->dims);
-    return enqueue_count(cp, sc, dev, points, offsets, S, g, vol->N, vol->M, nullptr, &cv, C, o, st);
+    return enqueue_count(cp, sc, dev, nullptr, points, offsets, S, g, vol->N, vol->M, nullptr, &cv, C, o, st);
 }
 
 int fastcod_probe_stream(const float *points, int64_t P, uint32_t *sink, void *stream) {

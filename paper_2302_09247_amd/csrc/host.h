@@ -104,16 +104,16 @@ inline int cu_count(int dev) {
 // ---- compact volume layout ----
 constexpr int32_t kMaxCoarseWords = 8192;      // 32 KB of LDS per counting workgroup
 constexpr int32_t kBatchedCoarseWords = 512;   // per-wavefront LDS coarse map of the batched kernel (2 KB)
+constexpr int32_t kCoarseHead = 2;             // words before the coarse map: the number of codes
 struct CompactLayout {
     int32_t SBX, SBY, SBZ;
     int64_t W;        // words
-    int64_t ntiles;
     int64_t nvox;
     bool packed;
     int32_t rbits;
     int32_t csx, csyz, CBX, CBY, CBZ, ncoarse_words;
     int64_t ncodes;   // capacity of the code array (every voxel unless sized by compact_layout_fit)
-    size_t off_mb, off_tiles, off_coarse, off_codes, bytes;
+    size_t off_mb, off_coarse, off_codes, bytes;   // off_coarse: the code count, then the coarse map
 };
 
 inline bool compact_layout(const int32_t dims[3], int32_t N, int32_t M, CompactLayout &L,
@@ -126,7 +126,6 @@ inline bool compact_layout(const int32_t dims[3], int32_t N, int32_t M, CompactL
     // word indices are uint32 and padding must stay modest (thin grids use raster lookups)
     if (L.W >= (int64_t(1) << 31) || L.W * 32 > 8 * L.nvox + (int64_t(1) << 22)) return false;
     if ((int64_t)L.SBX * L.SBY >= (int64_t(1) << 31)) return false;
-    L.ntiles = (L.W + fc::kScanTile - 1) / fc::kScanTile;
     const int rb = bit_width((uint32_t)N), lb = bit_width((uint32_t)M);
     L.packed = rb + lb <= 32;
     L.rbits = rb;
@@ -150,9 +149,8 @@ inline bool compact_layout(const int32_t dims[3], int32_t N, int32_t M, CompactL
     if (!fits) return false;
     auto align = [](size_t v) { return (v + 255) & ~size_t(255); };
     L.off_mb = 0;
-    L.off_tiles = align(L.off_mb + 8 * (size_t)L.W);
-    L.off_coarse = align(L.off_tiles + 4 * (size_t)L.ntiles);
-    L.off_codes = align(L.off_coarse + 4 * (size_t)L.ncoarse_words);
+    L.off_coarse = align(L.off_mb + 8 * (size_t)L.W);
+    L.off_codes = align(L.off_coarse + 4 * (size_t)(kCoarseHead + L.ncoarse_words));
     L.ncodes = L.nvox;
     L.bytes = L.off_codes + (L.packed ? 4 : 8) * (size_t)L.nvox;   // at most every voxel occupied
     // the counting kernel reads pairs and codes through one buffer resource with 32-bit offsets
@@ -171,7 +169,7 @@ inline fc::CompactVol compact_view(void *buf, const CompactLayout &L, int32_t N,
     char *b = static_cast<char *>(buf);
     fc::CompactVol cv;
     cv.mb = reinterpret_cast<const uint2 *>(b + L.off_mb);
-    cv.coarse = reinterpret_cast<const uint32_t *>(b + L.off_coarse);
+    cv.coarse = reinterpret_cast<const uint32_t *>(b + L.off_coarse) + kCoarseHead;
     cv.csx = L.csx;
     cv.csyz = L.csyz;
     cv.CBX = L.CBX;
@@ -204,14 +202,28 @@ inline fc::Grid make_grid(const int32_t dims[3]) {
     return g;
 }
 
-// Builds the compact volume of (roi, lab) into `buf` (L.bytes, laid out by compact_layout) on `st`.
+// What the build expects zeroed in `buf`: the code count and the coarse map.
+inline int32_t *compact_zero_words(void *buf, const CompactLayout &L, int64_t *n) {
+    *n = kCoarseHead + L.ncoarse_words;
+    return reinterpret_cast<int32_t *>(static_cast<char *>(buf) + L.off_coarse);
+}
+
+// Builds the compact volume of (roi, lab) into `buf` (L.bytes, laid out by compact_layout) on `st`;
+// zeroed: compact_zero_words are zero already (by an earlier launch on `st`).
 inline hipError_t enqueue_compact_build(const int32_t *roi, const int32_t *lab, const int32_t dims[3], int32_t N,
-                                        int32_t M, const CompactLayout &L, void *buf, int cus, hipStream_t st) {
+                                        int32_t M, const CompactLayout &L, void *buf, int cus, hipStream_t st,
+                                        bool zeroed = false) {
     const fc::CompactVol cv = compact_view(buf, L, N, M);
     char *b = static_cast<char *>(buf);
-    return fc::launch_compact_build(roi, lab, make_grid(dims), N, M, cv, reinterpret_cast<uint32_t *>(b + L.off_mb),
-                                    b + L.off_codes, reinterpret_cast<uint32_t *>(b + L.off_tiles),
-                                    reinterpret_cast<uint32_t *>(b + L.off_coarse), L.W, cus, st);
+    int64_t nz = 0;
+    int32_t *zero = compact_zero_words(buf, L, &nz);
+    if (!zeroed) {
+        const hipError_t e = fc::launch_fill_i32(zero, nz, 0, cus, st);
+        if (e != hipSuccess) return e;
+    }
+    return fc::launch_compact_build(roi, lab, make_grid(dims), cv, reinterpret_cast<uint2 *>(b + L.off_mb),
+                                    b + L.off_codes, reinterpret_cast<uint32_t *>(zero) + kCoarseHead,
+                                    reinterpret_cast<uint32_t *>(zero), st);
 }
 
 inline int check_volume_args(const int32_t *roi, const int32_t *lab, const int32_t dims[3], int32_t N, int32_t M) {

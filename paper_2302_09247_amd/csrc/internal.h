@@ -27,8 +27,8 @@ struct RasterVol {
 };
 
 // Compact lookup: occupancy bits in 16x8x8 super-bricks (32 words of 32 voxels each), every
-// occupancy word paired with the number of occupied voxels before it (its rank base), and one
-// code per occupied voxel in that order.
+// occupancy word paired with the position of its first code (its rank base), and one code per
+// occupied voxel, those of one word in the order of its bits.
 struct CompactVol {
     const uint2 *mb;          // [W] {occupancy word, rank base}
     const uint32_t *coarse;   // one bit per (2^cs)^3 block: any occupied voxel inside
@@ -145,18 +145,19 @@ struct StreamSubject {
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, int cus, hipStream_t st);
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, int cus, hipStream_t st);
 
-// compact volume build: mb holds W {word, base} pairs, tile_sums ceil(W / kScanTile) words
-constexpr int kScanTile = 2048;
-hipError_t launch_compact_build(const int32_t *roi, const int32_t *lab, Grid g, int32_t N, int32_t M,
-                                CompactVol cv, uint32_t *mb, void *codes, uint32_t *tile_sums, uint32_t *coarse,
-                                int64_t W, int cus, hipStream_t st);
+// compact volume build: cv's layout and sizes, written through mb (W {word, base} pairs), codes and
+// coarse (ncoarse_words, zero on entry); ncodes: the number of codes written (zero on entry)
+hipError_t launch_compact_build(const int32_t *roi, const int32_t *lab, Grid g, CompactVol cv, uint2 *mb, void *codes,
+                                uint32_t *coarse, uint32_t *ncodes, hipStream_t st);
 
 // Per-call state zeroed by the partition launch, so that it needs no launches of its own: C when
 // it is not accumulated into, the pair histogram's tile cursors, a fixed scratch area's fallback bit
-// maps, the overflow and range counters.  Each range may be empty.
+// maps, the coarse map of a volume built by the same call, the overflow and range counters.  Each
+// range may be empty.
+constexpr int kZeroRanges = 4;
 struct ZeroRanges {
-    int32_t *w32[3] = {nullptr, nullptr, nullptr};
-    int64_t n32[3] = {0, 0, 0};
+    int32_t *w32[kZeroRanges] = {};
+    int64_t n32[kZeroRanges] = {};
     unsigned long long *w64 = nullptr;
     int64_t n64 = 0;
 };

@@ -4,7 +4,7 @@
 // rows it passes through (passthrough) and the set of target labels it passes through
 // (loc2region applied to its points) are formed, and every (row, label) pair of the two sets adds
 // one to C.  The stages here:
-//   * compact volume build: one read of both volumes -> occupancy bits + packed codes;
+//   * compact volume build: one pass over both volumes -> occupancy bits + packed codes;
 //   * partition: chunks of whole streamlines, equal or tapering (a binary search per chunk); the same
 //     launch zeroes the call's per-call state;
 //   * count kernels (wave-per-streamline over raster volumes, or flat point stream over the
@@ -488,307 +488,195 @@ hipError_t launch_fill_u64(unsigned long long *p, int64_t n, int cus, hipStream_
 // compact volume build
 // ---------------------------------------------------------------------------------------------
 
-// Occupancy word (index into the {word, base} pairs) and bit of voxel lin; false when the voxel
-// is not occupied (0 <= roi < N or 0 <= lab < M).
-__device__ __forceinline__ bool occupancy_bit(int32_t lin, int32_t r, int32_t m, const Grid &g, int32_t N, int32_t M,
-                                              int32_t SBX, int32_t SBXY, uint32_t &word, uint32_t &bit) {
-    if (!((unsigned)r < (unsigned)N || (unsigned)m < (unsigned)M)) return false;
-    const int32_t t = lin / g.X;
-    const int x = lin - t * g.X;
-    const int y = t % g.Y;
-    const int z = t / g.Y;
-    const uint32_t sb = (uint32_t)(x >> 4) + (uint32_t)SBX * (uint32_t)(y >> 3) + (uint32_t)SBXY * (uint32_t)(z >> 3);
-    const uint32_t b = (uint32_t)(x & 15) | ((uint32_t)(y & 7) << 4) | ((uint32_t)(z & 7) << 7);
-    word = (sb << 5) | (b >> 5);
-    bit = 1u << (b & 31u);
-    return true;
-}
-
-// Sets the occupancy bit of voxel lin.
-__device__ __forceinline__ void mark_voxel(int32_t lin, int32_t r, int32_t m, const Grid &g, int32_t N, int32_t M,
-                                           int32_t SBX, int32_t SBXY, uint32_t *mb) {
-    uint32_t w, bit;
-    if (occupancy_bit(lin, r, m, g, N, M, SBX, SBXY, w, bit)) atomicOr(&mb[2 * w], bit);
-}
-
-// Sets the occupancy bits of voxels lin0 .. lin0+3 with one atomic per run of them in one word
-// (four neighbours along x share a word unless a row or a 16-voxel run ends among them).
-__device__ __forceinline__ void mark_voxels4(int32_t lin0, const int32_t (&r)[4], const int32_t (&m)[4], const Grid &g,
-                                             int32_t N, int32_t M, int32_t SBX, int32_t SBXY, uint32_t *mb) {
-    uint32_t word = 0u, bits = 0u;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        uint32_t w, bit;
-        if (occupancy_bit(lin0 + q, r[q], m[q], g, N, M, SBX, SBXY, w, bit)) {
-            if (bits && w != word) {
-                atomicOr(&mb[2 * word], bits);
-                bits = 0u;
-            }
-            word = w;
-            bits |= bit;
-        }
-    }
-    if (bits) atomicOr(&mb[2 * word], bits);
-}
-
-// One pass over both volumes (X*Y*Z < 2^31): four voxels per thread and step with 16-byte loads
-// when both volumes are 16-byte aligned (VEC), else one.
-template <bool VEC>
-__global__ void k_compact_mark(const int32_t *__restrict__ roi, const int32_t *__restrict__ lab, Grid g,
-                               int32_t N, int32_t M, int32_t SBX, int32_t SBXY, uint32_t *__restrict__ mb) {
-    const int32_t nvox = g.X * g.Y * g.Z;
-    const int32_t stride = gridDim.x * blockDim.x;
-    if (VEC) {
-        const int32_t n4 = nvox >> 2;
-        typedef int32_t v4i __attribute__((ext_vector_type(4)));
-        const v4i *r4 = reinterpret_cast<const v4i *>(roi);
-        const v4i *m4 = reinterpret_cast<const v4i *>(lab);
-        // two groups of loads in flight before any mark: the marks are atomics, and on this
-        // architecture a wait for a later load also waits for every earlier atomic
-        for (int32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += 2 * stride) {
-            const int32_t i2 = i + stride;
-            const v4i r = __builtin_nontemporal_load(r4 + i), m = __builtin_nontemporal_load(m4 + i);
-            v4i r2 = {-1, -1, -1, -1}, m2 = {-1, -1, -1, -1};
-            if (i2 < n4) {
-                r2 = __builtin_nontemporal_load(r4 + i2);
-                m2 = __builtin_nontemporal_load(m4 + i2);
-            }
-            {
-                const int32_t ra[4] = {r.x, r.y, r.z, r.w}, ma[4] = {m.x, m.y, m.z, m.w};
-                mark_voxels4(4 * i, ra, ma, g, N, M, SBX, SBXY, mb);
-            }
-            {
-                const int32_t ra[4] = {r2.x, r2.y, r2.z, r2.w}, ma[4] = {m2.x, m2.y, m2.z, m2.w};
-                mark_voxels4(4 * i2, ra, ma, g, N, M, SBX, SBXY, mb);
-            }
-        }
-        for (int32_t lin = 4 * n4 + blockIdx.x * blockDim.x + threadIdx.x; lin < nvox; lin += stride)
-            mark_voxel(lin, roi[lin], lab[lin], g, N, M, SBX, SBXY, mb);
-    } else {
-        for (int32_t lin = blockIdx.x * blockDim.x + threadIdx.x; lin < nvox; lin += stride)
-            mark_voxel(lin, roi[lin], lab[lin], g, N, M, SBX, SBXY, mb);
-    }
-}
-
-// inclusive scan of one value per thread over a 256-thread block; returns the block total in `total`
-__device__ uint32_t block_scan_incl(uint32_t v, uint32_t *lds4, uint32_t &total) {
-    const int lane = lane_id(), w = threadIdx.x >> 6;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const uint32_t u = __shfl_up(v, d);
-        if (lane >= d) v += u;
-    }
-    if (lane == kWave - 1) lds4[w] = v;
-    __syncthreads();
-    uint32_t before = 0;
-    for (int k = 0; k < w; ++k) before += lds4[k];
-    total = lds4[0] + lds4[1] + lds4[2] + lds4[3];
-    __syncthreads();
-    return v + before;
-}
-
-constexpr int kWordsPerThread = kScanTile / kBlock;  // 8
-
-// Popcount of each kScanTile-word tile.  With `brick_coarse` (a coarse map of one bit per 16x8x8
-// super-brick, 32 words each) it also writes the map: tile b is super-bricks 64b .. 64b+63, words
-// 2b and 2b+1 of the map, four threads per super-brick.
-__global__ void k_compact_tile_sums(const uint32_t *__restrict__ mb, int64_t W, uint32_t *__restrict__ tile_sums,
-                                    uint32_t *__restrict__ brick_coarse) {
-    static_assert(kScanTile == 64 * 32 && kWordsPerThread * 4 == 32, "a tile is 64 super-bricks, 4 threads each");
-    __shared__ uint32_t lds4[4];
-    __shared__ uint32_t bits16[4];
-    const int64_t w0 = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kWordsPerThread;
-    uint32_t s = 0, any = 0;
-    for (int k = 0; k < kWordsPerThread; ++k)
-        if (w0 + k < W) {
-            const uint32_t wd = mb[2 * (w0 + k)];
-            s += __popc(wd);
-            any |= wd;
-        }
-    if (brick_coarse) {
-        // lanes 4q .. 4q+3 of a wavefront cover super-brick q of its 16
-        uint64_t occ = __ballot(any != 0u);
-        occ |= occ >> 1;
-        occ |= occ >> 2;
-        uint32_t b16 = 0u;
-        for (int q = 0; q < 16; ++q) b16 |= (uint32_t)((occ >> (4 * q)) & 1ull) << q;
-        if ((threadIdx.x & 63) == 0) bits16[threadIdx.x >> 6] = b16;
-    }
-    uint32_t total;
-    block_scan_incl(s, lds4, total);   // (its barriers also publish bits16)
-    if (threadIdx.x == 0) tile_sums[blockIdx.x] = total;
-    if (brick_coarse && threadIdx.x < 2)
-        brick_coarse[2 * blockIdx.x + threadIdx.x] = bits16[2 * threadIdx.x] | (bits16[2 * threadIdx.x + 1] << 16);
-}
-
-// one block: exclusive scan of the tile sums in place
-__global__ void k_compact_scan_tiles(uint32_t *__restrict__ tile_sums, int64_t ntiles) {
-    __shared__ uint32_t lds4[4];
-    uint32_t carry = 0;
-    for (int64_t a = 0; a < ntiles; a += kBlock) {
-        const int64_t i = a + threadIdx.x;
-        const uint32_t v = i < ntiles ? tile_sums[i] : 0u;
-        uint32_t total;
-        const uint32_t incl = block_scan_incl(v, lds4, total);
-        if (i < ntiles) tile_sums[i] = carry + incl - v;
-        carry += total;
-    }
-}
-
-// Rank base of every occupancy word: the number of occupied voxels in the words before it.
-// Rank bases of tile b's words.  kSumTiles: tile_base holds the tiles' popcounts, and the workgroup
-// sums those before b itself (for up to kBasesSumTiles tiles); else tile_base holds their scan.
-constexpr int64_t kBasesSumTiles = 1024;
-template <bool kSumTiles>
-__global__ void k_compact_bases(uint32_t *__restrict__ mb, const uint32_t *__restrict__ tile_base, int64_t W) {
-    __shared__ uint32_t lds4[4];
-    uint32_t tbase;
-    if (kSumTiles) {
-        uint32_t part = 0u;
-        for (int64_t t = threadIdx.x; t < (int64_t)blockIdx.x; t += blockDim.x) part += tile_base[t];
-        block_scan_incl(part, lds4, tbase);   // tbase = the sum over the workgroup
-    } else {
-        tbase = tile_base[blockIdx.x];
-    }
-    const int64_t w0 = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kWordsPerThread;
-    uint32_t words[kWordsPerThread];
-    uint32_t s = 0;
-    for (int k = 0; k < kWordsPerThread; ++k) {
-        words[k] = (w0 + k < W) ? mb[2 * (w0 + k)] : 0u;
-        s += __popc(words[k]);
-    }
-    uint32_t total;
-    uint32_t run = tbase + block_scan_incl(s, lds4, total) - s;
-    for (int k = 0; k < kWordsPerThread; ++k) {
-        if (w0 + k >= W) break;
-        mb[2 * (w0 + k) + 1] = run;
-        run += __popc(words[k]);
-    }
-}
-
-// Codes of the occupied voxels, in rank order.  A wavefront takes 64 words at a time and fills the
-// occupied ones two by two: word w covers x in [16 sbx, 16 sbx + 16) of rows y and y + 1 (y even) of
-// one z, so its 32 lanes read two runs of 16 consecutive voxels.
-// Occupancy words per wavefront group of the code fill: small, so that a solidly occupied region
-// (an ROI, a whole group of occupied words) is spread over many wavefronts.
-constexpr int kFillGroup = 16;
-
-template <bool PACKED>
-__global__ void k_compact_fill_codes(const uint32_t *__restrict__ mb, int64_t W, const int32_t *__restrict__ roi,
-                                     const int32_t *__restrict__ lab, Grid g, CompactVol cv, int32_t SBY,
-                                     void *__restrict__ codes) {
+// One pass over both volumes: each voxel is read once, and its occupancy bit, rank base and code are
+// written from registers.  A workgroup takes 8 super-bricks along x; each of its 8 wavefronts takes 64
+// voxels along x (4 super-bricks) of 8 rows and 2 slices: 4 steps of 4 rows, 4 voxels (16 bytes) per
+// lane.  Lane 16 r + q holds voxels 4 q .. 4 q + 3 of row r; the 8 lanes of a row pair and super-brick
+// (a group) share one occupancy word per step.  The workgroups' codes lie in the order in which they
+// reserve room for them (only each word's base has to know it), a workgroup's super-brick by
+// super-brick: the counting kernel's neighbouring lookups then share lines.
+//
+// Bound by the read of the volumes.  The five launches it replaces (zero fill, occupancy marks as
+// atomics, popcounts, scan, codes with a second read of the occupied voxels) had taken 71 us on a
+// 260x311x260 grid, 30 us on 145x174x145 and 18 us on 64^3.  A reservation and coarse bits of its own
+// for every wavefront took 75, 27 and 11 us: atomics on one line are served one after another.
+// kWide: rows of at least 4 voxels; a lane whose voxels pass the end of the row then takes its last 4
+// (16-byte loads need only the 4-byte alignment of the elements).
+// kNt: non-temporal loads, for volumes of more than kBuildCachedVoxels.  Cached, 168 MB of volumes
+// (260x311x260) displace the offsets and the zeroed C from the last-level cache, and the counting
+// kernel and the tile pass read them from memory: the build takes 35 instead of 42 us, the whole call
+// 2700 instead of 2644.  Small ones leave room: cached, 145x174x145 (29 MB) takes 395 instead of 397
+// us a call, and 64^3 20.5 instead of 21.0.
+// coarse[] and *ncodes are zero on entry.
+constexpr int kBuildSteps = 4;                   // steps of a wavefront: two a slice
+constexpr int kBuildParts = 16 / kBuildSteps;    // wavefronts per super-brick along z
+constexpr int kBuildWaves = 2 * kBuildParts;     // two 64-voxel chunks along x
+constexpr int64_t kBuildCachedVoxels = int64_t(1) << 23;   // 64 MB of volumes
+template <bool PACKED, bool kWide, bool kNt>
+__global__ void __launch_bounds__(kBuildWaves *kWave)
+k_compact_build(const int32_t *__restrict__ roi, const int32_t *__restrict__ lab, Grid g, CompactVol cv, int32_t SBY,
+                uint2 *__restrict__ mb, void *__restrict__ codes, uint32_t *__restrict__ coarse,
+                uint32_t *__restrict__ ncodes) {
+    __shared__ uint32_t s_cnt[8 * kBuildParts];   // codes of (super-brick, part)
+    __shared__ uint32_t s_any[kBuildWaves];       // occupied 8-voxel halves of a wavefront's super-bricks
+    __shared__ uint32_t s_base;
+    constexpr int kSteps = kBuildSteps;
     const int lane = lane_id();
-    const int64_t nwaves = (int64_t)gridDim.x * (blockDim.x / kWave);
-    for (int64_t grp = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x >> 6); grp * kFillGroup < W;
-         grp += nwaves) {
-        // lanes 0 .. kFillGroup-1 read the group's words; lane k then names word k in the loop below
-        const int64_t w = grp * kFillGroup + lane;
-        uint32_t word = 0u, base = 0u;
-        if (lane < kFillGroup && w < W) {
-            word = mb[2 * w];
-            base = mb[2 * w + 1];
-        }
-        uint64_t todo = __ballot(word != 0u);
-        while (todo) {
-            const int ka = __builtin_ctzll(todo);
-            todo &= todo - 1ull;
-            const int kb = todo ? __builtin_ctzll(todo) : ka;   // second word of the pair (or the first again)
-            if (todo) todo &= todo - 1ull;
-            const bool upper = lane >= 32;
-            const int k = upper ? kb : ka;
-            const uint32_t wda = (uint32_t)__builtin_amdgcn_readlane((int)word, ka);
-            const uint32_t wdb = (uint32_t)__builtin_amdgcn_readlane((int)word, kb);
-            const uint32_t bsa = (uint32_t)__builtin_amdgcn_readlane((int)base, ka);
-            const uint32_t bsb = (uint32_t)__builtin_amdgcn_readlane((int)base, kb);
-            const uint32_t wd = upper ? wdb : wda, bs = upper ? bsb : bsa;
-            const uint32_t j = (uint32_t)lane & 31u;
-            if (((wd >> j) & 1u) && !(upper && kb == ka)) {
-                const uint32_t ww = (uint32_t)(grp * kFillGroup + k);
-                const uint32_t sb = ww >> 5, wl = ww & 31u;
-                const uint32_t b = (wl << 5) | j;
-                const int x = (int)(sb % (uint32_t)cv.SBX) * 16 + (int)(b & 15u);
-                const int y = (int)((sb / (uint32_t)cv.SBX) % (uint32_t)SBY) * 8 + (int)((b >> 4) & 7u);
-                const int z = (int)(sb / (uint32_t)cv.SBXY) * 8 + (int)(b >> 7);
-                const int64_t lin = (int64_t)x + (int64_t)g.X * ((int64_t)y + (int64_t)g.Y * z);
-                const int32_t r = roi[lin], m = lab[lin];
-                const bool rv = (unsigned)r < (unsigned)cv.N, mv = (unsigned)m < (unsigned)cv.M;
-                const uint32_t at = bs + __popc(wd & ((1u << j) - 1u));
-                if (PACKED) {
-                    const uint32_t rf = rv ? (uint32_t)r : cv.rmask;
-                    const uint32_t mf = mv ? (uint32_t)m : (0xFFFFFFFFu >> cv.rbits);
-                    static_cast<uint32_t *>(codes)[at] = rf | (mf << cv.rbits);
-                } else {
-                    static_cast<int2 *>(codes)[at] = make_int2(rv ? r : -1, mv ? m : -1);
-                }
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int part = wv >> 1;
+    const int32_t nxg = (cv.SBX + 7) >> 3;
+    const int32_t xg = (int32_t)(blockIdx.x % (uint32_t)nxg), t = (int32_t)(blockIdx.x / (uint32_t)nxg);
+    const int32_t sby = t % SBY, sbz = t / SBY;
+    const int32_t xc = 2 * xg + (wv & 1);
+    const int q = lane & 15, rr = lane >> 4;
+    const int32_t x = xc * 64 + 4 * q;
+    const int32_t xs = kWide ? min(x, g.X - 4) : min(x, g.X - 1);
+    const int d = kWide ? x - xs : 0;   // elements below d belong to other lanes
+    uint32_t mine;                      // this lane's elements inside the row
+    if (x >= g.X) mine = 0u;
+    else mine = kWide ? (0xFu << d) & 0xFu : 0xFu >> max(0, x + 4 - g.X);
+    // codes in registers: packed (c0), or row and label (c0, c1)
+    uint32_t c0[kSteps][4], c1[PACKED ? 1 : kSteps][4];
+    uint32_t word[kSteps];
+    uint32_t occ = 0u;   // 4 bits a step: this lane's occupied elements
+    const int at_bit = 4 * (q & 3) + 16 * (rr & 1);
+#pragma unroll
+    for (int st = 0; st < kSteps; ++st) {
+        const int32_t y = sby * 8 + 4 * (st & 1) + rr, z = sbz * 8 + part * (kSteps / 2) + (st >> 1);
+        // (rows past the grid are read at its last row, and not occupied)
+        const int32_t row = g.X * (min(y, g.Y - 1) + g.Y * min(z, g.Z - 1));
+        int32_t r[4], m[4];
+        if (kWide) {
+            typedef int32_t v4i __attribute__((ext_vector_type(4), aligned(4)));
+            const v4i *pr = reinterpret_cast<const v4i *>(roi + (row + xs)), *pm = reinterpret_cast<const v4i *>(lab + (row + xs));
+            const v4i r4 = kNt ? __builtin_nontemporal_load(pr) : *pr, m4 = kNt ? __builtin_nontemporal_load(pm) : *pm;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                r[i] = r4[i];
+                m[i] = m4[i];
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int32_t xi = min(xs + i, g.X - 1);
+                r[i] = roi[row + xi];
+                m[i] = lab[row + xi];
             }
         }
-    }
-}
-
-// Coarse occupancy: bit of block (cx, cy, cz) of side 2^cs is set iff an occupancy word covering
-// it has a bit inside it.  One thread per block, 64 blocks per wavefront packed with a ballot.
-__global__ void k_compact_coarse(const uint32_t *__restrict__ mb, int32_t SBX, int32_t SBY, int32_t SBZ, int32_t csx,
-                                 int32_t csyz, int32_t CBX, int32_t CBY, int32_t CBZ, uint32_t *__restrict__ coarse) {
-    const int64_t ncb = (int64_t)CBX * CBY * CBZ;
-    const int64_t cb = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    bool occ = false;
-    if (cb < ncb) {
-        const int cx = (int)(cb % CBX);
-        const int64_t t = cb / CBX;
-        const int cy = (int)(t % CBY), cz = (int)(t / CBY);
-        if (csx == 3) {
-            // half of one 16x8x8 super-brick: x in [0,8) are bits 0-7 and 16-23 of each word
-            const uint32_t half = (cx & 1) ? 0xFF00FF00u : 0x00FF00FFu;
-            const int64_t sb = (cx >> 1) + (int64_t)SBX * (cy + (int64_t)SBY * cz);
-            for (int wl = 0; wl < 32; ++wl) occ |= (mb[2 * (sb * 32 + wl)] & half) != 0u;
-        } else {
-            // whole super-bricks: 1 << (csx - 4) in x, 1 << (csyz - 3) in y and z
-            const int fx = 1 << (csx - 4), fyz = 1 << (csyz - 3);
-            for (int sz = cz * fyz; sz < (cz + 1) * fyz && sz < SBZ; ++sz)
-                for (int sy = cy * fyz; sy < (cy + 1) * fyz && sy < SBY; ++sy)
-                    for (int sx = cx * fx; sx < (cx + 1) * fx && sx < SBX; ++sx) {
-                        const int64_t sb = sx + (int64_t)SBX * (sy + (int64_t)SBY * sz);
-                        for (int wl = 0; wl < 32; ++wl) occ |= mb[2 * (sb * 32 + wl)] != 0u;
-                    }
+        uint32_t o = 0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool rv = (unsigned)r[i] < (unsigned)cv.N, mv = (unsigned)m[i] < (unsigned)cv.M;
+            // (all ones: neither a row nor a label, as both fields hold a value that is none)
+            if (PACKED) {
+                c0[st][i] = (rv ? (uint32_t)r[i] : cv.rmask) |
+                            ((mv ? (uint32_t)m[i] : (0xFFFFFFFFu >> cv.rbits)) << cv.rbits);
+                o |= min(~c0[st][i], 1u) << i;
+            } else {
+                c0[st][i] = rv ? (uint32_t)r[i] : 0xFFFFFFFFu;
+                c1[st][i] = mv ? (uint32_t)m[i] : 0xFFFFFFFFu;
+                o |= min(~(c0[st][i] & c1[st][i]), 1u) << i;
+            }
         }
+        o &= (y < g.Y && z < g.Z) ? mine : 0u;
+        occ |= o << (4 * st);
+        uint32_t w = (o >> d) << at_bit;
+        w |= (uint32_t)__builtin_amdgcn_mov_dpp((int)w, 0xB1, 0xF, 0xF, true);   // quad_perm 1,0,3,2
+        w |= (uint32_t)__builtin_amdgcn_mov_dpp((int)w, 0x4E, 0xF, 0xF, true);   // quad_perm 2,3,0,1
+        w |= (uint32_t)__builtin_amdgcn_ds_swizzle((int)w, 0x401F);              // lane ^ 16
+        word[st] = w;
     }
-    const uint64_t bits = __ballot(occ);
-    const int64_t w = cb >> 6;   // this wavefront's 64 blocks
-    if ((threadIdx.x & 63) == 0) {
-        coarse[2 * w] = (uint32_t)bits;
-        coarse[2 * w + 1] = (uint32_t)(bits >> 32);
+    // codes of this part of each super-brick: its two groups' (rows 0, 1 and rows 2, 3 of a step)
+    uint32_t cnt = 0u, any = 0u;
+#pragma unroll
+    for (int st = 0; st < kSteps; ++st) {
+        cnt += (uint32_t)__popc(word[st]);
+        any |= word[st];
+    }
+    const uint32_t other = (uint32_t)__shfl_xor((int)cnt, 32);
+    const int sb = 4 * (wv & 1) + (q >> 2);   // super-brick within the workgroup
+    const uint64_t lo = __ballot((any & 0x00FF00FFu) != 0u), hi = __ballot((any & 0xFF00FF00u) != 0u);
+    if (rr == 0 && (q & 3) == 0) s_cnt[sb * kBuildParts + part] = cnt + other;
+    if (lane == 0) {
+        uint32_t halves = 0u;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {   // lanes 4 k (rows 0, 1) and 4 k + 32 (rows 2, 3) are super-brick k's
+            halves |= (uint32_t)(((lo | lo >> 32) >> (4 * k)) & 1ull) << (2 * k);
+            halves |= (uint32_t)(((hi | hi >> 32) >> (4 * k)) & 1ull) << (2 * k + 1);
+        }
+        s_any[wv] = halves;
+    }
+    __syncthreads();
+    uint32_t incl = lane < 8 * kBuildParts ? s_cnt[lane] : 0u;
+    const uint32_t own = incl;
+#pragma unroll
+    for (int k = 1; k < 8 * kBuildParts; k <<= 1) {
+        const uint32_t u = (uint32_t)__shfl_up((int)incl, k);
+        if (lane >= k) incl += u;
+    }
+    const uint32_t total = (uint32_t)__builtin_amdgcn_readlane((int)incl, 8 * kBuildParts - 1);
+    uint32_t base = (uint32_t)__shfl((int)(incl - own), sb * kBuildParts + part) + (rr >= 2 ? other : 0u);
+    if (total) {   // (uniform over the workgroup)
+        if (threadIdx.x == 0) {
+            s_base = atomicAdd(ncodes, total);
+            // coarse bits of the 16 halves: blocks of 8 << (csx - 3) voxels along x, one run of bits
+            uint32_t halves = 0u, bits = 0u;
+            for (int w = 0; w < kBuildWaves; ++w) halves |= s_any[w] << (8 * (w & 1));
+            for (int h = 0; h < 16; ++h) bits |= ((halves >> h) & 1u) << (h >> (cv.csx - 3));
+            const uint32_t cb = (uint32_t)((xg * 128) >> cv.csx) + (uint32_t)cv.CBX * (uint32_t)((sby * 8) >> cv.csyz) +
+                                (uint32_t)cv.CBXY * (uint32_t)((sbz * 8) >> cv.csyz);
+            const uint64_t run = (uint64_t)bits << (cb & 31u);
+            if ((uint32_t)run) atomicOr(&coarse[cb >> 5], (uint32_t)run);
+            if (run >> 32) atomicOr(&coarse[(cb >> 5) + 1], (uint32_t)(run >> 32));
+        }
+        __syncthreads();
+        base += s_base;
+    }
+    // each lane of a group writes the {word, base} pair of one step
+    const int32_t sbx = xc * 4 + (q >> 2);
+    const int sel = (q & 3) + 4 * (rr & 1);
+    uint32_t bases[kSteps];
+    uint2 pair = make_uint2(0u, 0u);
+#pragma unroll
+    for (int st = 0; st < kSteps; ++st) {
+        bases[st] = base;
+        base += (uint32_t)__popc(word[st]);
+        if (sel == st) pair = make_uint2(word[st], bases[st]);
+    }
+    if (sbx < cv.SBX && sel < kSteps)
+        mb[(((int64_t)sbx + (int64_t)cv.SBX * sby + (int64_t)cv.SBXY * sbz) << 5) + part * (2 * kSteps) +
+           2 * sel + (rr >> 1)] = pair;
+    if (!total) return;
+#pragma unroll
+    for (int st = 0; st < kSteps; ++st) {
+        const uint32_t o = (occ >> (4 * st)) & 0xFu;
+        if (!o) continue;
+        uint32_t at = bases[st] + (uint32_t)__popc(word[st] & ((1u << at_bit) - 1u));
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if ((o >> i) & 1u) {
+                if (PACKED) static_cast<uint32_t *>(codes)[at] = c0[st][i];
+                else static_cast<int2 *>(codes)[at] = make_int2((int)c0[st][i], (int)c1[PACKED ? 0 : st][i]);
+                ++at;
+            }
     }
 }
 
-hipError_t launch_compact_build(const int32_t *roi, const int32_t *lab, Grid g, int32_t N, int32_t M, CompactVol cv,
-                                uint32_t *mb, void *codes, uint32_t *tile_sums, uint32_t *coarse, int64_t W, int cus,
-                                hipStream_t st) {
-    const int64_t ntiles = (W + kScanTile - 1) / kScanTile;
+hipError_t launch_compact_build(const int32_t *roi, const int32_t *lab, Grid g, CompactVol cv, uint2 *mb, void *codes,
+                                uint32_t *coarse, uint32_t *ncodes, hipStream_t st) {
     const int32_t SBY = cv.SBXY / cv.SBX;
-    k_fill_i32<<<fill_blocks(2 * W, cus), kBlock, 0, st>>>(reinterpret_cast<int32_t *>(mb), 2 * W, 0);
-    const int64_t nvox = (int64_t)g.X * g.Y * g.Z;
-    const bool vec = ((reinterpret_cast<uintptr_t>(roi) | reinterpret_cast<uintptr_t>(lab)) & 15u) == 0;
-    if (vec) k_compact_mark<true><<<fill_blocks(nvox / 4, cus * 2), kBlock, 0, st>>>(roi, lab, g, N, M, cv.SBX, cv.SBXY, mb);
-    else k_compact_mark<false><<<fill_blocks(nvox, cus * 2), kBlock, 0, st>>>(roi, lab, g, N, M, cv.SBX, cv.SBXY, mb);
-    // the brick layout's coarse map (one bit per super-brick) comes from the tile sums pass
-    const bool brick = cv.csx == 4 && cv.csyz == 3;
-    k_compact_tile_sums<<<(unsigned)ntiles, kBlock, 0, st>>>(mb, W, tile_sums, brick ? coarse : nullptr);
-    if (ntiles <= kBasesSumTiles) {
-        k_compact_bases<true><<<(unsigned)ntiles, kBlock, 0, st>>>(mb, tile_sums, W);
-    } else {
-        k_compact_scan_tiles<<<1, kBlock, 0, st>>>(tile_sums, ntiles);
-        k_compact_bases<false><<<(unsigned)ntiles, kBlock, 0, st>>>(mb, tile_sums, W);
-    }
-    const int64_t groups = (W + kFillGroup - 1) / kFillGroup;
-    const unsigned fblocks = (unsigned)std::min<int64_t>((groups + kWavesPerBlock - 1) / kWavesPerBlock, (int64_t)cus * 8);
-    if (cv.packed) k_compact_fill_codes<true><<<fblocks, kBlock, 0, st>>>(mb, W, roi, lab, g, cv, SBY, codes);
-    else k_compact_fill_codes<false><<<fblocks, kBlock, 0, st>>>(mb, W, roi, lab, g, cv, SBY, codes);
-    const int32_t SBZ = (int32_t)(W / 32 / cv.SBXY);
-    const int32_t CBY = (g.Y + (1 << cv.csyz) - 1) >> cv.csyz, CBZ = (g.Z + (1 << cv.csyz) - 1) >> cv.csyz;
-    const int64_t nthreads = (int64_t)cv.ncoarse_words * 32;
-    if (!brick)
-        k_compact_coarse<<<(unsigned)((nthreads + kBlock - 1) / kBlock), kBlock, 0, st>>>(
-            mb, cv.SBX, SBY, SBZ, cv.csx, cv.csyz, cv.CBX, CBY, CBZ, coarse);
+    const int64_t SBZ = cv.W / 32 / cv.SBXY;
+    const unsigned blocks = (unsigned)((int64_t)((cv.SBX + 7) / 8) * SBY * SBZ);
+    const bool wide = g.X >= 4, nt = (int64_t)g.X * g.Y * g.Z > kBuildCachedVoxels;
+#define FC_BUILD(P_, W_, T_) \
+    k_compact_build<P_, W_, T_><<<blocks, kBuildWaves * kWave, 0, st>>>(roi, lab, g, cv, SBY, mb, codes, coarse, ncodes)
+    if (cv.packed && wide && nt) FC_BUILD(true, true, true);
+    else if (cv.packed && wide) FC_BUILD(true, true, false);
+    else if (cv.packed) FC_BUILD(true, false, false);
+    else if (wide && nt) FC_BUILD(false, true, true);
+    else if (wide) FC_BUILD(false, true, false);
+    else FC_BUILD(false, false, false);
+#undef FC_BUILD
     return hipGetLastError();
 }
 
@@ -799,18 +687,34 @@ hipError_t launch_compact_build(const int32_t *roi, const int32_t *lab, Grid g, 
 
 // Range that a streamline starting at point p belongs to: floor(n * h(p / P)), h the inverse of
 // g(x) = 1.5 x - 0.5 x^2, so the ranges shrink linearly from 1.5x to 0.5x the mean in the order they
-// are handed out and the last ones to start end close together.  Each step is monotone in p.
+// are handed out and the last ones to start end close together.  p counts to 24 bits (exact as a
+// float); each step, IEEE square root included, is monotone in p, as the table needs.
 struct RangeOf {
-    double inv_P, n;
+    int sh;
+    float inv_P, n;
+    int64_t P;
     int32_t last;
-    __device__ RangeOf(int64_t P, int64_t nparts)
-        : inv_P(P > 0 ? 1.0 / (double)P : 0.0), n((double)nparts), last((int32_t)nparts - 1) {}
+    __device__ RangeOf(int64_t points, int64_t nparts) : n((float)nparts), last((int32_t)nparts - 1) {
+        P = points > 0 ? points : 0;
+        sh = P >> 24 ? 40 - __clzll(P) : 0;
+        inv_P = P > 0 ? 1.0f / (float)(uint32_t)(P >> sh) : 0.0f;
+    }
     __device__ int32_t operator()(int64_t p) const {
-        const double u = fmin(fmax((double)p * inv_P, 0.0), 1.0);
-        const int32_t i = (int32_t)(n * (1.5 - sqrt(2.25 - 2.0 * u)));
+        const float u = fminf((float)(uint32_t)(clamp64(p, 0, P) >> sh) * inv_P, 1.0f);
+        const int32_t i = (int32_t)(n * (1.5f - sqrtf(2.25f - 2.0f * u)));
         return i < 0 ? 0 : (i > last ? last : i);
     }
 };
+
+// p[0 .. n) = 0 by the whole grid, 16 bytes a store
+__device__ __forceinline__ void grid_zero(int32_t *p, int64_t n, int64_t t0, int64_t stride) {
+    const int64_t head = min(n, (int64_t)((0u - (uint32_t)(reinterpret_cast<uintptr_t>(p) >> 2)) & 3u));
+    const int64_t n4 = (n - head) >> 2;
+    int4 *p4 = reinterpret_cast<int4 *>(p + head);
+    for (int64_t i = t0; i < n4; i += stride) p4[i] = make_int4(0, 0, 0, 0);
+    if (t0 < head) p[t0] = 0;
+    if (t0 < n - head - 4 * n4) p[head + 4 * n4 + t0] = 0;
+}
 
 // Bound by latency (and by the zero fill of C on large ones), so the offsets are read once, in order:
 // the thread of streamline s knows the ranges that begin with it, those in (range(s - 1), range(s)].
@@ -819,39 +723,45 @@ struct RangeOf {
 // whole wavefront.  first == nullptr: only the zero fills.
 __global__ void k_partition(const int64_t *__restrict__ offsets, int64_t S, int64_t nparts, int32_t *__restrict__ first,
                             ZeroRanges z) {
-    constexpr int kShort = 4;
+    constexpr int kShort = 2, kUnroll = 4;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
 #pragma unroll
-    for (int r = 0; r < 3; ++r)
-        for (int64_t i = t0; i < z.n32[r]; i += stride) z.w32[r][i] = 0;
+    for (int r = 0; r < kZeroRanges; ++r) grid_zero(z.w32[r], z.n32[r], t0, stride);
     for (int64_t i = t0; i < z.n64; i += stride) z.w64[i] = 0ull;
     if (!first) return;
     const int lane = lane_id();
     const RangeOf range_of(offsets[S], nparts);
-    for (int64_t b = t0 - lane; b <= S; b += stride) {   // (uniform over the wavefront)
-        const int64_t s = b + lane;
-        const int32_t hi = s < S ? range_of(offsets[s]) : (int32_t)nparts;
-        int32_t lo = __shfl_up(hi, 1);
-        if (lane == 0) lo = s > 0 ? range_of(offsets[s - 1]) : -1;
-        ++lo;
-        const bool mine = s <= S;
+    for (int64_t b0 = kUnroll * (t0 - lane); b0 <= S; b0 += kUnroll * stride) {   // (uniform over the wavefront)
+        int64_t off[kUnroll];
 #pragma unroll
-        for (int k = 0; k < kShort; ++k)
-            if (mine && lo + k <= hi) first[lo + k] = (int32_t)s;
-        uint64_t rest = __ballot(mine && lo + kShort <= hi);
-        while (rest) {
-            const int k = __builtin_ctzll(rest);
-            rest &= rest - 1ull;
-            const int32_t l = __builtin_amdgcn_readlane(lo, k), h = __builtin_amdgcn_readlane(hi, k);
-            for (int32_t i = l + kShort + lane; i <= h; i += kWave) first[i] = (int32_t)(b + k);
+        for (int j = 0; j < kUnroll; ++j) off[j] = offsets[min(b0 + j * kWave + lane, S)];
+        int32_t before = b0 > 0 ? range_of(offsets[b0 - 1]) : -1;   // range of the streamline before the wavefront's
+#pragma unroll
+        for (int j = 0; j < kUnroll; ++j) {
+            const int64_t s = b0 + j * kWave + lane;
+            const int32_t hi = s < S ? range_of(off[j]) : (int32_t)nparts;
+            const int32_t lo = __builtin_amdgcn_update_dpp(before, hi, 0x138, 0xF, 0xF, false) + 1;   // wave_shr:1
+            before = __builtin_amdgcn_readlane(hi, kWave - 1);
+            const bool mine = s <= S;
+#pragma unroll
+            for (int k = 0; k < kShort; ++k)
+                if (mine && lo + k <= hi) first[lo + k] = (int32_t)s;
+            uint64_t rest = __ballot(mine && lo + kShort <= hi);
+            while (rest) {
+                const int k = __builtin_ctzll(rest);
+                rest &= rest - 1ull;
+                const int32_t l = __builtin_amdgcn_readlane(lo, k), h = __builtin_amdgcn_readlane(hi, k);
+                for (int32_t i = l + kShort + lane; i <= h; i += kWave) first[i] = (int32_t)(b0 + j * kWave + k);
+            }
         }
     }
 }
 
 hipError_t launch_partition(const int64_t *offsets, int64_t S, int64_t nparts, int32_t *first, const ZeroRanges &z,
                             int cus, hipStream_t st) {
-    const int64_t n = std::max({first ? S + 1 : int64_t(1), z.n64, z.n32[0], z.n32[1], z.n32[2]});
+    int64_t n = std::max(first ? (S + 4) / 4 : int64_t(1), z.n64);
+    for (int64_t k : z.n32) n = std::max(n, (k + 3) / 4);
     k_partition<<<fill_blocks(n, cus), kBlock, 0, st>>>(offsets, S, nparts, first, z);
     return hipGetLastError();
 }
