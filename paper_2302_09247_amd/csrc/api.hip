@@ -32,10 +32,9 @@ struct Workspace {
     DevBuf fallback;    // fallback scratch (all-zero between launches)
     DevBuf flags;       // validation flags
     DevBuf ct;          // transposed accumulation copy of C (C beyond the histogram's tiles)
-    DevBuf ends;        // per-streamline end labels of the endpoint modes
     DevBuf pairs;       // appended C updates: slice lengths, tile histogram, slices, sorted copy
     void free_buffers() {
-        for (DevBuf *b : {&compact, &first, &ovf, &fallback, &flags, &ct, &ends, &pairs}) b->release();
+        for (DevBuf *b : {&compact, &first, &ovf, &fallback, &flags, &ct, &pairs}) b->release();
     }
 };
 
@@ -173,14 +172,14 @@ struct CountPlan {
     bool transposed = false;   // counted atomically into a transposed copy CT[M][N], then transposed
     bool zero_c = false;       // C overwritten (zeroed first)
     bool fused_zero = false;   // the partition launch does the zeroing
-    int nl = 0;                // end labels per streamline (endpoint modes)
+    bool ends = false;         // an endpoint mode
     int64_t NM = 0, ntiles = 0;
     int batch = 2;
     int64_t blocks = 0, nparts = 0, nwaves = 0, cap = 0;
     fc::FallbackScratch fs{};
     size_t off_hist = 0, off_pairs = 0, off_sorted = 0;
     // bytes of each scratch region (0 = not needed)
-    size_t ovf_bytes = 0, ct_bytes = 0, ends_bytes = 0, fb_bytes = 0, first_bytes = 0, pairs_bytes = 0;
+    size_t ovf_bytes = 0, ct_bytes = 0, fb_bytes = 0, first_bytes = 0, pairs_bytes = 0;
 };
 
 // Scratch regions of one call (device pointers, sized by CountPlan).  `fallback` must be all-zero,
@@ -189,7 +188,6 @@ struct CountScratch {
     bool zero_fallback = false;
     void *ovf = nullptr;        // overflow count, range counter (256 B), then the overflow queue
     int32_t *ct = nullptr;      // transposed copy of C
-    int32_t *ends = nullptr;    // end labels: last[S] (and first[S])
     uint32_t *fallback = nullptr;
     int32_t *first = nullptr;   // nparts + 1 range starts
     char *pairs = nullptr;      // slice lengths | tile histogram | slices | sorted copy
@@ -225,10 +223,7 @@ int make_count_plan(int64_t S, int32_t N, int32_t M, const fc::CompactVol *cv, c
     if (S == 0) return FASTCOD_OK;
     cp.ovf_bytes = fc::overflow_header_bytes(1) + 8 * (size_t)S;
     if (cp.transposed) cp.ct_bytes = 4 * (size_t)N * (size_t)M;
-    if (o.mode == FASTCOD_MODE_END || o.mode == FASTCOD_MODE_BOTH_ENDS) {
-        cp.nl = o.mode == FASTCOD_MODE_BOTH_ENDS ? 2 : 1;
-        cp.ends_bytes = 4 * (size_t)S * cp.nl;
-    }
+    cp.ends = o.mode == FASTCOD_MODE_END || o.mode == FASTCOD_MODE_BOTH_ENDS;
     if (!fallback_layout(N, M, max_fallback_bytes, cp.fs))
         return fail(FASTCOD_ENOMEM, "the overflow fallback's bit maps for this N and M exceed the scratch area");
     cp.fb_bytes = 4 * (size_t)cp.fs.stride * (size_t)cp.fs.blocks;
@@ -241,7 +236,7 @@ int make_count_plan(int64_t S, int32_t N, int32_t M, const fc::CompactVol *cv, c
     // wavefront's point ranges are long enough to amortise their deeper pipeline start
     const bool long_ranges = S >= kLongRangesFrom;
     cp.batch = o.batch != 0 ? o.batch : (long_ranges ? 4 : 2);
-    int per_cu = fc::count_stream_blocks_per_cu(o.scale != 1.0f, cv->packed != 0, cp.batch, cp.nl != 0, o.upsample,
+    int per_cu = fc::count_stream_blocks_per_cu(o.scale != 1.0f, cv->packed != 0, cp.batch, cp.ends, o.upsample,
                                                 4 * (size_t)cv->ncoarse_words);
     if (o.blocks_per_cu > 0 && o.blocks_per_cu < per_cu) per_cu = o.blocks_per_cu;
     cp.blocks = (int64_t)cus * per_cu;
@@ -287,9 +282,8 @@ int enqueue_count(const CountPlan &cp, const CountScratch &sc, int dev, const Vo
     auto build = [&](bool zeroed) {
         return enqueue_compact_build(vb->roi, vb->lab, vb->dims, N, M, *vb->L, vb->buf, cus, st, zeroed);
     };
-    // the partition launch zeroes what the build needs, so the build follows it, unless something
-    // before the partition reads the volume
-    const bool build_late = vb && !cp.seed_end && S > 0 && cp.nl == 0;
+    // the partition launch zeroes what the build needs, so the build follows it
+    const bool build_late = vb && !cp.seed_end && S > 0;
     if (vb && !build_late && S > 0) FC_HIP(build(false));
     if (cp.seed_end) {
         // Alg. 1's count: one update per streamline, straight into C
@@ -330,13 +324,7 @@ int enqueue_count(const CountPlan &cp, const CountScratch &sc, int dev, const Vo
         FC_HIP(fc::launch_fill_i32(a.C, cp.NM, 0, cus, st));
     }
     a.up = o.upsample;
-    a.ends = fc::EndLabels{0, nullptr, nullptr};
-    if (cp.nl > 0) {
-        int32_t *last = sc.ends;
-        int32_t *first = cp.nl == 2 ? last + S : nullptr;
-        a.ends = fc::EndLabels{o.mode, last, first};
-        FC_HIP(fc::launch_end_labels(a, rv, cv, o.mode, last, first, cus, st));
-    }
+    a.end_mode = cp.ends ? o.mode : 0;
     a.ovf.count = static_cast<unsigned long long *>(sc.ovf);
     a.ovf.list = reinterpret_cast<int64_t *>(static_cast<char *>(sc.ovf) + fc::overflow_header_bytes(1));
     a.ovf.cap = S;
@@ -408,10 +396,6 @@ int enqueue_count_ws(Workspace &ws, int dev, const VolumeBuild *vb, const float 
     if (cp.ct_bytes) {
         FC_HIP(ws.ct.ensure(cp.ct_bytes, false));
         sc.ct = static_cast<int32_t *>(ws.ct.p);
-    }
-    if (cp.ends_bytes) {
-        FC_HIP(ws.ends.ensure(cp.ends_bytes, false));
-        sc.ends = static_cast<int32_t *>(ws.ends.p);
     }
     if (cp.fb_bytes) {
         FC_HIP(ws.fallback.ensure(cp.fb_bytes, true));   // zeroed once; the fallback keeps it zero
@@ -549,8 +533,7 @@ int plan_enqueue(fastcod_plan &pl, int cus, hipStream_t st) {
     const int64_t header_words = (int64_t)(fc::overflow_header_bytes(fc::kBatchedKinds) / 8);
     if (pl.nitems == 0) FC_HIP(fc::launch_fill_u64(pl.ovf.count, header_words, cus, st));
     const int32_t *kl = pl.kind_lo;
-    const int ends = (int)fc::BatchedKind::kEnds, seed = (int)fc::BatchedKind::kSeedEnd;
-    FC_HIP(fc::launch_end_labels_batched(subs, kl[ends], kl[ends + 1] - kl[ends], cus, st));
+    const int seed = (int)fc::BatchedKind::kSeedEnd;
     if (pl.nitems > 0) {
         FC_HIP(fc::launch_partition_batched(subs, static_cast<const int64_t *>(pl.d_item_base.p), pl.n, pl.nitems,
                                             static_cast<int2 *>(pl.d_items.p), pl.ovf.count, header_words, cus, st));
@@ -659,7 +642,6 @@ int plan_build(const fastcod_subject *subjects, int32_t n, uint32_t flags, const
     };
     std::map<Key, fc::CompactVol> built;
     int64_t total_s = 0, max_nw_n = 1, max_nw_m = 1, max_m = 1;
-    size_t ends_words = 0;
     for (int32_t t = 0; t < n; ++t) {
         const int32_t k = order[t];
         const fastcod_subject &u = subjects[k];
@@ -696,11 +678,7 @@ int plan_build(const fastcod_subject *subjects, int32_t n, uint32_t flags, const
         ss.C = u.C_out;
         ss.si = (uint32_t)u.M;
         ss.sm = 1u;
-        ss.ends = fc::EndLabels{0, nullptr, nullptr};
-        if (o.mode == FASTCOD_MODE_END || o.mode == FASTCOD_MODE_BOTH_ENDS) {
-            ss.ends.mode = o.mode;   // label arrays placed below
-            ends_words += (size_t)u.n_streamlines * (o.mode == FASTCOD_MODE_BOTH_ENDS ? 2 : 1);
-        }
+        ss.end_mode = o.mode == FASTCOD_MODE_END || o.mode == FASTCOD_MODE_BOTH_ENDS ? o.mode : 0;
         ss.up = o.upsample;
         pl->subs.push_back(ss);
         pl->sizes.push_back((int64_t)u.N * u.M);
@@ -708,23 +686,6 @@ int plan_build(const fastcod_subject *subjects, int32_t n, uint32_t flags, const
         max_nw_n = std::max<int64_t>(max_nw_n, (u.N + 31) / 32);
         max_nw_m = std::max<int64_t>(max_nw_m, (u.M + 31) / 32);
         max_m = std::max<int64_t>(max_m, u.M);
-    }
-    // end labels of the endpoint-mode subjects: one plan-owned allocation, last[S] (and first[S]) each
-    if (ends_words > 0) {
-        void *buf = nullptr;
-        hipError_t e = hipMalloc(&buf, 4 * ends_words);
-        if (e != hipSuccess) return fail(FASTCOD_ENOMEM, std::string("hipMalloc: ") + hipGetErrorString(e));
-        pl->volumes.push_back(buf);
-        int32_t *p = static_cast<int32_t *>(buf);
-        for (auto &ss : pl->subs) {
-            if (ss.ends.mode == 0) continue;
-            ss.ends.last = p;
-            p += ss.S;
-            if (ss.ends.mode == FASTCOD_MODE_BOTH_ENDS) {
-                ss.ends.first = p;
-                p += ss.S;
-            }
-        }
     }
     // point counts (the item split follows them)
     pl->points.assign(n, 0);
@@ -1062,7 +1023,6 @@ int fastcod_volume_count_noalloc(const fastcod_volume *vol, const float *points,
     CountScratch sc;
     sc.ovf = take(cp.ovf_bytes);
     sc.ct = reinterpret_cast<int32_t *>(take(cp.ct_bytes));
-    sc.ends = reinterpret_cast<int32_t *>(take(cp.ends_bytes));
     sc.fallback = reinterpret_cast<uint32_t *>(take(cp.fb_bytes));
     sc.first = reinterpret_cast<int32_t *>(take(cp.first_bytes));
     sc.pairs = take(cp.pairs_bytes);

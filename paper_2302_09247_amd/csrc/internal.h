@@ -102,15 +102,8 @@ struct FallbackScratch {
 
 // C is addressed as C[i * si + m * sm]: row-major [N][M] (si = M, sm = 1) or the transposed
 // accumulation layout [M][N] (si = 1, sm = N); N * M < 2^31.
-// Target labels of the endpoint modes.  mode 0: every point's label (pass-through); mode 1: the
-// label of each streamline's last point only; mode 2: the labels of its first and last points.
-// last[s] / first[s]: those labels per streamline (-1 = none), computed before the count.
-struct EndLabels {
-    int32_t mode;
-    const int32_t *last;
-    const int32_t *first;
-};
-
+// end_mode 0: every point's label counts (pass-through); 1: the label of each streamline's last point
+// only; 2: the labels of its first and last points.
 struct CountArgs {
     const float *pts;
     const int64_t *offsets;
@@ -120,7 +113,7 @@ struct CountArgs {
     int32_t *C;
     uint32_t si, sm;
     Overflow ovf;
-    EndLabels ends;
+    int32_t end_mode;
     int32_t up;   // upsampling factor: up - 1 points inserted between neighbouring points (1 = none)
 };
 
@@ -137,7 +130,7 @@ struct StreamSubject {
     CompactVol cv;
     int32_t *C;
     uint32_t si, sm;
-    EndLabels ends;
+    int32_t end_mode;
     int32_t up;   // upsampling factor (1 = none)
 };
 
@@ -176,10 +169,6 @@ struct Ranges {
 int count_stream_blocks_per_cu(bool scaled, bool packed, int batch, bool ends, int up, size_t dyn_lds);
 
 hipError_t launch_count_wave(const CountArgs &a, const RasterVol &rv, int blocks, hipStream_t st);
-// endpoint modes: last[s] (and, mode 2, first[s]) = label of streamline s's last (first) point,
-// looked up in the raster volume when rv is given, else in the compact volume cv
-hipError_t launch_end_labels(const CountArgs &a, const RasterVol *rv, const CompactVol *cv, int mode, int32_t *last,
-                             int32_t *first, int cus, hipStream_t st);
 // parcellation outputs of C [N][M]: label [N], frac [N][M], sums [N] (each may be null)
 hipError_t launch_parcellate(const int32_t *C, int32_t N, int32_t M, int32_t *label, float *frac, int64_t *sums,
                              int cus, hipStream_t st);
@@ -225,7 +214,7 @@ hipError_t launch_zero_subjects(const StreamSubject *subs, const int64_t *sizes,
 hipError_t launch_partition_batched(const StreamSubject *subs, const int64_t *item_base, int32_t nsub, int64_t nitems,
                                     int2 *items, unsigned long long *zero, int64_t nzero, int cus, hipStream_t st);
 // Kinds of subject of the batched form, each counted by its own launch (subjects of one kind are
-// neighbours in the descriptor table): pass-through, endpoint modes 1/2 (end labels first),
+// neighbours in the descriptor table): pass-through, endpoint modes 1/2,
 // upsampled pass-through (u = 2, or u = 3..4), Alg. 1's seed-to-end count (no work items).
 enum class BatchedKind : int { kPass = 0, kEnds = 1, kUp2 = 2, kUp4 = 3, kSeedEnd = 4 };
 constexpr int kBatchedKinds = 5;
@@ -239,8 +228,6 @@ int count_batched_blocks_per_cu(int batch, int coarse_words, BatchedKind kind = 
 // items[0, nitems) of subjects of one kind (kPass, kEnds, kUp2, kUp4)
 hipError_t launch_count_batched(const StreamSubject *subs, const int2 *items, int64_t nitems, const Overflow &ovf,
                                 int32_t coarse_words, int blocks, int batch, BatchedKind kind, hipStream_t st);
-// table entries [lo, lo + n): end labels of their streamlines [s_begin, S) (entries in an endpoint mode)
-hipError_t launch_end_labels_batched(const StreamSubject *subs, int32_t lo, int32_t n, int cus, hipStream_t st);
 // table entries [lo, lo + n): Alg. 1's count of their streamlines [s_begin, S)
 hipError_t launch_count_seed_end_batched(const StreamSubject *subs, int32_t lo, int32_t n, int cus, hipStream_t st);
 hipError_t launch_fallback_batched(const StreamSubject *subs, int32_t nsub, const Overflow &ovf, FallbackScratch fs,

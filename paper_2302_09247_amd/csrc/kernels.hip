@@ -126,6 +126,15 @@ struct CompactLookup {
     __device__ void get(int ix, int iy, int iz, int &r, int &m) const { compact_get(v, ix, iy, iz, r, m); }
 };
 
+// Row and label of the point at p (-1: none).
+template <typename Lookup, bool SCALED>
+__device__ __forceinline__ void lookup_point(const float *p, float scale, const Grid &g, const Lookup &lk, int &r,
+                                             int &m) {
+    int ix, iy, iz;
+    r = m = -1;
+    if (voxelise<SCALED>(p[0], p[1], p[2], scale, g, ix, iy, iz)) lk.get(ix, iy, iz, r, m);
+}
+
 // ---------------------------------------------------------------------------------------------
 // per-wavefront set of the open streamline's distinct keys (LDS, open addressing)
 //   key = row for ROI hits, label | kLabelTag for target hits (rows and labels are < 2^31 - 1)
@@ -782,7 +791,7 @@ __global__ void __launch_bounds__(kBlock) k_count_wave(CountArgs a, RasterVol rv
     DirectSink sink{a.C};
     const int64_t Ptot = a.offsets[a.S] > 0 ? a.offsets[a.S] : 0;
     const int64_t nw = (int64_t)gridDim.x * kWavesPerBlock;
-    const bool endmode = a.ends.mode != 0;   // endpoint modes: labels come from a.ends at the close
+    const bool endmode = a.end_mode != 0;   // endpoint modes: the labels are looked up at the close
     const int up = a.up < 1 ? 1 : (a.up > kMaxUp ? kMaxUp : a.up);   // upsampling factor
     for (int64_t s = (int64_t)blockIdx.x * kWavesPerBlock + wv; s < a.S; s += nw) {
         const int64_t b0 = clamp64(a.offsets[s], 0, Ptot);
@@ -865,7 +874,11 @@ __global__ void __launch_bounds__(kBlock) k_count_wave(CountArgs a, RasterVol rv
             }
         }
         if (endmode && !set.skip && set.nI > 0) {
-            const int ml = a.ends.last[s], mf = a.ends.mode == 2 ? a.ends.first[s] : -1;
+            // (rows were found, so the streamline has points)
+            int r, ml, mf = -1;
+            const RasterLookup lk{rv};
+            lookup_point<RasterLookup, SCALED>(a.pts + 3 * (b1 - 1), a.scale, a.g, lk, r, ml);
+            if (a.end_mode == 2) lookup_point<RasterLookup, SCALED>(a.pts + 3 * b0, a.scale, a.g, lk, r, mf);
             const uint64_t cand = __ballot((lane == 0 && ml >= 0) || (lane == 1 && mf >= 0 && mf != ml));
             if (cand && !set.add(0ull, 0, cand, lane == 0 ? ml : mf)) {
                 push_overflow(a.ovf, b0);
@@ -924,13 +937,6 @@ __device__ __forceinline__ int64_t uniform64(int64_t v) {
     return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// A wave-uniform read of memory that no launch in flight writes (the end labels, filled by an
-// earlier launch), through the scalar data cache: a vector load would make the wavefront wait for
-// every gather and point load it has in flight, as vector-memory loads complete in issue order.
-__device__ __forceinline__ int32_t uniform_const_load(const int32_t *p, int64_t i) {
-    return ((const __attribute__((address_space(4))) int32_t *)p)[i];
-}
-
 // Next point range (work item) of wavefront `wave`: queue c = wave mod Q holds ranges c, c + Q,
 // c + 2Q, ..., handed out in that order by its own counter (Q: kRangeQueues, or the largest power of
 // two not above the grid's wavefronts, so that every queue has wavefronts).
@@ -986,9 +992,11 @@ __device__ void stream_range(const StreamSubject &sub, const uint32_t *coarse, i
         return;
     }
     const uint32_t L = (uint32_t)(P1 - P0);   // points of the range; positions are relative to P0
-    // endpoint modes (kEnds instantiations only): no point contributes its label; each closing
-    // streamline gets its end labels
-    const bool endmode = kEnds && uniform32(sub.ends.mode) != 0;
+    // endpoint modes (kEnds instantiations only): no point contributes its label but a streamline's
+    // last (and, both_ends, its first); lab_prev is the label of the point before the window (or of
+    // the batch's last window's end), lab_first that of the open streamline's first point
+    const bool both_ends = kEnds && uniform32(sub.end_mode) == 2;
+    int lab_prev = -1, lab_first = -1;
     // upsampling (kUp > 1 instantiations): sub-point t = 1 .. up-1 of a point lies a_t = fl32(t/up)
     // of the way to the next point of its streamline, in scaled coordinates
     const int up = kUp > 1 ? uniform32(sub.up) : 1;
@@ -1014,9 +1022,9 @@ __device__ void stream_range(const StreamSubject &sub, const uint32_t *coarse, i
             nxt = (uint32_t)__builtin_amdgcn_readlane((int)voff, k0);
         }
     };
-    // starts in [wb, wend) (wend <= wb + 64) as lane bits relative to wb; consumes them.  `mult`
-    // (endpoint modes) counts the streamlines starting at each lane: empty streamlines share a start.
-    auto take_starts = [&](uint32_t wb, uint32_t wend, int &mult) -> uint64_t {
+    // starts in [wb, wend) (wend <= wb + 64) as lane bits relative to wb; consumes them (empty
+    // streamlines share a start)
+    auto take_starts = [&](uint32_t wb, uint32_t wend) -> uint64_t {
         uint64_t starts = 0;
         while (nxt < wend) {
             const uint64_t inwin = __ballot(lane >= k0) & __ballot(voff < wend);
@@ -1025,9 +1033,7 @@ __device__ void stream_range(const StreamSubject &sub, const uint32_t *coarse, i
             while (it) {
                 const int k = __builtin_ctzll(it);
                 it &= it - 1ull;
-                const int q = __builtin_amdgcn_readlane((int)qv, k);
-                starts |= 1ull << q;
-                if (endmode) mult += lane == q ? 1 : 0;
+                starts |= 1ull << __builtin_amdgcn_readlane((int)qv, k);
             }
             consumed(inwin);
         }
@@ -1037,12 +1043,9 @@ __device__ void stream_range(const StreamSubject &sub, const uint32_t *coarse, i
         while (nxt < limit) consumed(__ballot(lane >= k0) & __ballot(voff < limit));
     };
     load_starts();
-    // the open streamline is vb - 1 + k0: the last one whose start has been consumed
-    auto close_open = [&](int64_t id) {
-        if (endmode) {
-            id = id < s0 ? s0 : (id >= s1 ? s1 - 1 : id);
-            set.add_end_labels(uniform_const_load(sub.ends.last, id), sub.ends.mode == 2 ? uniform_const_load(sub.ends.first, id) : -1);
-        }
+    // the open streamline ends; ml: the label of its last point (endpoint modes)
+    auto close_open = [&](int ml) {
+        if (kEnds) set.add_end_labels(ml, both_ends ? lab_first : -1);
         set.close(sink, sub.si, sub.sm);
     };
     int last_r = -1, last_m = -1;
@@ -1163,10 +1166,11 @@ __device__ void stream_range(const StreamSubject &sub, const uint32_t *coarse, i
             // open streamline, whose hits all came earlier)
             const uint32_t bend = (w0 + BW < L) ? w0 + BW : L;
             if (nxt < bend) {
-                if (set.has_state()) close_open(vb - 1 + k0);
+                if (set.has_state()) close_open(nxt == w0 ? lab_prev : -1);
                 skip_starts(bend);
+                lab_first = -1;
             }
-            last_r = last_m = -1;
+            last_r = last_m = lab_prev = -1;
             return;
         }
 #pragma unroll
@@ -1175,12 +1179,13 @@ __device__ void stream_range(const StreamSubject &sub, const uint32_t *coarse, i
             if (wb >= L) break;
             const uint32_t wend = (wb + kWave < L) ? wb + kWave : L;
             // streamline starts inside this window -> bit q of `starts` for lane q
-            const int64_t id0 = vb - 1 + k0;   // the streamline open at the window's first point
-            int mult = 0;
-            const uint64_t starts = (nxt < wend) ? take_starts(wb, wend, mult) : 0ull;
+            const uint64_t starts = (nxt < wend) ? take_starts(wb, wend) : 0ull;
             if (fl[b] == 0ull) {
-                if (starts && set.has_state()) close_open(id0);
-                last_r = last_m = -1;
+                if (starts) {
+                    if (set.has_state()) close_open((starts & 1ull) ? lab_prev : -1);
+                    lab_first = -1;
+                }
+                last_r = last_m = lab_prev = -1;
                 continue;
             }
             // sub-points t >= 1 exist only where the next point continues the lane's streamline:
@@ -1198,7 +1203,7 @@ __device__ void stream_range(const StreamSubject &sub, const uint32_t *coarse, i
             for (int t = 0; t < kUp; ++t) {
                 const bool ok = t == 0 || in_mask(nextok);
                 rr[t] = ok ? r[b * kUp + t] : -1;
-                mm[t] = (ok && !endmode) ? m[b * kUp + t] : -1;
+                mm[t] = (ok && !kEnds) ? m[b * kUp + t] : -1;
             }
             // each lane's last counted sub-point (t = up - 1) precedes the next lane's point
             int rl = rr[0], ml = mm[0];
@@ -1236,19 +1241,25 @@ __device__ void stream_range(const StreamSubject &sub, const uint32_t *coarse, i
                     }
                 }
             };
+            int lab_last = lab_prev;   // label of the closing streamline's last point
+            if (kEnds) {
+                const int ml_in = m[b * kUp];   // the lanes' labels
+                lab_prev = __builtin_amdgcn_readlane(ml_in, (int)min(L - 1u - wb, (uint32_t)(kWave - 1)));
+                if (wb == 0u) lab_first = __builtin_amdgcn_readlane(ml_in, 0);
+            }
             if (!starts) {   // the whole window belongs to the open streamline
                 add(~0ull, wb);
                 continue;
             }
             int pos = 0;
-            int64_t id = id0;
             uint64_t st = starts;
             for (;;) {
                 const int end = st ? __builtin_ctzll(st) : kWave;
                 add(lanes_between(pos, end), wb + pos);
                 if (!st) break;
-                close_open(id);
-                if (endmode) id += __builtin_amdgcn_readlane(mult, end);
+                if (kEnds && end > 0) lab_last = __builtin_amdgcn_readlane(m[b * kUp], end - 1);
+                close_open(lab_last);
+                if (kEnds) lab_first = __builtin_amdgcn_readlane(m[b * kUp], end);
                 pos = end;
                 st &= st - 1ull;
             }
@@ -1324,7 +1335,7 @@ __device__ void stream_range(const StreamSubject &sub, const uint32_t *coarse, i
             rank[v] = rank2[v];
         }
     }
-    close_open(vb - 1 + k0);
+    close_open(lab_prev);
 }
 
 // Calls f(s0, s1) for the streamline ranges of wavefront `wave`: ranges [first[i], first[i + 1]) from
@@ -1415,7 +1426,7 @@ __global__ void __launch_bounds__(kBlock) k_count_stream_up(StreamSubject sub, O
 // counter; each wavefront keeps the coarse map of the subject it last worked on in its own LDS.
 // The scale is always applied (multiplying by 1.0f is exact), the code width is read per subject.
 // One instantiation per kind of subject: pass-through (kEnds false, kUp 1), the endpoint modes
-// (kEnds: labels from sub.ends at each close), and upsampled pass-through (kUp 2 or 4, with
+// (kEnds: end labels at each close), and upsampled pass-through (kUp 2 or 4, with
 // sub.up <= kUp); a launch takes the items of subjects of one kind only.
 template <int kBatch, bool kEnds, int kUp>
 __global__ void __launch_bounds__(kBlock) k_count_batched(const StreamSubject *__restrict__ subs,
@@ -1498,7 +1509,7 @@ static StreamSubject stream_subject(const CountArgs &a, const CompactVol &cv) {
     s.C = a.C;
     s.si = a.si;
     s.sm = a.sm;
-    s.ends = a.ends;
+    s.end_mode = a.end_mode;
     s.up = a.up;
     return s;
 }
@@ -1538,7 +1549,7 @@ hipError_t launch_count_stream(const CountArgs &a, const CompactVol &cv, const R
         else k_count_stream_up<4><<<blocks, kBlock, dyn, st>>>(sub, a.ovf, rg, po);
         return hipGetLastError();
     }
-    const bool ends = a.ends.mode != 0;
+    const bool ends = a.end_mode != 0;
     if (batch == 2) {
         if (ends) launch_stream_b<2, true>(a, cv, rg, blocks, po, st);
         else launch_stream_b<2, false>(a, cv, rg, blocks, po, st);
@@ -1593,7 +1604,7 @@ template <typename Lookup, bool SCALED>
 __device__ void fallback_streamline(const float *__restrict__ pts, const int64_t *__restrict__ offsets, int64_t S,
                                     const Grid &g, float scale, const Lookup &lk, int32_t *__restrict__ C, uint32_t si,
                                     uint32_t sm, int64_t p, uint32_t *bmN, uint32_t *bmM, uint32_t *labels,
-                                    int *s_nlab, const EndLabels &ends, int up) {
+                                    int *s_nlab, int end_mode, int up) {
     const int64_t Ptot = offsets[S] > 0 ? offsets[S] : 0;
     // streamline containing point p: the last s with offsets[s] <= p.  The offsets never decrease,
     // so of blockDim.x evenly spaced candidates the ones at or below p are a prefix of the threads,
@@ -1628,9 +1639,10 @@ __device__ void fallback_streamline(const float *__restrict__ pts, const int64_t
     };
     __syncthreads();
     // endpoint modes: the labels are the streamline's end labels
-    if (ends.mode != 0 && threadIdx.x == 0) {
-        const int ml = ends.last[lo], mf = ends.mode == 2 ? ends.first[lo] : -1;
-        int n = 0;
+    if (end_mode != 0 && threadIdx.x == 0 && nsub > 0) {
+        int r, ml, mf = -1, n = 0;
+        if (!sub_lookup<Lookup, SCALED>(pts, b0, nsub - 1, up, scale, g, lk, r, ml)) ml = -1;
+        if (end_mode == 2 && !sub_lookup<Lookup, SCALED>(pts, b0, 0, up, scale, g, lk, r, mf)) mf = -1;
         if (ml >= 0) atomicExch(&labels[n++], (uint32_t)ml);
         if (mf >= 0 && mf != ml) atomicExch(&labels[n++], (uint32_t)mf);
         *s_nlab = n;
@@ -1645,7 +1657,7 @@ __device__ void fallback_streamline(const float *__restrict__ pts, const int64_t
             }
         }
     };
-    if (ends.mode == 0) {
+    if (end_mode == 0) {
 #pragma unroll
         for (int j = 0; j < kFallbackCached; ++j) add_label(cm[j]);
         for (int64_t k = k_rest; k < nsub; k += blockDim.x) {
@@ -1705,7 +1717,7 @@ __global__ void __launch_bounds__(kBlock) k_fallback(CountArgs a, Lookup lk, Fal
     const int64_t nq_c = nq < a.ovf.cap ? nq : a.ovf.cap;
     for (int64_t q = blockIdx.x; q < nq_c; q += gridDim.x)
         fallback_streamline<Lookup, SCALED>(a.pts, a.offsets, a.S, a.g, a.scale, lk, a.C, a.si, a.sm,
-                                            a.ovf.list[q] & kPointMask, bmN, bmM, labels, &s_nlab, a.ends, a.up);
+                                            a.ovf.list[q] & kPointMask, bmN, bmM, labels, &s_nlab, a.end_mode, a.up);
 }
 
 // Batched fallback: the queue entry names its subject.
@@ -1724,41 +1736,13 @@ __global__ void __launch_bounds__(kBlock) k_fallback_batched(const StreamSubject
         const StreamSubject &sub = subs[subject];
         fallback_streamline<CompactLookup, true>(sub.pts, sub.offsets, sub.S, sub.g, sub.scale, CompactLookup{sub.cv},
                                                  sub.C, sub.si, sub.sm, e & kPointMask, bmN, bmM, labels, &s_nlab,
-                                                 sub.ends, sub.up);
+                                                 sub.end_mode, sub.up);
     }
 }
 
 // ---------------------------------------------------------------------------------------------
-// endpoint modes: per-streamline end labels; Alg. 1's seed-to-endpoint count
+// Alg. 1's seed-to-endpoint count
 // ---------------------------------------------------------------------------------------------
-
-template <typename Lookup, bool SCALED>
-__device__ __forceinline__ void lookup_point(const float *p, float scale, const Grid &g, const Lookup &lk, int &r,
-                                             int &m) {
-    int ix, iy, iz;
-    r = m = -1;
-    if (voxelise<SCALED>(p[0], p[1], p[2], scale, g, ix, iy, iz)) lk.get(ix, iy, iz, r, m);
-}
-
-// last[s] = label of streamline s's last point, first[s] (mode 2) = label of its first point; -1
-// for an empty streamline or a point without a label.  One thread per streamline.
-template <typename Lookup, bool SCALED>
-__global__ void k_end_labels(CountArgs a, Lookup lk, int32_t mode, int32_t *__restrict__ last,
-                             int32_t *__restrict__ first) {
-    const int64_t Ptot = a.offsets[a.S] > 0 ? a.offsets[a.S] : 0;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < a.S; s += stride) {
-        const int64_t b0 = clamp64(a.offsets[s], 0, Ptot);
-        const int64_t b1 = clamp64(a.offsets[s + 1], b0, Ptot);
-        int r, ml = -1, mf = -1;
-        if (b1 > b0) {
-            lookup_point<Lookup, SCALED>(a.pts + 3 * (b1 - 1), a.scale, a.g, lk, r, ml);
-            if (mode == 2) lookup_point<Lookup, SCALED>(a.pts + 3 * b0, a.scale, a.g, lk, r, mf);
-        }
-        last[s] = ml;
-        if (mode == 2) first[s] = mf;
-    }
-}
 
 // C(row of the first point, label of the last point) += 1 per streamline (the seed is the first
 // point).  One thread per streamline.
@@ -1775,22 +1759,6 @@ __global__ void k_count_seed_end(CountArgs a, Lookup lk) {
         lookup_point<Lookup, SCALED>(a.pts + 3 * (b1 - 1), a.scale, a.g, lk, r2, m2);
         if (r >= 0 && m2 >= 0) atomicAdd(a.C + (uint32_t)r * a.si + (uint32_t)m2 * a.sm, 1);
     }
-}
-
-template <typename Lookup>
-static void launch_end_labels_l(const CountArgs &a, const Lookup &lk, int mode, int32_t *last, int32_t *first,
-                                int cus, hipStream_t st) {
-    const unsigned blocks = fill_blocks(a.S, cus);
-    if (a.scale != 1.0f) k_end_labels<Lookup, true><<<blocks, kBlock, 0, st>>>(a, lk, mode, last, first);
-    else k_end_labels<Lookup, false><<<blocks, kBlock, 0, st>>>(a, lk, mode, last, first);
-}
-
-hipError_t launch_end_labels(const CountArgs &a, const RasterVol *rv, const CompactVol *cv, int mode, int32_t *last,
-                             int32_t *first, int cus, hipStream_t st) {
-    if (a.S <= 0) return hipSuccess;
-    if (rv) launch_end_labels_l(a, RasterLookup{*rv}, mode, last, first, cus, st);
-    else launch_end_labels_l(a, CompactLookup{*cv}, mode, last, first, cus, st);
-    return hipGetLastError();
 }
 
 template <typename Lookup>
@@ -1995,29 +1963,6 @@ hipError_t launch_count_batched(const StreamSubject *subs, const int2 *items, in
     return hipGetLastError();
 }
 
-// End labels of table entries [lo, lo + gridDim.y) in an endpoint mode: sub.ends.last[s] (and, mode 2,
-// sub.ends.first[s]) for streamlines [s_begin, S) of each, as k_end_labels for one subject.
-__global__ void k_end_labels_batched(const StreamSubject *__restrict__ subs, int32_t lo) {
-    const StreamSubject &sub = subs[lo + blockIdx.y];
-    const int mode = sub.ends.mode;
-    if (mode != 1 && mode != 2) return;
-    const int64_t Ptot = sub.offsets[sub.S] > 0 ? sub.offsets[sub.S] : 0;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const CompactLookup lk{sub.cv};
-    for (int64_t s = clamp64(sub.s_begin, 0, sub.S) + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < sub.S;
-         s += stride) {
-        const int64_t b0 = clamp64(sub.offsets[s], 0, Ptot);
-        const int64_t b1 = clamp64(sub.offsets[s + 1], b0, Ptot);
-        int r, ml = -1, mf = -1;
-        if (b1 > b0) {
-            lookup_point<CompactLookup, true>(sub.pts + 3 * (b1 - 1), sub.scale, sub.g, lk, r, ml);
-            if (mode == 2) lookup_point<CompactLookup, true>(sub.pts + 3 * b0, sub.scale, sub.g, lk, r, mf);
-        }
-        const_cast<int32_t *>(sub.ends.last)[s] = ml;   // the plan's or request's own label arrays
-        if (mode == 2) const_cast<int32_t *>(sub.ends.first)[s] = mf;
-    }
-}
-
 // Alg. 1's count for table entries [lo, lo + gridDim.y): C(row of the first point, label of the last
 // point) += 1 for streamlines [s_begin, S) of each, as k_count_seed_end for one subject.
 __global__ void k_count_seed_end_batched(const StreamSubject *__restrict__ subs, int32_t lo) {
@@ -2035,12 +1980,6 @@ __global__ void k_count_seed_end_batched(const StreamSubject *__restrict__ subs,
         lookup_point<CompactLookup, true>(sub.pts + 3 * (b1 - 1), sub.scale, sub.g, lk, r2, m2);
         if (r >= 0 && m2 >= 0) atomicAdd(sub.C + (uint32_t)r * sub.si + (uint32_t)m2 * sub.sm, 1);
     }
-}
-
-hipError_t launch_end_labels_batched(const StreamSubject *subs, int32_t lo, int32_t n, int cus, hipStream_t st) {
-    if (n <= 0) return hipSuccess;
-    k_end_labels_batched<<<dim3((unsigned)(cus > 0 ? cus : 64) * 2, (unsigned)n), kBlock, 0, st>>>(subs, lo);
-    return hipGetLastError();
 }
 
 hipError_t launch_count_seed_end_batched(const StreamSubject *subs, int32_t lo, int32_t n, int cus, hipStream_t st) {

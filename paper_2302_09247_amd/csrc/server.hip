@@ -175,7 +175,7 @@ class HipExecutor final : public fcs::Executor {
             kind_lo[k] = 0;
             for (const fcs::Chunk &c : chunks) kind_lo[k] += kind_of(c) < k ? 1 : 0;
         }
-        const int seed = (int)fc::BatchedKind::kSeedEnd, ends = (int)fc::BatchedKind::kEnds;
+        const int seed = (int)fc::BatchedKind::kSeedEnd;
         // fallback scratch for the largest volume of this launch
         int32_t maxN = 1, maxM = 1;
         for (const fcs::Chunk &c : chunks) {
@@ -203,11 +203,7 @@ class HipExecutor final : public fcs::Executor {
             ss.C = device_C(r);
             ss.si = (uint32_t)v.M;
             ss.sm = 1u;
-            ss.ends = fc::EndLabels{0, nullptr, nullptr};
-            if (r.mode == FASTCOD_MODE_END || r.mode == FASTCOD_MODE_BOTH_ENDS) {
-                int32_t *last = reinterpret_cast<int32_t *>(base_ + r.off_ends);
-                ss.ends = fc::EndLabels{r.mode, last, r.mode == FASTCOD_MODE_BOTH_ENDS ? last + r.S : nullptr};
-            }
+            ss.end_mode = r.mode == FASTCOD_MODE_END || r.mode == FASTCOD_MODE_BOTH_ENDS ? r.mode : 0;
             ss.up = r.up;
             int64_t ni = 0;
             if (k < kind_lo[seed]) {   // the seed-to-end kind takes no work items
@@ -226,9 +222,7 @@ class HipExecutor final : public fcs::Executor {
         const int64_t header_words = (int64_t)(fc::overflow_header_bytes(fc::kBatchedKinds) / 8);
         if (hip(hipMemcpyAsync(s.d_desc.p, s.h_desc, desc_base_off_ + 8 * (size_t)(n + 1), hipMemcpyHostToDevice, comp_),
                 "descriptor upload") ||
-            (nitems == 0 && hip(fc::launch_fill_u64(ovf_.count, header_words, cus_, comp_), "counter reset")) ||
-            hip(fc::launch_end_labels_batched(subs, kind_lo[ends], kind_lo[ends + 1] - kind_lo[ends], cus_, comp_),
-                "end labels"))
+            (nitems == 0 && hip(fc::launch_fill_u64(ovf_.count, header_words, cus_, comp_), "counter reset")))
             return FASTCOD_EHIP;
         if (nitems > 0) {
             if (hip(fc::launch_partition_batched(subs, d_base, n, nitems, static_cast<int2 *>(s.d_items.p), ovf_.count,

@@ -165,7 +165,6 @@ struct Request {
     int cancel_status = FASTCOD_ECANCELED;          // FASTCOD_ERANGE: offsets found decreasing at set-up
     int64_t t_submit = 0, t_admit = 0, t_done = 0;
     int64_t off_C = -1, off_offsets = -1, off_points = -1;
-    int64_t off_ends = -1;                           // end labels (endpoint modes): last[S] (and first[S])
     int64_t issued_s = 0, ready_s = 0, next_s = 0;
     std::deque<std::pair<Token, int64_t>> uploads;   // (token, streamline end) in issue order
     Token ready = 0;                                 // FASTCOD_REQ_AFTER_STREAM: the caller's stream at submission
@@ -264,18 +263,11 @@ class Core {
     }
     int32_t volume_count() const { return (int32_t)vols_.size(); }
 
-    // end labels a request keeps on the device (endpoint modes)
-    static uint64_t ends_bytes(int64_t S, int32_t mode) {
-        if (mode == FASTCOD_MODE_END) return 4 * (uint64_t)S;
-        if (mode == FASTCOD_MODE_BOTH_ENDS) return 8 * (uint64_t)S;
-        return 0;
-    }
     // Device bytes a request holds while admitted (volume excluded).
-    static uint64_t request_bytes(int64_t S, int64_t P, int32_t N, int32_t M, uint32_t flags, int32_t mode = 0) {
+    static uint64_t request_bytes(int64_t S, int64_t P, int32_t N, int32_t M, uint32_t flags) {
         uint64_t b = Arena::round(8 * (uint64_t)(S + 1));
         if (!(flags & FASTCOD_REQ_DEVICE_POINTS)) b += Arena::round(12 * (uint64_t)P);
         if (!(flags & FASTCOD_REQ_DEVICE_C)) b += Arena::round(4 * (uint64_t)N * (uint64_t)M);
-        if (ends_bytes(S, mode)) b += Arena::round(ends_bytes(S, mode));
         return b;
     }
 
@@ -307,7 +299,7 @@ class Core {
         if (P < 0) return set_err(err, FASTCOD_ERANGE, "offsets decrease");
         if (P > 0 && !q.points) return set_err(err, FASTCOD_EINVAL, "points is NULL");
         if (P >= (int64_t(1) << 47)) return set_err(err, FASTCOD_EINVAL, "too many points");
-        const uint64_t need = request_bytes(S, P, v->N, v->M, q.flags, q.mode) + Arena::round(v->bytes) +
+        const uint64_t need = request_bytes(S, P, v->N, v->M, q.flags) + Arena::round(v->bytes) +
                               Arena::round(v->tmp_bytes);
         if (need > arena_.size())
             return set_err(err, FASTCOD_ENOMEM, "request needs " + std::to_string(need) +
@@ -430,8 +422,7 @@ class Core {
         arena_.release(r.off_C);
         arena_.release(r.off_offsets);
         arena_.release(r.off_points);
-        arena_.release(r.off_ends);
-        r.off_C = r.off_offsets = r.off_points = r.off_ends = -1;
+        r.off_C = r.off_offsets = r.off_points = -1;
         if (r.ready) {
             ex_->release(r.ready);
             r.ready = 0;
@@ -553,10 +544,8 @@ class Core {
         if (v.off < 0) need += Arena::round(v.bytes) + Arena::round(v.tmp_bytes);
         if (!(r.flags & FASTCOD_REQ_DEVICE_POINTS)) need += Arena::round(12 * (uint64_t)r.P);
         if (!(r.flags & FASTCOD_REQ_DEVICE_C)) need += Arena::round(4 * (uint64_t)r.N * (uint64_t)r.M);
-        const uint64_t eb = ends_bytes(r.S, r.mode);
-        if (eb) need += Arena::round(eb);
         for (;;) {
-            int64_t offs[6] = {-1, -1, -1, -1, -1, -1};
+            int64_t offs[5] = {-1, -1, -1, -1, -1};
             bool ok = true;
             auto take = [&](int k, uint64_t bytes) {
                 if (!ok) return;
@@ -570,7 +559,6 @@ class Core {
             take(2, 8 * (uint64_t)(r.S + 1));
             if (!(r.flags & FASTCOD_REQ_DEVICE_POINTS)) take(3, 12 * (uint64_t)r.P);
             if (!(r.flags & FASTCOD_REQ_DEVICE_C)) take(4, 4 * (uint64_t)r.N * (uint64_t)r.M);
-            if (eb) take(5, eb);
             if (ok) {
                 if (v.off < 0) {
                     v.off = offs[0];
@@ -586,7 +574,6 @@ class Core {
                 r.off_offsets = offs[2];
                 r.off_points = offs[3];
                 r.off_C = offs[4];
-                r.off_ends = offs[5];
                 return true;
             }
             for (int64_t o : offs) arena_.release(o);
@@ -813,7 +800,7 @@ class Service {
                     info->t_admit_ns = r->t_admit;
                     info->t_done_ns = r->t_done;
                     info->chunks = r->chunks;
-                    info->device_bytes = (int64_t)Core::request_bytes(r->S, r->P, r->N, r->M, r->flags, r->mode);
+                    info->device_bytes = (int64_t)Core::request_bytes(r->S, r->P, r->N, r->M, r->flags);
                 }
                 const int st = r->status;
                 core_.forget(id);

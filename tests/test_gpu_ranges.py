@@ -54,3 +54,29 @@ def test_ranges(fc, S, giant):
         vol.count(dev[0], dev[1], mode=mode, out=out, noalloc=True, blocks_per_cu=1)
         torch.cuda.synchronize()
         np.testing.assert_array_equal(out.cpu().numpy().astype(np.int64), exp, err_msg="noalloc")
+
+
+@pytest.mark.parametrize("mode", [1, 2])
+@pytest.mark.parametrize("batch", [2, 4])
+def test_end_labels_at_window_edges(fc, mode, batch):
+    # streamlines whose ends lie on either side of the kernel's 64-point windows and of its batches,
+    # with stretches without any hit between hits (windows and batches that look nothing up)
+    vols = synth.volumes_interleaved64()
+    rng = np.random.default_rng(7 * mode + batch)
+    lens = rng.choice([0, 1, 2, 62, 63, 64, 65, 66, 127, 128, 129, 255, 256, 257], 3000)
+    off = np.zeros(lens.size + 1, np.int64)
+    off[1:] = np.cumsum(lens)
+    P = int(off[-1])
+    pts = (np.repeat(rng.uniform(4, 60, (P // 8 + 1, 3)), 8, axis=0)[:P] + rng.uniform(-2, 2, (P, 3))).astype(np.float32)
+    far = np.repeat(rng.random(P // 48 + 1) < 0.6, 48)[:P]
+    pts[far] += 1000.0
+    ends = np.concatenate([off[:-1][lens > 0], off[1:][lens > 0] - 1])
+    pts[ends] = np.where(far[ends, None], pts[ends] - 1000.0, pts[ends])   # most ends do hit
+    exp = oracle.count(pts, off, vols.roi, vols.lab, vols.N, vols.M, mode=mode)
+    assert exp.sum() > 1000
+    dev = [torch.from_numpy(a).cuda() for a in (pts, off, vols.roi, vols.lab)]
+    for kw in (dict(blocks_per_cu=1), dict()):
+        print(f"end labels mode={mode} batch={batch} {kw}", flush=True)
+        C = fc.count(*dev, vols.N, vols.M, mode=mode, variant=2, batch=batch, **kw)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(C.cpu().numpy().astype(np.int64), exp, err_msg=f"{kw}")
