@@ -32,7 +32,7 @@ struct Workspace {
     DevBuf fallback;    // fallback scratch (all-zero between launches)
     DevBuf flags;       // validation flags
     DevBuf ct;          // transposed accumulation copy of C (C beyond the histogram's tiles)
-    DevBuf pairs;       // appended C updates: slice lengths, tile histogram, slices, sorted copy
+    DevBuf pairs;       // appended C updates: slice lengths, run table, slices, sorted copy
     void free_buffers() {
         for (DevBuf *b : {&compact, &first, &ovf, &fallback, &flags, &ct, &pairs}) b->release();
     }
@@ -173,7 +173,8 @@ struct CountPlan {
     bool zero_c = false;       // C overwritten (zeroed first)
     bool fused_zero = false;   // the partition launch does the zeroing
     bool ends = false;         // an endpoint mode
-    int64_t NM = 0, ntiles = 0;
+    int64_t NM = 0;
+    fc::PairTiles tiles;
     int batch = 2;
     int64_t blocks = 0, nparts = 0, nwaves = 0, cap = 0;
     fc::FallbackScratch fs{};
@@ -190,7 +191,7 @@ struct CountScratch {
     int32_t *ct = nullptr;      // transposed copy of C
     uint32_t *fallback = nullptr;
     int32_t *first = nullptr;   // nparts + 1 range starts
-    char *pairs = nullptr;      // slice lengths | tile histogram | slices | sorted copy
+    char *pairs = nullptr;      // slice lengths | run table | slices | sorted copy
 };
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
@@ -214,9 +215,8 @@ int make_count_plan(int64_t S, int32_t N, int32_t M, const fc::CompactVol *cv, c
     // keeps the counting kernel 5-8% shorter; the whole call is then within a few percent either way.
     // An explicit pair_capacity keeps the pair buffer.
     cp.NM = (int64_t)N * M;
-    cp.ntiles = (cp.NM + (1 << fc::kPairTileLog2) - 1) >> fc::kPairTileLog2;
     const bool direct = o.pair_capacity == 0 && S < kDirectMaxStreamlines && cp.NM <= kDirectMaxEntries;
-    cp.append = cv != nullptr && S > 0 && cp.ntiles <= fc::kMaxPairTiles && !direct;
+    cp.append = cv != nullptr && S > 0 && cp.NM <= (int64_t)fc::kMaxPairTiles << fc::kMaxPairTileLog2 && !direct;
     cp.transposed = !noalloc && !cp.append && !direct && cv != nullptr && S > 0 && M > 1 && N >= 64;
     cp.zero_c = !(o.flags & FASTCOD_ACCUMULATE) && !cp.transposed;
     cp.fused_zero = cv != nullptr && S > 0;
@@ -253,12 +253,13 @@ int make_count_plan(int64_t S, int32_t N, int32_t M, const fc::CompactVol *cv, c
     cp.nwaves = cp.blocks * fc::kWavesPerBlock;
     int64_t total = o.pair_capacity > 0 ? o.pair_capacity : std::min<int64_t>(std::max<int64_t>(8 * S, 1 << 20), 1 << 28);
     total = std::min<int64_t>(std::min<int64_t>(total, INT32_MAX), max_pairs);
-    cp.cap = cp.append ? (total / cp.nwaves) & ~int64_t(3) : 0;   // 16-byte aligned slices
+    cp.cap = cp.append ? (total / cp.nwaves) & ~int64_t(7) : 0;   // slices 16-byte aligned, also in 16 bits
     if (cp.append) {
+        cp.tiles = fc::pair_tiles(cp.NM, S, cp.nwaves, cp.cap);
         cp.off_hist = align256(4 * (size_t)cp.nwaves);
-        cp.off_pairs = align256(cp.off_hist + 4 * (size_t)fc::pair_hist_words(cp.ntiles));
+        cp.off_pairs = align256(cp.off_hist + 4 * (size_t)cp.tiles.hist_words);
         cp.off_sorted = align256(cp.off_pairs + 4 * (size_t)(cp.nwaves * cp.cap));
-        cp.pairs_bytes = cp.off_sorted + 4 * (size_t)(cp.nwaves * cp.cap);
+        cp.pairs_bytes = cp.off_sorted + 2 * (size_t)(cp.nwaves * cp.cap);
     } else {
         cp.pairs_bytes = 4 * (size_t)cp.nwaves;   // slice lengths only (every update is an atomic)
     }
@@ -345,15 +346,11 @@ int enqueue_count(const CountPlan &cp, const CountScratch &sc, int dev, const Vo
             z.w32[0] = C;
             z.n32[0] = cp.NM;
         }
-        if (cp.append) {
-            z.w32[1] = reinterpret_cast<int32_t *>(pb + cp.off_hist);
-            z.n32[1] = fc::pair_hist_cursor_words(cp.ntiles);
-        }
         if (sc.zero_fallback) {
-            z.w32[2] = reinterpret_cast<int32_t *>(sc.fallback);
-            z.n32[2] = (int64_t)(cp.fb_bytes / 4);
+            z.w32[1] = reinterpret_cast<int32_t *>(sc.fallback);
+            z.n32[1] = (int64_t)(cp.fb_bytes / 4);
         }
-        if (build_late) z.w32[3] = compact_zero_words(vb->buf, *vb->L, &z.n32[3]);
+        if (build_late) z.w32[2] = compact_zero_words(vb->buf, *vb->L, &z.n32[2]);
         z.w64 = a.ovf.count;   // overflow count and range queues
         z.n64 = header_words;
         fc::Ranges rg;
@@ -366,11 +363,11 @@ int enqueue_count(const CountPlan &cp, const CountScratch &sc, int dev, const Vo
         if (o.event_begin) FC_HIP(hipEventRecord((hipEvent_t)o.event_begin, st));
         FC_HIP(fc::launch_count_stream(a, *cv, rg, (int)cp.blocks, cp.batch, po, st));
         if (o.event_end) FC_HIP(hipEventRecord((hipEvent_t)o.event_end, st));
-        FC_HIP(fc::launch_fallback_compact(a, *cv, fs, st));
         if (cp.append)
-            FC_HIP(fc::launch_pair_histogram(po, (int32_t)cp.nwaves, (int32_t)cp.ntiles, C, cp.NM,
+            FC_HIP(fc::launch_pair_histogram(po, (int32_t)cp.nwaves, cp.tiles, a, *cv, fs, C, cp.NM,
                                              reinterpret_cast<uint32_t *>(pb + cp.off_hist),
-                                             reinterpret_cast<uint32_t *>(pb + cp.off_sorted), cus, st));
+                                             reinterpret_cast<uint32_t *>(pb + cp.off_sorted), st));
+        else FC_HIP(fc::launch_fallback_compact(a, *cv, fs, st));
         if (cp.transposed) FC_HIP(fc::launch_transpose(a.C, C, N, M, (o.flags & FASTCOD_ACCUMULATE) != 0, st));
     } else {
         if (o.event_begin) FC_HIP(hipEventRecord((hipEvent_t)o.event_begin, st));

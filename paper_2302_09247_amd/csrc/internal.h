@@ -60,15 +60,33 @@ struct PairOut {
 };
 
 // Histogram of the appended updates into C, tile by tile in LDS.
-constexpr int kPairTileLog2 = 14;                   // 16K counters (64 KB of LDS) per tile of C
 constexpr int kMaxPairTiles = 4096;                 // up to 2^26 entries of C take this path
-// Workgroups (1024 threads) of the tile-count and scatter passes: 512, two per CU of a 256-CU
-// device, all resident at once.  Each keeps ntiles offsets; every tile cursor takes one atomic
-// per workgroup, so more workgroups mean a longer queue of atomics on each cursor (1024 measured
-// slower, 256 leave too few loads in flight).
-inline int pair_hist_blocks(int64_t ntiles) {
-    (void)ntiles;
-    return 512;
+constexpr int kMaxPairTileLog2 = 14;                // 16K counters (64 KB of LDS) per tile of C
+constexpr int kMinPairTileLog2 = 11;
+// Sorting workgroups (1024 threads): with up to 64 of the fallback beside them, two per CU of a 256-CU
+// device, all resident at once.
+constexpr int kPairBlocks = 448;
+constexpr int kPairRound = 16 * 1024;              // updates a workgroup sorts at a time
+struct PairTiles {
+    int32_t log2 = 0, n = 0, blocks = 0;   // entries per tile, tiles, sorting workgroups
+    int64_t hist_words = 0;                // round counts and run table
+};
+// The smallest tiles of which at most 512 cover C (one round of the tile pass), so that a small C is
+// spread over the chip too: a C of 564,000 entries in 35 tiles of 2^14 took 20 us, mostly in 35
+// workgroups' LDS atomics.
+// Sorting workgroups for about four updates a streamline, half a round each: fewer of them leave longer
+// runs to the tile pass.
+inline PairTiles pair_tiles(int64_t NM, int64_t S, int64_t nwaves, int64_t cap) {
+    PairTiles pt;
+    pt.log2 = kMinPairTileLog2;
+    while (pt.log2 < kMaxPairTileLog2 && ((NM + (int64_t(1) << pt.log2) - 1) >> pt.log2) > 512) ++pt.log2;
+    pt.n = (int32_t)((NM + (int64_t(1) << pt.log2) - 1) >> pt.log2);
+    int64_t blocks = (4 * S + kPairRound / 2 - 1) / (kPairRound / 2);
+    if (blocks < (nwaves + 63) / 64) blocks = (nwaves + 63) / 64;   // at most 64 slices each
+    pt.blocks = (int32_t)(blocks < kPairBlocks ? blocks : kPairBlocks);
+    const int64_t most = (nwaves + pt.blocks - 1) / pt.blocks * cap;   // updates of one workgroup
+    pt.hist_words = 2 * kPairBlocks + ((most + kPairRound - 1) / kPairRound * pt.blocks * (pt.n + 1) + 1) / 2;
+    return pt;
 }
 
 struct Overflow {
@@ -144,10 +162,9 @@ hipError_t launch_compact_build(const int32_t *roi, const int32_t *lab, Grid g, 
                                 uint32_t *coarse, uint32_t *ncodes, hipStream_t st);
 
 // Per-call state zeroed by the partition launch, so that it needs no launches of its own: C when
-// it is not accumulated into, the pair histogram's tile cursors, a fixed scratch area's fallback bit
-// maps, the coarse map of a volume built by the same call, the overflow and range counters.  Each
+// it is not accumulated into, a fixed scratch area's fallback bit maps, the coarse map of a volume built by the same call, the overflow and range counters.  Each
 // range may be empty.
-constexpr int kZeroRanges = 4;
+constexpr int kZeroRanges = 3;
 struct ZeroRanges {
     int32_t *w32[kZeroRanges] = {};
     int64_t n32[kZeroRanges] = {};
@@ -179,15 +196,11 @@ hipError_t launch_count_seed_end(const CountArgs &a, const RasterVol *rv, const 
 hipError_t launch_count_stream(const CountArgs &a, const CompactVol &cv, const Ranges &rg, int blocks, int batch,
                                const PairOut &po, hipStream_t st);
 // C[NM] += histogram of the updates in the slices (nwaves slices of po.cap entries, lengths in
-// po.counts), ntiles = ceil(NM / 16K).  hist: pair_hist_words(ntiles) words, of which the first
-// pair_hist_cursor_words(ntiles) (the tile cursors) must be zero on entry; sorted: nwaves * po.cap
-// words.
-hipError_t launch_pair_histogram(const PairOut &po, int32_t nwaves, int32_t ntiles, int32_t *C, int64_t NM,
-                                 uint32_t *hist, uint32_t *sorted, int cus, hipStream_t st);
-inline int64_t pair_hist_cursor_words(int64_t ntiles) { return 32 * ntiles; }   // one 128-byte line per tile
-inline int64_t pair_hist_words(int64_t ntiles) {
-    return 32 * (int64_t)kMaxPairTiles + kMaxPairTiles + 64 + pair_hist_blocks(ntiles) * ntiles;
-}
+// po.counts); before it, the overflow queue of `a` (as launch_fallback_compact).  pt: pair_tiles of the
+// same sizes; hist: pt.hist_words words; sorted: nwaves * po.cap 16-bit entries.
+hipError_t launch_pair_histogram(const PairOut &po, int32_t nwaves, const PairTiles &pt, const CountArgs &a,
+                                 const CompactVol &cv, FallbackScratch fs, int32_t *C, int64_t NM, uint32_t *hist,
+                                 uint32_t *sorted32, hipStream_t st);
 hipError_t launch_fallback_raster(const CountArgs &a, const RasterVol &rv, FallbackScratch fs,
                                   hipStream_t st);
 hipError_t launch_fallback_compact(const CountArgs &a, const CompactVol &cv, FallbackScratch fs,

@@ -12,7 +12,7 @@
 //     in a per-wavefront LDS hash set, and emit its |I| x |M| pair updates: the flat-stream
 //     kernel appends them to per-wavefront slices of a pair buffer, the others (and a full slice)
 //     add them into C with global atomics;
-//   * pair histogram: a counting sort of the appended updates by tile of C, then one LDS
+//   * pair histogram: the appended updates sorted by tile of C, workgroup by workgroup, then one LDS
 //     histogram per tile added into C;
 //   * fallback: streamlines with more distinct keys than the LDS set holds, one workgroup each,
 //     with global bit maps.
@@ -1707,17 +1707,23 @@ __device__ void fallback_streamline(const float *__restrict__ pts, const int64_t
 
 constexpr int64_t kPointMask = (int64_t(1) << kSubjectShift) - 1;
 
+// The overflow queue's streamlines, one per workgroup at a time (workgroups [0, fs.blocks)).
 template <typename Lookup, bool SCALED>
-__global__ void __launch_bounds__(kBlock) k_fallback(CountArgs a, Lookup lk, FallbackScratch fs) {
-    __shared__ int s_nlab;
+__device__ __forceinline__ void fallback_queue(const CountArgs &a, const Lookup &lk, const FallbackScratch &fs, int *s_nlab) {
     uint32_t *bmN = fs.words + (int64_t)blockIdx.x * fs.stride;
     uint32_t *bmM = bmN + fs.nwordsN;
     uint32_t *labels = bmM + fs.nwordsM;
     const int64_t nq = (int64_t)*a.ovf.count;
     const int64_t nq_c = nq < a.ovf.cap ? nq : a.ovf.cap;
-    for (int64_t q = blockIdx.x; q < nq_c; q += gridDim.x)
+    for (int64_t q = blockIdx.x; q < nq_c; q += fs.blocks)
         fallback_streamline<Lookup, SCALED>(a.pts, a.offsets, a.S, a.g, a.scale, lk, a.C, a.si, a.sm,
-                                            a.ovf.list[q] & kPointMask, bmN, bmM, labels, &s_nlab, a.end_mode, a.up);
+                                            a.ovf.list[q] & kPointMask, bmN, bmM, labels, s_nlab, a.end_mode, a.up);
+}
+
+template <typename Lookup, bool SCALED>
+__global__ void __launch_bounds__(kBlock) k_fallback(CountArgs a, Lookup lk, FallbackScratch fs) {
+    __shared__ int s_nlab;
+    fallback_queue<Lookup, SCALED>(a, lk, fs, &s_nlab);
 }
 
 // Batched fallback: the queue entry names its subject.
@@ -2092,11 +2098,11 @@ hipError_t launch_transpose_many(const TransposeJob *jobs, int32_t njobs, int64_
 }
 
 // ---------------------------------------------------------------------------------------------
-// histogram of appended C updates: a counting sort by tile of C, then one LDS histogram per tile
+// histogram of appended C updates: each workgroup sorts its own updates by tile of C, then one LDS
+// histogram per tile over every workgroup's run of it
 // ---------------------------------------------------------------------------------------------
 
 constexpr uint32_t kNoEntry = 0xFFFFFFFFu;   // never an update (updates index C: < 2^31)
-constexpr int kPairUnroll = 8;               // independent loads in flight per thread
 
 // Slices [w0, w1) of workgroup b out of nblk.
 __device__ __forceinline__ void slice_range(int32_t nwaves, int b, int nblk, int32_t &w0, int32_t &w1) {
@@ -2106,65 +2112,14 @@ __device__ __forceinline__ void slice_range(int32_t nwaves, int b, int nblk, int
 
 constexpr int kMaxSlicesPerBlock = 64;   // nblk >= nwaves / 64 (checked by the launcher)
 
-// Calls f(entry) for every update in this workgroup's slices, taken as one flat index range (pre:
-// LDS prefix of the slice lengths) so that every thread keeps kPairUnroll loads in flight.
-template <typename F>
-__device__ __forceinline__ void for_each_update(const PairOut &po, int32_t nwaves, uint32_t *pre, F &&f) {
-    int32_t w0, w1;
-    slice_range(nwaves, blockIdx.x, gridDim.x, w0, w1);
-    const int ns = w1 - w0;
-    if (threadIdx.x < (unsigned)ns) pre[threadIdx.x + 1] = min(po.counts[w0 + threadIdx.x], po.cap);
-    if (threadIdx.x == 0) pre[0] = 0u;
-    __syncthreads();
-    if (threadIdx.x == 0)
-        for (int k = 1; k <= ns; ++k) pre[k] += pre[k - 1];
-    __syncthreads();
-    const uint32_t total = pre[ns];
-    for (uint32_t k0 = threadIdx.x; k0 < total; k0 += kPairUnroll * blockDim.x) {
-        uint32_t v[kPairUnroll];
-#pragma unroll
-        for (int j = 0; j < kPairUnroll; ++j) {
-            const uint32_t k = k0 + j * blockDim.x;
-            v[j] = kNoEntry;
-            if (k < total) {
-                int lo = 0, hi = ns - 1;   // the slice holding flat index k: pre[lo] <= k < pre[lo + 1]
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (pre[mid] <= k) lo = mid;
-                    else hi = mid - 1;
-                }
-                v[j] = __builtin_nontemporal_load(po.pairs + (size_t)(w0 + lo) * po.cap + (k - pre[lo]));
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < kPairUnroll; ++j)
-            if (v[j] != kNoEntry) f(v[j]);
-    }
-}
-
-// Tile histogram of workgroup b's updates; reserves b's run inside each tile with one atomic on
-// the tile's cursor (cursors one 128-byte line apart): boff[b * ntiles + t] = offset of the run.
-__global__ void __launch_bounds__(1024) k_pair_tile_counts(PairOut po, int32_t nwaves, int32_t ntiles,
-                                                           uint32_t *__restrict__ cursor, uint32_t *__restrict__ boff) {
-    __shared__ uint32_t h[kMaxPairTiles];
-    __shared__ uint32_t pre[kMaxSlicesPerBlock + 1];
-    for (int t = threadIdx.x; t < ntiles; t += blockDim.x) h[t] = 0u;
-    __syncthreads();
-    for_each_update(po, nwaves, pre, [&](uint32_t e) {
-        const uint32_t t = e >> kPairTileLog2;
-        if (t < (uint32_t)ntiles) atomicAdd(&h[t], 1u);
-    });
-    __syncthreads();
-    for (int t = threadIdx.x; t < ntiles; t += blockDim.x)
-        boff[(size_t)blockIdx.x * ntiles + t] = h[t] ? atomicAdd(&cursor[32 * t], h[t]) : 0u;
-}
-
 // Exclusive scan of c[0 .. n) in LDS (n <= kMaxPairTiles) by a 1024-thread workgroup; thread i
-// owns entries 4i .. 4i+3 and gets their counts back in own[].  wsum: 16 words of LDS.
-__device__ __forceinline__ uint32_t block_scan_tiles(uint32_t *c, int32_t n, uint32_t (&own)[4], uint32_t *wsum) {
+// owns entries 4i .. 4i+3.  wsum: 16 words of LDS.  Every 2^every_log2-th entry of the scan, and the
+// total after them, also go to o[].
+__device__ __forceinline__ uint32_t block_scan_tiles(uint32_t *c, int32_t n, uint32_t *wsum, uint16_t *__restrict__ o,
+                                                     int every_log2) {
     static_assert(kMaxPairTiles == 4 * 1024, "four tiles per thread");
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    uint32_t s = 0u;
+    uint32_t s = 0u, own[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int t = 4 * tid + q;
@@ -2189,139 +2144,206 @@ __device__ __forceinline__ uint32_t block_scan_tiles(uint32_t *c, int32_t n, uin
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int t = 4 * tid + q;
-        if (t < n) c[t] = run;
+        if (t < n) {
+            c[t] = run;
+            if ((t & ((1 << every_log2) - 1)) == 0) o[t >> every_log2] = (uint16_t)run;
+        }
         run += own[q];
     }
+    if (tid == 0) o[n >> every_log2] = (uint16_t)total;
     return total;
 }
 
-constexpr int kScatterUnroll = 6;                      // loads in flight per thread (64 VGPRs in all)
-constexpr int kScatterRound = kScatterUnroll * 1024;   // updates staged in LDS per round
-
-// Each update into its tile's run of `sorted`, at workgroup b's reserved offset.  Every workgroup
-// first scans the tile totals (cursor[32 t]) into the tiles' bases; workgroup 0 also stores them in
-// base[0 .. ntiles] for the tile pass.  A round of up to kScatterRound updates is then grouped by
-// tile in LDS and the stores go out in that order, so neighbouring lanes write neighbouring entries
-// of a run instead of one entry per run each.  Two workgroups per CU: 64 VGPRs and 57.9 KB of LDS
-// each.
-__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8)))
-k_pair_scatter(PairOut po, int32_t nwaves, int32_t ntiles, const uint32_t *__restrict__ cursor,
-               uint32_t *__restrict__ base, const uint32_t *__restrict__ boff, uint32_t *__restrict__ sorted) {
-    __shared__ uint32_t cur[kMaxPairTiles];     // next entry of this workgroup's run in each tile
-    __shared__ uint32_t cnt[kMaxPairTiles];     // the round's count per tile, then its offset in stage
-    __shared__ uint32_t stage[kScatterRound];   // the round's updates, grouped by tile
+// Workgroups [0, fs.blocks): the overflow queue (the fallback of a pair-buffer call; it adds to C
+// atomically, and C is not touched otherwise before the tile pass).
+// Workgroups fs.blocks + b, b < nblk: the updates of slices [w0, w1) in rounds of up to kPairRound,
+// each round grouped by tile in LDS and written to sorted[] in that order, coalesced, as 16-bit indices
+// within their tile.  Round j of workgroup b starts at sorted[blk[b].y + j * kPairRound] and is run table
+// row j * nblk + b: off[row][t] = where its updates of tile t start in the round (off[row][ntiles]: its
+// end); blk[b].x = its rounds.
+//
+// Bound by latency on a million updates, by memory and LDS atomics on ten million.  A sort of all
+// updates at once (tile histograms and run reservations with an atomic per workgroup and tile, then a
+// pass that stored each update into its tile's run) took 26 us for 2M updates after a fallback launch
+// of 5 us, and 86 us after 12 us for 11M; here no workgroup waits for another, and the two passes over
+// the updates take 14 and 44 us with the fallback beside them.  Two workgroups per CU: 64 VGPRs and
+// 48.6 KB of LDS each.
+__global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8), amdgpu_num_sgpr(80)))
+k_pair_sort(PairOut po, int32_t nwaves, int32_t ntiles, int32_t tile_log2, int32_t nblk, uint2 *__restrict__ blk,
+            uint16_t *__restrict__ off, uint16_t *__restrict__ sorted, CountArgs a, CompactLookup lk, FallbackScratch fs) {
+    constexpr int kUnroll = 4;
+    __shared__ uint32_t cnt[kMaxPairTiles];                      // the round's count per bin, then its offset in stage
+    __shared__ __align__(16) uint16_t stage[kPairRound];         // the round's updates, grouped by tile
     __shared__ uint32_t pre[kMaxSlicesPerBlock + 1];
     __shared__ uint32_t wsum[16];
-    for (int t = threadIdx.x; t < ntiles; t += blockDim.x) cnt[t] = cursor[32 * t];   // tile totals
-    __syncthreads();
-    {
-        uint32_t own[4];
-        const uint32_t all = block_scan_tiles(cnt, ntiles, own, wsum);   // cnt: the tiles' bases
-        __syncthreads();
-        for (int t = threadIdx.x; t < ntiles; t += blockDim.x) {
-            cur[t] = cnt[t] + boff[(size_t)blockIdx.x * ntiles + t];
-            if (blockIdx.x == 0) base[t] = cnt[t];
-        }
-        if (blockIdx.x == 0 && threadIdx.x == 0) base[ntiles] = all;
-        __syncthreads();
-        for (int t = threadIdx.x; t < ntiles; t += blockDim.x) cnt[t] = 0u;
+    __shared__ int s_nlab;
+    if (blockIdx.x < (unsigned)fs.blocks) {
+        fallback_queue<CompactLookup, true>(a, lk, fs, &s_nlab);
+        return;
     }
+    const int b = (int)blockIdx.x - fs.blocks;
     int32_t w0, w1;
-    slice_range(nwaves, blockIdx.x, gridDim.x, w0, w1);
+    slice_range(nwaves, b, nblk, w0, w1);
     const int ns = w1 - w0;
-    if (threadIdx.x < (unsigned)ns) pre[threadIdx.x + 1] = min(po.counts[w0 + threadIdx.x], po.cap);
-    if (threadIdx.x == 0) pre[0] = 0u;
-    __syncthreads();
-    if (threadIdx.x == 0)
-        for (int k = 1; k <= ns; ++k) pre[k] += pre[k - 1];
+    if (threadIdx.x < kWave) {
+        const int lane = threadIdx.x;
+        uint32_t x = lane < ns ? min(po.counts[w0 + lane], po.cap) : 0u;   // (past ns: pre = the total)
+#pragma unroll
+        for (int d = 1; d < kWave; d <<= 1) {
+            const uint32_t y = __shfl_up(x, d);
+            if (lane >= d) x += y;
+        }
+        pre[lane + 1] = x;
+        if (lane == 0) pre[0] = 0u;
+    }
     __syncthreads();
     const uint32_t total = pre[ns];
-    for (uint32_t r0 = 0; r0 < total; r0 += kScatterRound) {   // uniform over the workgroup
-        uint32_t v[kScatterUnroll], rank[kScatterUnroll];
+    const uint32_t out0 = (uint32_t)w0 * po.cap;   // (nwaves * cap < 2^31, cap a multiple of 8)
+    const uint32_t *src = po.pairs + (size_t)w0 * po.cap;   // (at most 64 slices: 32-bit offsets)
+    // A tile has 2^copies_log2 neighbouring bins, a lane counts in the one of its number: neighbouring
+    // updates mostly share a tile, and atomics on one LDS word are served one after another.
+    const int copies_log2 = min(4, 31 - __clz(kMaxPairTiles / ntiles));
+    const int32_t nbins = ntiles << copies_log2;
+    const uint32_t copy = threadIdx.x & ((1u << copies_log2) - 1u);
+    auto bin = [&](uint32_t e) { return ((e >> tile_log2) << copies_log2) | copy; };
+    int row = b;
+    for (uint32_t r0 = 0; r0 < total; r0 += kPairRound, row += nblk) {   // uniform over the workgroup
+        for (int t = threadIdx.x; t < nbins; t += 1024) cnt[t] = 0u;
+        const uint32_t r1 = min(total, r0 + (uint32_t)kPairRound);
+        // f(update) for the round's updates, kUnroll loads in flight.  Both passes below load them (the
+        // second time from the caches): held in registers, the code is unrolled for all of them, and
+        // fetching it takes longer than running it.
+        auto for_each = [&](auto &&f) {
+#pragma unroll 1
+            for (uint32_t k0 = r0 + threadIdx.x; k0 < r1; k0 += kUnroll * 1024u) {
+                uint32_t v[kUnroll];
 #pragma unroll
-        for (int j = 0; j < kScatterUnroll; ++j) {
-            const uint32_t k = r0 + threadIdx.x + j * 1024u;
-            v[j] = kNoEntry;
-            if (k < total) {
-                int lo = 0, hi = ns - 1;   // the slice holding flat index k: pre[lo] <= k < pre[lo + 1]
-                while (lo < hi) {
-                    const int mid = (lo + hi + 1) >> 1;
-                    if (pre[mid] <= k) lo = mid;
-                    else hi = mid - 1;
+                for (int j = 0; j < kUnroll; ++j) {
+                    const uint32_t k = k0 + j * 1024u;
+                    int lo = 0;   // the slice holding flat index k: pre[lo] <= k < pre[lo + 1]
+#pragma unroll
+                    for (int d = kMaxSlicesPerBlock / 2; d > 0; d >>= 1) lo += pre[lo + d] <= k ? d : 0;
+                    v[j] = kNoEntry;
+                    if (k < r1) v[j] = src[(uint32_t)lo * po.cap + (k - pre[lo])];
                 }
-                v[j] = __builtin_nontemporal_load(po.pairs + (size_t)(w0 + lo) * po.cap + (k - pre[lo]));
+#pragma unroll
+                for (int j = 0; j < kUnroll; ++j)
+                    if ((v[j] >> tile_log2) < (uint32_t)ntiles) f(v[j]);   // (kNoEntry: no tile)
             }
-        }
-#pragma unroll
-        for (int j = 0; j < kScatterUnroll; ++j) {
-            const uint32_t t = v[j] >> kPairTileLog2;   // kNoEntry: t >= ntiles
-            if (t < (uint32_t)ntiles) rank[j] = atomicAdd(&cnt[t], 1u);
-            else v[j] = kNoEntry;
-        }
+        };
         __syncthreads();
-        uint32_t own[4];
-        const uint32_t n = block_scan_tiles(cnt, ntiles, own, wsum);   // cnt: offsets in stage
+        for_each([&](uint32_t e) { atomicAdd(&cnt[bin(e)], 1u); });
         __syncthreads();
-#pragma unroll
-        for (int j = 0; j < kScatterUnroll; ++j)
-            if (v[j] != kNoEntry) stage[cnt[v[j] >> kPairTileLog2] + rank[j]] = v[j];
+        const uint32_t n = block_scan_tiles(cnt, nbins, wsum, off + (size_t)row * (ntiles + 1), copies_log2);
         __syncthreads();
-        for (uint32_t i = threadIdx.x; i < n; i += 1024u) {
-            const uint32_t e = stage[i], t = e >> kPairTileLog2;
-            sorted[cur[t] + (i - cnt[t])] = e;
-        }
+        const uint32_t low = (1u << tile_log2) - 1u;
+        for_each([&](uint32_t e) { stage[atomicAdd(&cnt[bin(e)], 1u)] = (uint16_t)(e & low); });
         __syncthreads();
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int t = 4 * (int)threadIdx.x + q;
-            if (t < ntiles) {
-                cur[t] += own[q];
-                cnt[t] = 0u;
-            }
-        }
+        uint4 *dst = reinterpret_cast<uint4 *>(sorted + out0 + r0);   // (16-byte aligned: multiples of 8 entries)
+        for (uint32_t i = threadIdx.x; i < (n + 7) / 8; i += 1024u) dst[i] = reinterpret_cast<const uint4 *>(stage)[i];
         __syncthreads();
     }
+    if (threadIdx.x == 0) blk[b] = make_uint2((total + kPairRound - 1) / kPairRound, out0);
 }
 
-// One workgroup per tile: C[tile] += the histogram of the tile's updates.
-__global__ void __launch_bounds__(512) k_pair_tile_add(const uint32_t *__restrict__ sorted,
-                                                       const uint32_t *__restrict__ base, int32_t *__restrict__ Cm,
-                                                       int64_t NM) {
-    constexpr uint32_t kTile = 1u << kPairTileLog2;
-    __shared__ uint32_t h[kTile];
-    for (uint32_t k = threadIdx.x; k < kTile; k += blockDim.x) h[k] = 0u;
-    __syncthreads();
-    const uint32_t b = base[blockIdx.x], e = base[blockIdx.x + 1];
-    for (uint32_t k0 = b + threadIdx.x; k0 < e; k0 += kPairUnroll * blockDim.x) {
-        uint32_t v[kPairUnroll];
-#pragma unroll
-        for (int j = 0; j < kPairUnroll; ++j) {
-            const uint32_t k = k0 + j * blockDim.x;
-            v[j] = k < e ? __builtin_nontemporal_load(sorted + k) : kNoEntry;
-        }
-#pragma unroll
-        for (int j = 0; j < kPairUnroll; ++j)
-            if (v[j] != kNoEntry) atomicAdd(&h[v[j] & (kTile - 1u)], 1u);
-    }
-    __syncthreads();
-    const int64_t t0 = (int64_t)blockIdx.x << kPairTileLog2;
+// One workgroup per tile of 2^kLog2 entries: C[tile] += the histogram of the tile's updates.  Eight
+// lanes read a run together, kRuns runs of a group in flight.  C's entries are loaded behind the first
+// updates: loads complete in order, so ahead of them they would hold the updates up.  (Reading whole
+// tiles from one sorted array took 20 us for 2M updates in 35 tiles, 14 us for 1M in 503 and 19 us for
+// 11M; this takes 11, 15 and 35 us, in exchange for the passes above.)
+template <int kLog2>
+__global__ void __launch_bounds__(512) k_pair_tile_add(const uint16_t *__restrict__ sorted, const uint16_t *__restrict__ off,
+                                                       const uint2 *__restrict__ blk, int32_t nblk, int32_t ntiles,
+                                                       int32_t *__restrict__ Cm, int64_t NM) {
+    constexpr uint32_t kTile = 1u << kLog2;
+    constexpr int kSteps = kTile / (4 * 512);
+    constexpr int kRuns = kPairBlocks / 64;
+    static_assert(kSteps >= 1 && kPairBlocks == 64 * kRuns, "512 threads: 64 groups of 8 lanes");
+    __shared__ __align__(16) uint32_t h[kTile];
+    const int64_t t0 = (int64_t)blockIdx.x << kLog2;
     int32_t *C = Cm + t0;   // the tile's entries of C
     const uint32_t len = (uint32_t)min((int64_t)kTile, NM - t0);
-    if (len == kTile && (reinterpret_cast<uintptr_t>(C) & 15u) == 0) {
-        // whole tile: four entries per thread and step, all loads of C first
-        constexpr int kSteps = kTile / (4 * 512);
-        int4 c[kSteps];
+    const bool whole = len == kTile && (reinterpret_cast<uintptr_t>(C) & 15u) == 0;
+    const int grp = threadIdx.x >> 3, l8 = threadIdx.x & 7;
+    uint2 run[kRuns];
+    uint32_t most = 0u;
+#pragma unroll
+    for (int k = 0; k < kRuns; ++k) {
+        const int b = grp + 64 * k;
+        run[k] = b < nblk ? blk[b] : make_uint2(0u, 0u);
+    }
+#pragma unroll
+    for (int j = 0; j < kSteps; ++j) reinterpret_cast<uint4 *>(h)[threadIdx.x + j * 512] = make_uint4(0u, 0u, 0u, 0u);
+    uint32_t s[kRuns], e[kRuns];
+    auto bounds = [&](uint32_t j) {   // of the groups' runs in round j
+        uint32_t a0[kRuns], a1[kRuns];
+#pragma unroll
+        for (int k = 0; k < kRuns; ++k) {
+            const uint16_t *o = off + (size_t)(j * nblk + grp + 64 * k) * (ntiles + 1) + blockIdx.x;
+            a0[k] = a1[k] = 0u;
+            if (j < run[k].x) {
+                a0[k] = o[0];
+                a1[k] = o[1];
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kRuns; ++k) {
+            const uint32_t at = run[k].y + j * (uint32_t)kPairRound;
+            s[k] = at + a0[k] + l8;
+            e[k] = at + a1[k];
+        }
+    };
+    uint32_t v[kRuns];
+    auto load = [&]() -> bool {   // the next updates of the groups' runs; true if there are more after them
+        bool more = false;
+#pragma unroll
+        for (int k = 0; k < kRuns; ++k) {
+            v[k] = kNoEntry;
+            if (s[k] < e[k]) v[k] = sorted[s[k]];
+            s[k] += 8u;
+            more |= s[k] < e[k];
+        }
+        return __any(more);
+    };
+    auto add = [&]() {
+#pragma unroll
+        for (int k = 0; k < kRuns; ++k)
+            if (v[k] != kNoEntry) atomicAdd(&h[v[k]], 1u);
+    };
+    bounds(0u);
+    bool more = load();
+    __builtin_amdgcn_sched_barrier(0);
+    int4 c[kSteps];
+    if (whole) {
+#pragma unroll
+        for (int j = 0; j < kSteps; ++j) c[j] = reinterpret_cast<const int4 *>(C)[threadIdx.x + j * 512];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < kRuns; ++k) most = max(most, run[k].x);
+    __syncthreads();   // h is zero
+    for (uint32_t j = 0;;) {
+        add();
+        if (more) {
+            more = load();
+            continue;
+        }
+        ++j;
+        if (!__any(j < most)) break;
+        bounds(j);
+        more = load();
+    }
+    __syncthreads();
+    if (whole) {
         int4 *C4 = reinterpret_cast<int4 *>(C);
         const uint4 *h4 = reinterpret_cast<const uint4 *>(h);
 #pragma unroll
-        for (int j = 0; j < kSteps; ++j) c[j] = C4[threadIdx.x + j * 512];
-#pragma unroll
         for (int j = 0; j < kSteps; ++j) {
-            const uint4 a = h4[threadIdx.x + j * 512];
-            c[j].x += (int)a.x;
-            c[j].y += (int)a.y;
-            c[j].z += (int)a.z;
-            c[j].w += (int)a.w;
+            const uint4 d = h4[threadIdx.x + j * 512];
+            c[j].x += (int)d.x;
+            c[j].y += (int)d.y;
+            c[j].z += (int)d.z;
+            c[j].w += (int)d.w;
             C4[threadIdx.x + j * 512] = c[j];
         }
     } else {
@@ -2329,19 +2351,21 @@ __global__ void __launch_bounds__(512) k_pair_tile_add(const uint32_t *__restric
     }
 }
 
-hipError_t launch_pair_histogram(const PairOut &po, int32_t nwaves, int32_t ntiles, int32_t *C, int64_t NM,
-                                 uint32_t *hist, uint32_t *sorted, int cus, hipStream_t st) {
-    if (ntiles < 1 || ntiles > kMaxPairTiles || nwaves < 1) return hipErrorInvalidValue;
-    const int nblk = pair_hist_blocks(ntiles);
-    if ((int64_t)nblk * kMaxSlicesPerBlock < nwaves) return hipErrorInvalidValue;
-    // hist: cursors (32 words per tile, zero on entry) | tile bases (ntiles + 1) | per-workgroup offsets
-    uint32_t *cursor = hist;
-    uint32_t *base = cursor + 32 * (size_t)kMaxPairTiles;
-    uint32_t *boff = base + kMaxPairTiles + 64;
-    (void)cus;
-    k_pair_tile_counts<<<nblk, 1024, 0, st>>>(po, nwaves, ntiles, cursor, boff);
-    k_pair_scatter<<<nblk, 1024, 0, st>>>(po, nwaves, ntiles, cursor, base, boff, sorted);
-    k_pair_tile_add<<<ntiles, 512, 0, st>>>(sorted, base, C, NM);
+hipError_t launch_pair_histogram(const PairOut &po, int32_t nwaves, const PairTiles &pt, const CountArgs &a,
+                                 const CompactVol &cv, FallbackScratch fs, int32_t *C, int64_t NM, uint32_t *hist,
+                                 uint32_t *sorted32, hipStream_t st) {
+    if (pt.n < 1 || pt.n > kMaxPairTiles || nwaves < 1 || pt.blocks < 1) return hipErrorInvalidValue;
+    if ((int64_t)pt.blocks * kMaxSlicesPerBlock < nwaves) return hipErrorInvalidValue;
+    uint2 *blk = reinterpret_cast<uint2 *>(hist);
+    uint16_t *off = reinterpret_cast<uint16_t *>(hist + 2 * kPairBlocks), *sorted = reinterpret_cast<uint16_t *>(sorted32);
+    k_pair_sort<<<fs.blocks + pt.blocks, 1024, 0, st>>>(po, nwaves, pt.n, pt.log2, pt.blocks, blk, off, sorted, a,
+                                                       CompactLookup{cv}, fs);
+    switch (pt.log2) {
+        case 11: k_pair_tile_add<11><<<pt.n, 512, 0, st>>>(sorted, off, blk, pt.blocks, pt.n, C, NM); break;
+        case 12: k_pair_tile_add<12><<<pt.n, 512, 0, st>>>(sorted, off, blk, pt.blocks, pt.n, C, NM); break;
+        case 13: k_pair_tile_add<13><<<pt.n, 512, 0, st>>>(sorted, off, blk, pt.blocks, pt.n, C, NM); break;
+        default: k_pair_tile_add<14><<<pt.n, 512, 0, st>>>(sorted, off, blk, pt.blocks, pt.n, C, NM); break;
+    }
     return hipGetLastError();
 }
 
