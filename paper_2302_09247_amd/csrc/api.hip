@@ -133,6 +133,11 @@ constexpr int64_t kDirectMaxStreamlines = int64_t(1) << 17;   // calls below thi
 constexpr int64_t kDirectMaxEntries = int64_t(1) << 20;       // ... on a C of at most this many entries
                                                               // add their updates to C as atomics
 
+// Plans of more pass-through points than this count into transposed copies of C.  The copies save about a
+// quarter of the atomic requests and cost a launch and a pass over C: 12 subjects of 200M points take
+// 1090 us a launch with and 1151 without them, 24 little subjects of 3.4M points 53.3 with and 41.8 without.
+constexpr int64_t kTransposeMinPoints = int64_t(1) << 24;
+
 // Fallback scratch layout for a C of N rows and M labels: per workgroup an N-bit map, an M-bit map
 // and an M-entry label list, as many workgroups (<= 64) as fit `max_bytes`; false if not even one.
 bool fallback_layout(int32_t N, int32_t M, int64_t max_bytes, fc::FallbackScratch &fs) {
@@ -237,7 +242,7 @@ int make_count_plan(int64_t S, int32_t N, int32_t M, const fc::CompactVol *cv, c
     const bool long_ranges = S >= kLongRangesFrom;
     cp.batch = o.batch != 0 ? o.batch : (long_ranges ? 4 : 2);
     int per_cu = fc::count_stream_blocks_per_cu(o.scale != 1.0f, cv->packed != 0, cp.batch, cp.ends, o.upsample,
-                                                4 * (size_t)cv->ncoarse_words);
+                                                fc::coarse_lds_bytes(cv->ncoarse_words));
     if (o.blocks_per_cu > 0 && o.blocks_per_cu < per_cu) per_cu = o.blocks_per_cu;
     cp.blocks = (int64_t)cus * per_cu;
     if (S <= cp.blocks * fc::kWavesPerBlock * kStaticRangeStreamlines) {
@@ -498,10 +503,11 @@ int plan_items(fastcod_plan &pl, const PlanSched &ps, int cus, hipStream_t st) {
         pl.kind_blocks[k] = cus * std::max(1, std::min(per_cu, occ));
     }
     pl.kind_blocks[0] = pl.blocks;
-    const int64_t total = (int64_t)pl.blocks * fc::kWavesPerBlock * ps.items_per_wave;
     double ptot = 0;
     for (int32_t k = 0; k < pl.n; ++k)
         if (k < pl.kind_lo[(int)fc::BatchedKind::kSeedEnd]) ptot += (double)pl.points[k];
+    const int64_t total = std::min<int64_t>((int64_t)pl.blocks * fc::kWavesPerBlock * ps.items_per_wave,
+                                            (int64_t)(ptot / (double)fc::kMinItemPoints) + 1);
     std::vector<int64_t> base(pl.n + 1, 0);
     for (int32_t k = 0; k < pl.n; ++k) {
         int64_t ni = 0;
@@ -524,21 +530,25 @@ int plan_items(fastcod_plan &pl, const PlanSched &ps, int cus, hipStream_t st) {
 // The launch sequence (eager or under capture).
 int plan_enqueue(fastcod_plan &pl, int cus, hipStream_t st) {
     const auto *subs = static_cast<const fc::StreamSubject *>(pl.d_subs.p);
-    FC_HIP(fc::launch_zero_subjects(subs, static_cast<const int64_t *>(pl.d_sizes.p), pl.n, cus, st));
-    // overflow count and every kind's work-item queues: zeroed by the partition launch (by a fill
-    // when no subject has work items)
+    // one launch zeroes every C, the overflow count and every kind's queues, and writes the work items
     const int64_t header_words = (int64_t)(fc::overflow_header_bytes(fc::kBatchedKinds) / 8);
-    if (pl.nitems == 0) FC_HIP(fc::launch_fill_u64(pl.ovf.count, header_words, cus, st));
+    int64_t most_s = 0, most_entries = 0;
+    for (int32_t k = 0; k < pl.n; ++k) {
+        most_s = std::max(most_s, pl.subs[k].S);
+        most_entries = std::max(most_entries, pl.sizes[k]);
+    }
+    FC_HIP(fc::launch_prepare_batched(subs, static_cast<const int64_t *>(pl.d_item_base.p),
+                                      static_cast<const int64_t *>(pl.d_sizes.p), pl.n, most_s, most_entries,
+                                      pl.nitems > 0 ? static_cast<int2 *>(pl.d_items.p) : nullptr, pl.ovf.count,
+                                      header_words, cus, st));
     const int32_t *kl = pl.kind_lo;
     const int seed = (int)fc::BatchedKind::kSeedEnd;
     if (pl.nitems > 0) {
-        FC_HIP(fc::launch_partition_batched(subs, static_cast<const int64_t *>(pl.d_item_base.p), pl.n, pl.nitems,
-                                            static_cast<int2 *>(pl.d_items.p), pl.ovf.count, header_words, cus, st));
         const int2 *items = static_cast<const int2 *>(pl.d_items.p);
         for (int k = 0; k < seed; ++k) {
             fc::Overflow o = pl.ovf;
             o.work = pl.ovf.count + fc::kQueueWords * (1 + (size_t)k * fc::kRangeQueues);
-            FC_HIP(fc::launch_count_batched(subs, items + pl.item_lo[k], pl.item_lo[k + 1] - pl.item_lo[k], o,
+            FC_HIP(fc::launch_count_batched(subs, pl.n, items + pl.item_lo[k], pl.item_lo[k + 1] - pl.item_lo[k], o,
                                             kBatchedCoarseWords, pl.kind_blocks[k], pl.sched.batch,
                                             (fc::BatchedKind)k, st));
         }
@@ -699,7 +709,9 @@ int plan_build(const fastcod_subject *subjects, int32_t n, uint32_t flags, const
         for (const auto &ss : pl->subs) writers[ss.C]++;
         std::vector<int32_t> pick;
         size_t words = 0;
-        for (int32_t t = 0; t < n; ++t) {
+        int64_t points = 0;
+        for (int32_t t = 0; t < n; ++t) points += pl->points[t];
+        for (int32_t t = 0; t < n && points > kTransposeMinPoints; ++t) {
             const fastcod_subject &u = subjects[order[t]];
             if (pl->subs[t].S > 0 && u.M > 1 && u.N >= 64 && writers[u.C_out] == 1) {
                 pick.push_back(t);

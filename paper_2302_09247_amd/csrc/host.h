@@ -104,7 +104,7 @@ inline int cu_count(int dev) {
 // ---- compact volume layout ----
 constexpr int32_t kMaxCoarseWords = 8192;      // 32 KB of LDS per counting workgroup
 constexpr int32_t kBatchedCoarseWords = 512;   // per-wavefront LDS coarse map of the batched kernel (2 KB)
-constexpr int32_t kCoarseHead = 2;             // words before the coarse map: the number of codes
+constexpr int32_t kCoarseHead = 4;             // words before the coarse map (16-byte aligned): the number of codes
 struct CompactLayout {
     int32_t SBX, SBY, SBZ;
     int64_t W;        // words

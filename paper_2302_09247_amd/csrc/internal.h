@@ -182,6 +182,8 @@ struct Ranges {
     int64_t nparts;
     uint32_t per, extra;
 };
+// LDS of a workgroup's copy of a coarse map, stored 16 bytes at a time
+inline size_t coarse_lds_bytes(int32_t words) { return 4 * (size_t)((words + 3) & ~3); }
 // resident 256-thread workgroups per CU of the flat-stream kernel
 int count_stream_blocks_per_cu(bool scaled, bool packed, int batch, bool ends, int up, size_t dyn_lds);
 
@@ -222,10 +224,16 @@ struct TransposeJob {
 hipError_t launch_transpose_many(const TransposeJob *jobs, int32_t njobs, int64_t ntiles, int cus, hipStream_t st);
 
 // batched form
-hipError_t launch_zero_subjects(const StreamSubject *subs, const int64_t *sizes, int32_t nsub, int cus, hipStream_t st);
-// (also zeroes zero[0 .. nzero): the counting launches' overflow count and range queues)
-hipError_t launch_partition_batched(const StreamSubject *subs, const int64_t *item_base, int32_t nsub, int64_t nitems,
-                                    int2 *items, unsigned long long *zero, int64_t nzero, int cus, hipStream_t st);
+// zeroes every subject's C (sizes: entries; nullptr: none), writes the work items (items == nullptr: none)
+// and zeroes zero[0 .. nzero) (the counting launches' overflow count and range queues);
+// most_streamlines, most_entries: the largest subject's streamlines and entries of C to zero
+hipError_t launch_prepare_batched(const StreamSubject *subs, const int64_t *item_base, const int64_t *sizes, int32_t nsub,
+                                  int64_t most_streamlines, int64_t most_entries, int2 *items, unsigned long long *zero,
+                                  int64_t nzero, int cus, hipStream_t st);
+// Points a work item holds at least, on average: smaller launches get fewer items, and with at most one
+// per wavefront nothing is drawn from a queue.  (24 little subjects of 3.4M points in all: 45.1 us a
+// launch at 512, 41.4 at 256, 58.6 at 1024, 58 with 28,672 items whatever the points.)
+constexpr int64_t kMinItemPoints = 256;
 // Kinds of subject of the batched form, each counted by its own launch (subjects of one kind are
 // neighbours in the descriptor table): pass-through, endpoint modes 1/2,
 // upsampled pass-through (u = 2, or u = 3..4), Alg. 1's seed-to-end count (no work items).
@@ -238,9 +246,9 @@ inline BatchedKind batched_kind(int mode, int up) {
     return mode == 1 || mode == 2 ? BatchedKind::kEnds : BatchedKind::kPass;
 }
 int count_batched_blocks_per_cu(int batch, int coarse_words, BatchedKind kind = BatchedKind::kPass);
-// items[0, nitems) of subjects of one kind (kPass, kEnds, kUp2, kUp4)
-hipError_t launch_count_batched(const StreamSubject *subs, const int2 *items, int64_t nitems, const Overflow &ovf,
-                                int32_t coarse_words, int blocks, int batch, BatchedKind kind, hipStream_t st);
+// items[0, nitems) of subjects of one kind (kPass, kEnds, kUp2, kUp4) of the table's nsub entries
+hipError_t launch_count_batched(const StreamSubject *subs, int32_t nsub, const int2 *items, int64_t nitems,
+                                const Overflow &ovf, int32_t coarse_words, int blocks, int batch, BatchedKind kind, hipStream_t st);
 // table entries [lo, lo + n): Alg. 1's count of their streamlines [s_begin, S)
 hipError_t launch_count_seed_end_batched(const StreamSubject *subs, int32_t lo, int32_t n, int cus, hipStream_t st);
 hipError_t launch_fallback_batched(const StreamSubject *subs, int32_t nsub, const Overflow &ovf, FallbackScratch fs,

@@ -713,6 +713,11 @@ struct RangeOf {
         const int32_t i = (int32_t)(n * (1.5f - sqrtf(2.25f - 2.0f * u)));
         return i < 0 ? 0 : (i > last ? last : i);
     }
+    // the same for ranges of equal size
+    __device__ int32_t equal(int64_t p) const {
+        const int32_t i = (int32_t)(n * fminf((float)(uint32_t)(clamp64(p, 0, P) >> sh) * inv_P, 1.0f));
+        return i < 0 ? 0 : (i > last ? last : i);
+    }
 };
 
 // p[0 .. n) = 0 by the whole grid, 16 bytes a store
@@ -735,13 +740,9 @@ __global__ void k_partition(const int64_t *__restrict__ offsets, int64_t S, int6
     constexpr int kShort = 2, kUnroll = 4;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-#pragma unroll
-    for (int r = 0; r < kZeroRanges; ++r) grid_zero(z.w32[r], z.n32[r], t0, stride);
-    for (int64_t i = t0; i < z.n64; i += stride) z.w64[i] = 0ull;
-    if (!first) return;
     const int lane = lane_id();
-    const RangeOf range_of(offsets[S], nparts);
-    for (int64_t b0 = kUnroll * (t0 - lane); b0 <= S; b0 += kUnroll * stride) {   // (uniform over the wavefront)
+    const RangeOf range_of(first ? offsets[S] : 0, nparts);
+    for (int64_t b0 = first ? kUnroll * (t0 - lane) : S + 1; b0 <= S; b0 += kUnroll * stride) {   // (uniform over the wavefront)
         int64_t off[kUnroll];
 #pragma unroll
         for (int j = 0; j < kUnroll; ++j) off[j] = offsets[min(b0 + j * kWave + lane, S)];
@@ -765,6 +766,10 @@ __global__ void k_partition(const int64_t *__restrict__ offsets, int64_t S, int6
             }
         }
     }
+    // (the zero fills come last: a wait for a load also waits for the stores before it)
+#pragma unroll
+    for (int r = 0; r < kZeroRanges; ++r) grid_zero(z.w32[r], z.n32[r], t0, stride);
+    for (int64_t i = t0; i < z.n64; i += stride) z.w64[i] = 0ull;
 }
 
 hipError_t launch_partition(const int64_t *offsets, int64_t S, int64_t nparts, int32_t *first, const ZeroRanges &z,
@@ -956,18 +961,28 @@ constexpr int64_t kMaxRangePoints = int64_t(1) << 28;  // longest point range th
 constexpr int kSetWords = kRCap + 2 * kLCap + kTCap;
 using StreamSet = DeferredSet<kRCap, kLCap, kTCap>;
 
+// A streamline range and the offsets it needs, as loaded.
+struct RangeBounds {
+    int64_t s0, s1;          // streamlines
+    int64_t P, p0, p1;       // offsets[S], offsets[s0], offsets[s1]
+};
+__device__ __forceinline__ RangeBounds range_bounds(const int64_t *offsets, int64_t S, int64_t s0, int64_t s1) {
+    const auto offs = gview(offsets);
+    return {s0, s1, offs[S], offs[s0], offs[s1]};
+}
+
 // Counts streamlines [s0, s1) of one subject (whole streamlines only) into sub.C through `sink`.
 // `coarse` is the subject's coarse occupancy map in LDS.  PACKED: 0/1 = code width known at compile
 // time, 2 = read from cv.packed.
 template <bool SCALED, int PACKED, int kBatch, bool kEnds, int kUp, bool kBrick, typename Sink>
-__device__ void stream_range(const StreamSubject &sub, const uint32_t *coarse, int64_t s0, int64_t s1, int32_t subject,
+__device__ void stream_range(const StreamSubject &sub, const uint32_t *coarse, const RangeBounds &rb, int32_t subject,
                              const Overflow &ovf, StreamSet &set, Sink &sink) {
     constexpr int kV = kBatch * kUp;   // lookups per batch: kUp sub-points of each of kBatch windows
     const int lane = lane_id();
     const CompactVol &cv = sub.cv;
-    const int64_t S = sub.S;
+    const int64_t s0 = rb.s0, s1 = rb.s1;
     const auto offs = gview(sub.offsets);
-    const int64_t Ptot = uniform64(offs[S] > 0 ? offs[S] : 0);
+    const int64_t Ptot = uniform64(rb.P > 0 ? rb.P : 0);
     // occupancy pairs and codes share one allocation and one resource (codes at cv.codes_off)
     const __amdgpu_buffer_rsrc_t rvol = make_rsrc(cv.mb, cv.span);
     const int codes_off = uniform32((int)cv.codes_off);
@@ -978,8 +993,8 @@ __device__ void stream_range(const StreamSubject &sub, const uint32_t *coarse, i
     const uint32_t SBX = (uint32_t)cv.SBX, SBXY = (uint32_t)cv.SBXY;
     const uint32_t csx = (uint32_t)cv.csx, csyz = (uint32_t)cv.csyz, CBX = (uint32_t)cv.CBX, CBXY = (uint32_t)cv.CBXY;
     constexpr uint32_t kOutOfRange = 0xFFFFFFF8u;   // buffer offset past every resource: reads 0, no traffic
-    const int64_t P0 = uniform64(clamp64(offs[s0], 0, Ptot));
-    const int64_t P1 = uniform64(clamp64(offs[s1], P0, Ptot));
+    const int64_t P0 = uniform64(clamp64(rb.p0, 0, Ptot));
+    const int64_t P1 = uniform64(clamp64(rb.p1, P0, Ptot));
     if (P0 >= P1) return;
     if (P1 - P0 > kMaxRangePoints) {
         // positions below are 32-bit offsets from P0: a range this long (a few giant streamlines
@@ -1338,23 +1353,42 @@ __device__ void stream_range(const StreamSubject &sub, const uint32_t *coarse, i
     close_open(lab_prev);
 }
 
-// Calls f(s0, s1) for the streamline ranges of wavefront `wave`: ranges [first[i], first[i + 1]) from
-// its queue, or (no table) the wavefront's one range of about S / nparts streamlines.
+// A coarse map to LDS, 16 bytes a thread and step (by `threads` threads; the map is 16-byte aligned, and
+// what follows its last word in its allocation may be read and stored: ncoarse_words rounded up to 4).
+// Returns the first step's load; store it with put_coarse, so that other loads can fly beside it.
+__device__ __forceinline__ uint4 get_coarse(const CompactVol &cv, int t) {
+    uint4 v = make_uint4(0u, 0u, 0u, 0u);
+    if (4 * t < cv.ncoarse_words) v = reinterpret_cast<const uint4 *>(cv.coarse)[t];
+    return v;
+}
+__device__ __forceinline__ void put_coarse(const CompactVol &cv, uint32_t *lds, uint4 v, int t, int threads) {
+    const int n4 = (cv.ncoarse_words + 3) >> 2;
+    if (t < n4) reinterpret_cast<uint4 *>(lds)[t] = v;
+    for (int k = t + threads; k < n4; k += threads)
+        reinterpret_cast<uint4 *>(lds)[k] = reinterpret_cast<const uint4 *>(cv.coarse)[k];
+}
+
+// The streamline ranges of wavefront `wave`: ranges [first[i], first[i + 1]) from its queue, or (no table)
+// one range of about S / nparts streamlines, whose offsets first_range loads ahead of their use.
+__device__ __forceinline__ RangeBounds first_range(const Ranges &rg, const StreamSubject &sub, uint32_t wave) {
+    if (rg.first) return {0, 0, 0, 0, 0};
+    const int64_t s0 = min(sub.S, (int64_t)wave * rg.per + min(wave, rg.extra));
+    return range_bounds(sub.offsets, sub.S, s0, min(sub.S, s0 + rg.per + (wave < rg.extra ? 1 : 0)));
+}
+// Calls f(bounds) for each of them.
 template <typename F>
-__device__ __forceinline__ void for_each_range(const Ranges &rg, const Overflow &ovf, uint32_t wave, int64_t S, F &&f) {
+__device__ __forceinline__ void for_each_range(const Ranges &rg, const StreamSubject &sub, const Overflow &ovf, uint32_t wave,
+                                               RangeBounds rb, F &&f) {
     const bool table = rg.first != nullptr;
     for (;;) {
-        int64_t s0, s1;
         if (table) {
             const int64_t part = next_range(ovf, wave);
             if (part >= rg.nparts) break;
-            s0 = uniform64(clamp64(rg.first[part], 0, S));
-            s1 = uniform64(clamp64(rg.first[part + 1], s0, S));
-        } else {
-            s0 = (int64_t)wave * rg.per + min(wave, rg.extra);
-            s1 = min(S, s0 + rg.per + (wave < rg.extra ? 1 : 0));
+            const int64_t s0 = uniform64(clamp64(rg.first[part], 0, sub.S));
+            const int64_t s1 = uniform64(clamp64(rg.first[part + 1], s0, sub.S));
+            rb = range_bounds(sub.offsets, sub.S, s0, s1);
         }
-        if (s0 < s1) f(s0, s1);
+        if (rb.s0 < rb.s1) f(rb);
         if (!table) break;
     }
 }
@@ -1368,17 +1402,19 @@ __device__ __forceinline__ void count_stream_body(const StreamSubject &sub, cons
     constexpr int kSinkCap = kBatch == 4 ? 8 * kWave : 4 * kWave;
     __shared__ uint32_t s_set[kWavesPerBlock * kSetWords];
     __shared__ __align__(16) uint32_t s_pend[kWavesPerBlock * kSinkCap];
-    extern __shared__ uint32_t s_coarse[];   // coarse occupancy bit map, cv.ncoarse_words words
+    extern __shared__ __align__(16) uint32_t s_coarse[];   // coarse occupancy bit map (coarse_lds_bytes)
     const int wv = uniform32(threadIdx.x >> 6);
-    for (int k = threadIdx.x; k < sub.cv.ncoarse_words; k += blockDim.x) s_coarse[k] = sub.cv.coarse[k];
-    __syncthreads();
+    const uint32_t wave = blockIdx.x * kWavesPerBlock + wv;
+    const RangeBounds rb = first_range(rg, sub, wave);
+    const uint4 cmap = get_coarse(sub.cv, threadIdx.x);
     StreamSet set;
     set.init(s_set + wv * kSetWords);
-    const uint32_t wave = blockIdx.x * kWavesPerBlock + wv;
+    put_coarse(sub.cv, s_coarse, cmap, threadIdx.x, kBlock);
+    __syncthreads();
     AppendSink<kSinkCap> sink;
     sink.init(s_pend + wv * kSinkCap, sub.C, po, wave);
-    for_each_range(rg, ovf, wave, sub.S, [&](int64_t s0, int64_t s1) {
-        stream_range<SCALED, PACKED ? 1 : 0, kBatch, kEnds, 1, kBrick>(sub, s_coarse, s0, s1, 0, ovf, set, sink);
+    for_each_range(rg, sub, ovf, wave, rb, [&](const RangeBounds &r) {
+        stream_range<SCALED, PACKED ? 1 : 0, kBatch, kEnds, 1, kBrick>(sub, s_coarse, r, 0, ovf, set, sink);
     });
     sink.drain(po, wave);
 }
@@ -1407,17 +1443,19 @@ __global__ void __launch_bounds__(kBlock) k_count_stream_up(StreamSubject sub, O
     constexpr int kSinkCap = 4 * kWave;
     __shared__ uint32_t s_set[kWavesPerBlock * kSetWords];
     __shared__ __align__(16) uint32_t s_pend[kWavesPerBlock * kSinkCap];
-    extern __shared__ uint32_t s_coarse[];
+    extern __shared__ __align__(16) uint32_t s_coarse[];
     const int wv = uniform32(threadIdx.x >> 6);
-    for (int k = threadIdx.x; k < sub.cv.ncoarse_words; k += blockDim.x) s_coarse[k] = sub.cv.coarse[k];
-    __syncthreads();
+    const uint32_t wave = blockIdx.x * kWavesPerBlock + wv;
+    const RangeBounds rb = first_range(rg, sub, wave);
+    const uint4 cmap = get_coarse(sub.cv, threadIdx.x);
     StreamSet set;
     set.init(s_set + wv * kSetWords);
-    const uint32_t wave = blockIdx.x * kWavesPerBlock + wv;
+    put_coarse(sub.cv, s_coarse, cmap, threadIdx.x, kBlock);
+    __syncthreads();
     AppendSink<kSinkCap> sink;
     sink.init(s_pend + wv * kSinkCap, sub.C, po, wave);
-    for_each_range(rg, ovf, wave, sub.S, [&](int64_t s0, int64_t s1) {
-        stream_range<true, 2, kB, false, kUp, false>(sub, s_coarse, s0, s1, 0, ovf, set, sink);
+    for_each_range(rg, sub, ovf, wave, rb, [&](const RangeBounds &r) {
+        stream_range<true, 2, kB, false, kUp, false>(sub, s_coarse, r, 0, ovf, set, sink);
     });
     sink.drain(po, wave);
 }
@@ -1429,12 +1467,13 @@ __global__ void __launch_bounds__(kBlock) k_count_stream_up(StreamSubject sub, O
 // (kEnds: end labels at each close), and upsampled pass-through (kUp 2 or 4, with
 // sub.up <= kUp); a launch takes the items of subjects of one kind only.
 template <int kBatch, bool kEnds, int kUp>
-__global__ void __launch_bounds__(kBlock) k_count_batched(const StreamSubject *__restrict__ subs,
+__global__ void __launch_bounds__(kBlock) k_count_batched(const StreamSubject *__restrict__ subs, int32_t nsub,
                                                           const int2 *__restrict__ items, int64_t nitems,
                                                           Overflow ovf, int32_t coarse_words) {
     __shared__ uint32_t s_set[kWavesPerBlock * kSetWords];
     __shared__ uint32_t s_pend[kWavesPerBlock * kWave];
-    extern __shared__ uint32_t s_coarse[];   // kWavesPerBlock * coarse_words
+    typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+    extern __shared__ __align__(16) uint32_t s_coarse[];   // kWavesPerBlock * coarse_words (at most 512, a multiple of 4)
     const int lane = lane_id(), wv = uniform32(threadIdx.x >> 6);
     uint32_t *coarse = s_coarse + wv * coarse_words;
     StreamSet set;
@@ -1444,11 +1483,14 @@ __global__ void __launch_bounds__(kBlock) k_count_batched(const StreamSubject *_
     sink.init(s_pend + wv * kWave, nullptr);
     int loaded = -1;
     const uint32_t wave = blockIdx.x * kWavesPerBlock + wv;
-    for (;;) {
-        const int64_t item = next_range(ovf, wave);
+    // one item per wavefront: no queue
+    const bool queued = nitems > (int64_t)gridDim.x * kWavesPerBlock;
+    for (int64_t turn = 0; queued || turn == 0; ++turn) {
+        const int64_t item = queued ? next_range(ovf, wave) : (int64_t)wave;
         if (item >= nitems) break;
         const int2 it = items[item];
-        const int subject = uniform32(it.x);
+        // (offsets that decrease leave items unwritten: the result is undefined then, the accesses are not)
+        const int subject = uniform32(min(max(it.x, 0), nsub - 1));
         const StreamSubject &sub = subs[subject];
         const int64_t s0 = uniform64(clamp64(it.y, 0, sub.S));
         int64_t s1 = sub.S;
@@ -1458,12 +1500,21 @@ __global__ void __launch_bounds__(kBlock) k_count_batched(const StreamSubject *_
         }
         s1 = uniform64(clamp64(s1, s0, sub.S));
         if (s0 >= s1) continue;
+        const RangeBounds rb = range_bounds(sub.offsets, sub.S, s0, s1);
         if (subject != loaded) {
-            for (int k = lane; k < sub.cv.ncoarse_words; k += kWave) coarse[k] = gview(sub.cv.coarse)[k];
+            // two 16-byte loads a lane, at most 512 words
+            const auto src = reinterpret_cast<const __attribute__((address_space(1))) v4u *>(gview(sub.cv.coarse));
+            const int n4 = (sub.cv.ncoarse_words + 3) >> 2;
+            v4u c0 = {}, c1 = {};
+            if (lane < n4) c0 = src[lane];
+            if (lane + kWave < n4) c1 = src[lane + kWave];
+            v4u *dst = reinterpret_cast<v4u *>(coarse);
+            if (lane < n4) dst[lane] = c0;
+            if (lane + kWave < n4) dst[lane + kWave] = c1;
             loaded = subject;
         }
         sink.C = sub.C;
-        stream_range<true, 2, kBatch, kEnds, kUp, false>(sub, coarse, s0, s1, subject, ovf, set, sink);
+        stream_range<true, 2, kBatch, kEnds, kUp, false>(sub, coarse, rb, subject, ovf, set, sink);
         sink.drain();   // the next item may belong to another subject's C
     }
 }
@@ -1518,7 +1569,7 @@ template <int B, bool E, bool K>
 static void launch_stream_bk(const CountArgs &a, const CompactVol &cv, const Ranges &rg, int blocks,
                              const PairOut &po, hipStream_t st) {
     const bool scaled = a.scale != 1.0f;
-    const size_t dyn = 4 * (size_t)cv.ncoarse_words;
+    const size_t dyn = coarse_lds_bytes(cv.ncoarse_words);
     const StreamSubject sub = stream_subject(a, cv);
 #define FC_LAUNCH_STREAM(S_, P_)                                                                               \
     do {                                                                                                       \
@@ -1543,7 +1594,7 @@ static void launch_stream_b(const CountArgs &a, const CompactVol &cv, const Rang
 hipError_t launch_count_stream(const CountArgs &a, const CompactVol &cv, const Ranges &rg, int blocks,
                                int batch, const PairOut &po, hipStream_t st) {
     if (a.up > 1) {
-        const size_t dyn = 4 * (size_t)cv.ncoarse_words;
+        const size_t dyn = coarse_lds_bytes(cv.ncoarse_words);
         const StreamSubject sub = stream_subject(a, cv);
         if (a.up == 2) k_count_stream_up<2><<<blocks, kBlock, dyn, st>>>(sub, a.ovf, rg, po);
         else k_count_stream_up<4><<<blocks, kBlock, dyn, st>>>(sub, a.ovf, rg, po);
@@ -1872,57 +1923,60 @@ hipError_t launch_parcellate(const int32_t *C, int32_t N, int32_t M, int32_t *la
 // batched form: work items, zero fill of every C, launchers
 // ---------------------------------------------------------------------------------------------
 
-// items[i] = (subject, first streamline of [s_begin, S) at or after point P0 + floor(j * (P - P0) / n_s))
-// for the j-th of the subject's n_s items (P0 = offsets[s_begin], P = offsets[S]); item_base[s] ..
-// item_base[s+1] are subject s's items.  The same launch zeroes zero[0 .. nzero) (the counting
-// launches' overflow count and range queues), which saves a launch of its own.
-__global__ void k_partition_batched(const StreamSubject *__restrict__ subs, const int64_t *__restrict__ item_base,
-                                    int32_t nsub, int2 *__restrict__ items, unsigned long long *__restrict__ zero,
-                                    int64_t nzero) {
-    const int64_t n = item_base[nsub];
+// Prepares a launch; blockIdx.y is the subject.  Its C is zeroed (sizes: entries of each subject's C;
+// nullptr: not here), and its work items item_base[s] .. item_base[s + 1] are written: item j = (subject,
+// first streamline of [s_begin, S) whose start lies in the j-th of the n_s equal parts of the points
+// offsets[s_begin] .. offsets[S]).  The offsets are read once, in order, as in k_partition: a binary
+// search per item took 8.5 us on little subjects and 16 us on large ones, after a launch for the zero
+// fill of its own.  Also zeroes zero[0 .. nzero): the counting launches' overflow count and queues.
+__global__ void k_prepare_batched(const StreamSubject *__restrict__ subs, const int64_t *__restrict__ item_base,
+                                  const int64_t *__restrict__ sizes, int2 *__restrict__ items,
+                                  unsigned long long *__restrict__ zero, int64_t nzero) {
+    constexpr int kShort = 2;
+    const int32_t k = (int32_t)blockIdx.y;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nzero; i += stride) zero[i] = 0ull;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-        int lo = 0, hi = nsub;   // subject: last s with item_base[s] <= i
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (item_base[mid] <= i) lo = mid;
-            else hi = mid;
+    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const StreamSubject &sub = subs[k];
+    const int64_t i0 = item_base[k], S = sub.S, sb = clamp64(sub.s_begin, 0, S);
+    const int32_t ns = items ? (int32_t)(item_base[k + 1] - i0) : 0;
+    const int lane = lane_id();
+    const auto offs = gview(sub.offsets);
+    const int64_t P0 = ns > 0 ? offs[sb] : 0;
+    const RangeOf range_of(ns > 0 ? offs[S] - P0 : 0, ns);
+    for (int64_t b0 = t0 - lane; b0 < (ns > 0 ? S - sb : 0); b0 += stride) {   // (uniform over the wavefront)
+        const int64_t s = sb + b0 + lane;
+        const bool mine = s < S;
+        const int32_t before = b0 > 0 ? range_of.equal(offs[sb + b0 - 1] - P0) : -1;
+        const int32_t in = range_of.equal(offs[mine ? s : S] - P0);
+        const int32_t hi = s == S - 1 ? ns - 1 : in;   // (the last streamline takes the items left over)
+        const int32_t lo = __builtin_amdgcn_update_dpp(before, in, 0x138, 0xF, 0xF, false) + 1;   // wave_shr:1
+#pragma unroll
+        for (int q = 0; q < kShort; ++q)
+            if (mine && lo + q <= hi) items[i0 + lo + q] = make_int2(k, (int)(lo + q <= in ? s : S));
+        uint64_t rest = __ballot(mine && lo + kShort <= hi);
+        while (rest) {
+            const int q = __builtin_ctzll(rest);
+            rest &= rest - 1ull;
+            const int32_t l = __builtin_amdgcn_readlane(lo, q), h = __builtin_amdgcn_readlane(hi, q),
+                          n = __builtin_amdgcn_readlane(in, q);
+            const int64_t sq = sb + b0 + q;
+            for (int32_t i = l + kShort + lane; i <= h; i += kWave) items[i0 + i] = make_int2(k, (int)(i <= n ? sq : S));
         }
-        const StreamSubject &sub = subs[lo];
-        const int64_t j = i - item_base[lo], ns = item_base[lo + 1] - item_base[lo];
-        const int64_t sb = clamp64(sub.s_begin, 0, sub.S);
-        const int64_t P0 = sub.offsets[sb];
-        int64_t P = sub.offsets[sub.S];
-        if (P < P0) P = P0;
-        const int64_t target = P0 + (int64_t)(((__int128)j * (P - P0)) / ns);
-        int64_t a = sb, b = sub.S;
-        while (a < b) {
-            const int64_t mid = (a + b) >> 1;
-            if (sub.offsets[mid] < target) a = mid + 1;
-            else b = mid;
-        }
-        items[i] = make_int2(lo, (int)a);
     }
+    // (the zero fills come last: a wait for a load also waits for the stores before it)
+    if (sizes) grid_zero(sub.C, sizes[k], t0, stride);
+    if (k == 0)
+        for (int64_t i = t0; i < nzero; i += stride) zero[i] = 0ull;
 }
 
-// C of every subject set to zero (blockIdx.y = subject)
-__global__ void k_zero_subjects(const StreamSubject *__restrict__ subs, const int64_t *__restrict__ sizes) {
-    const StreamSubject &sub = subs[blockIdx.y];
-    const int64_t n = sizes[blockIdx.y];
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) sub.C[i] = 0;
-}
-
-hipError_t launch_zero_subjects(const StreamSubject *subs, const int64_t *sizes, int32_t nsub, int cus, hipStream_t st) {
-    k_zero_subjects<<<dim3((unsigned)(cus > 0 ? cus : 64), (unsigned)nsub), kBlock, 0, st>>>(subs, sizes);
-    return hipGetLastError();
-}
-
-hipError_t launch_partition_batched(const StreamSubject *subs, const int64_t *item_base, int32_t nsub, int64_t nitems,
-                                    int2 *items, unsigned long long *zero, int64_t nzero, int cus, hipStream_t st) {
-    k_partition_batched<<<fill_blocks(std::max<int64_t>(nitems, nzero), cus), kBlock, 0, st>>>(subs, item_base, nsub,
-                                                                                             items, zero, nzero);
+hipError_t launch_prepare_batched(const StreamSubject *subs, const int64_t *item_base, const int64_t *sizes, int32_t nsub,
+                                  int64_t most_streamlines, int64_t most_entries, int2 *items, unsigned long long *zero,
+                                  int64_t nzero, int cus, hipStream_t st) {
+    // one streamline or four entries of C per thread and step, up to 16 workgroups per CU in all
+    const int64_t n = std::max(std::max(most_streamlines, (most_entries + 3) / 4), nzero);
+    int64_t blocks = std::min((n + kBlock - 1) / kBlock, std::max<int64_t>((int64_t)cus * 16 / nsub, 1));
+    k_prepare_batched<<<dim3((unsigned)std::max<int64_t>(blocks, 1), (unsigned)nsub), kBlock, 0, st>>>(subs, item_base, sizes,
+                                                                                                     items, zero, nzero);
     return hipGetLastError();
 }
 
@@ -1946,24 +2000,24 @@ int count_batched_blocks_per_cu(int batch, int coarse_words, BatchedKind kind) {
     }
 }
 
-hipError_t launch_count_batched(const StreamSubject *subs, const int2 *items, int64_t nitems, const Overflow &ovf,
-                                int32_t coarse_words, int blocks, int batch, BatchedKind kind, hipStream_t st) {
+hipError_t launch_count_batched(const StreamSubject *subs, int32_t nsub, const int2 *items, int64_t nitems,
+                                const Overflow &ovf, int32_t coarse_words, int blocks, int batch, BatchedKind kind, hipStream_t st) {
     if (nitems <= 0) return hipSuccess;
     const size_t dyn = 4 * (size_t)kWavesPerBlock * (size_t)coarse_words;
     switch (kind) {
         case BatchedKind::kEnds:
-            if (batch == 2) k_count_batched<2, true, 1><<<blocks, kBlock, dyn, st>>>(subs, items, nitems, ovf, coarse_words);
-            else k_count_batched<4, true, 1><<<blocks, kBlock, dyn, st>>>(subs, items, nitems, ovf, coarse_words);
+            if (batch == 2) k_count_batched<2, true, 1><<<blocks, kBlock, dyn, st>>>(subs, nsub, items, nitems, ovf, coarse_words);
+            else k_count_batched<4, true, 1><<<blocks, kBlock, dyn, st>>>(subs, nsub, items, nitems, ovf, coarse_words);
             break;
         case BatchedKind::kUp2:   // two windows of two lookups each per batch, as k_count_stream_up<2>
-            k_count_batched<2, false, 2><<<blocks, kBlock, dyn, st>>>(subs, items, nitems, ovf, coarse_words);
+            k_count_batched<2, false, 2><<<blocks, kBlock, dyn, st>>>(subs, nsub, items, nitems, ovf, coarse_words);
             break;
         case BatchedKind::kUp4:
-            k_count_batched<1, false, 4><<<blocks, kBlock, dyn, st>>>(subs, items, nitems, ovf, coarse_words);
+            k_count_batched<1, false, 4><<<blocks, kBlock, dyn, st>>>(subs, nsub, items, nitems, ovf, coarse_words);
             break;
         default:
-            if (batch == 2) k_count_batched<2, false, 1><<<blocks, kBlock, dyn, st>>>(subs, items, nitems, ovf, coarse_words);
-            else k_count_batched<4, false, 1><<<blocks, kBlock, dyn, st>>>(subs, items, nitems, ovf, coarse_words);
+            if (batch == 2) k_count_batched<2, false, 1><<<blocks, kBlock, dyn, st>>>(subs, nsub, items, nitems, ovf, coarse_words);
+            else k_count_batched<4, false, 1><<<blocks, kBlock, dyn, st>>>(subs, nsub, items, nitems, ovf, coarse_words);
             break;
     }
     return hipGetLastError();
@@ -2428,9 +2482,9 @@ __global__ void __launch_bounds__(kBlock) k_probe_atomics(int32_t *__restrict__ 
 template <int kBatch, bool kBrick>
 __global__ void __launch_bounds__(kBlock) k_probe_lookup(StreamSubject sub, int64_t P, int64_t nwaves,
                                                          uint32_t *__restrict__ sink) {
-    extern __shared__ uint32_t s_coarse[];
+    extern __shared__ __align__(16) uint32_t s_coarse[];
     const CompactVol &cv = sub.cv;
-    for (int k = threadIdx.x; k < cv.ncoarse_words; k += blockDim.x) s_coarse[k] = cv.coarse[k];
+    put_coarse(cv, s_coarse, get_coarse(cv, threadIdx.x), threadIdx.x, kBlock);
     __syncthreads();
     const int lane = lane_id();
     const int64_t wave = (int64_t)blockIdx.x * kWavesPerBlock + uniform32((int)(threadIdx.x >> 6));
@@ -2551,7 +2605,7 @@ hipError_t launch_probe_atomics(int32_t *C, int64_t n_words, const uint32_t *idx
 
 hipError_t launch_probe_lookup(const StreamSubject &sub, int64_t P, int cus, uint32_t *sink, hipStream_t st) {
     if (P <= 0) return hipSuccess;
-    const size_t dyn = 4 * (size_t)sub.cv.ncoarse_words;
+    const size_t dyn = coarse_lds_bytes(sub.cv.ncoarse_words);
     const bool brick = sub.cv.csx == 4 && sub.cv.csyz == 3;
     const void *fn = brick ? reinterpret_cast<const void *>(&k_probe_lookup<4, true>)
                            : reinterpret_cast<const void *>(&k_probe_lookup<4, false>);

@@ -27,7 +27,6 @@ namespace {
 
 constexpr int kTickSlots = 4;            // descriptor tables in rotation (> ticks in flight)
 constexpr int kItemsPerWave = 4;         // work items per wavefront of a full launch
-constexpr int64_t kMinItemPoints = 256;  // smaller launches get fewer, larger items
 
 class HipExecutor final : public fcs::Executor {
   public:
@@ -185,7 +184,7 @@ class HipExecutor final : public fcs::Executor {
         if (int rc = ensure_fallback(maxN, maxM)) return rc;
         int64_t total = 0;
         for (int32_t k = 0; k < kind_lo[seed]; ++k) total += chunks[k].req->offsets[chunks[k].s1] - chunks[k].req->offsets[chunks[k].s0];
-        const int64_t want = std::max<int64_t>(1, std::min<int64_t>(items_full_, total / kMinItemPoints));
+        const int64_t want = std::max<int64_t>(1, std::min<int64_t>(items_full_, total / fc::kMinItemPoints));
         s.h_base[0] = 0;
         for (int32_t k = 0; k < n; ++k) {
             const fcs::Chunk &c = chunks[k];
@@ -218,22 +217,24 @@ class HipExecutor final : public fcs::Executor {
         const auto *subs = static_cast<const fc::StreamSubject *>(s.d_desc.p);
         const auto *d_base = reinterpret_cast<const int64_t *>(static_cast<const char *>(s.d_desc.p) + desc_base_off_);
         const int2 *items = static_cast<const int2 *>(s.d_items.p);
-        // the counters and range queues are reset by the partition launch (by a fill without items)
+        // the counters and range queues are reset by the launch that writes the items (by a fill without items)
         const int64_t header_words = (int64_t)(fc::overflow_header_bytes(fc::kBatchedKinds) / 8);
         if (hip(hipMemcpyAsync(s.d_desc.p, s.h_desc, desc_base_off_ + 8 * (size_t)(n + 1), hipMemcpyHostToDevice, comp_),
                 "descriptor upload") ||
             (nitems == 0 && hip(fc::launch_fill_u64(ovf_.count, header_words, cus_, comp_), "counter reset")))
             return FASTCOD_EHIP;
         if (nitems > 0) {
-            if (hip(fc::launch_partition_batched(subs, d_base, n, nitems, static_cast<int2 *>(s.d_items.p), ovf_.count,
-                                                 header_words, cus_, comp_),
-                    "partition"))
+            int64_t most_s = 0;
+            for (const fcs::Chunk &c : chunks) most_s = std::max(most_s, c.s1 - c.s0);
+            if (hip(fc::launch_prepare_batched(subs, d_base, nullptr, n, most_s, 0, static_cast<int2 *>(s.d_items.p),
+                                               ovf_.count, header_words, cus_, comp_),
+                    "work items"))
                 return FASTCOD_EHIP;
             for (int k = 0; k < seed; ++k) {
                 const int64_t lo = s.h_base[kind_lo[k]], hi = s.h_base[kind_lo[k + 1]];
                 fc::Overflow o = ovf_;
                 o.work = ovf_.count + fc::kQueueWords * (1 + (size_t)k * fc::kRangeQueues);
-                if (hip(fc::launch_count_batched(subs, items + lo, hi - lo, o, kBatchedCoarseWords, kind_blocks_[k], 4,
+                if (hip(fc::launch_count_batched(subs, n, items + lo, hi - lo, o, kBatchedCoarseWords, kind_blocks_[k], 4,
                                                  (fc::BatchedKind)k, comp_),
                         "count"))
                     return FASTCOD_EHIP;

@@ -80,3 +80,28 @@ def test_end_labels_at_window_edges(fc, mode, batch):
         C = fc.count(*dev, vols.N, vols.M, mode=mode, variant=2, batch=batch, **kw)
         torch.cuda.synchronize()
         np.testing.assert_array_equal(C.cpu().numpy().astype(np.int64), exp, err_msg=f"{kw}")
+
+
+@pytest.mark.parametrize("sizes", [(1, 1, 1), (3, 4097, 0, 70), (20_000, 30_000), (150_000, 5)])
+def test_batched_items(fc, sizes):
+    # plans with fewer work items than wavefronts and with more, streamlines that begin hundreds of
+    # items, runs of empty ones, a subject without streamlines
+    subs, exps = [], []
+    for k, S in enumerate(sizes):
+        pts, off, vols = _case(max(S, 1), k % 2 == 1, 300 + k)
+        off = off[: S + 1]
+        pts = pts[: int(off[-1])]
+        exps.append(oracle.count(pts, off, vols.roi, vols.lab, vols.N, vols.M))
+        pts = pts if len(pts) else np.zeros((1, 3), np.float32)   # (never read)
+        subs.append(dict(points=torch.from_numpy(pts).cuda(), offsets=torch.from_numpy(off).cuda(),
+                         roi=torch.from_numpy(vols.roi).cuda(), lab=torch.from_numpy(vols.lab).cuda(), N=vols.N, M=vols.M,
+                         C=torch.empty((vols.N, vols.M), dtype=torch.int32, device="cuda")))
+    print(f"batched items sizes={sizes} points={[s['points'].shape[0] for s in subs]}", flush=True)
+    plan = fc.Plan(subs)
+    for _ in range(3):
+        for s in subs:
+            s["C"].fill_(9)
+        plan.launch()
+        torch.cuda.synchronize()
+        for k, s in enumerate(subs):
+            np.testing.assert_array_equal(s["C"].cpu().numpy().astype(np.int64), exps[k], err_msg=f"subject {k}")
