@@ -20,6 +20,9 @@
 #include "internal.h"
 
 #include <algorithm>
+#include <map>
+#include <mutex>
+#include <tuple>
 
 namespace fc {
 
@@ -1519,13 +1522,30 @@ __global__ void __launch_bounds__(kBlock) k_count_batched(const StreamSubject *_
     }
 }
 
+// Resident workgroups per CU of kernel fn (kBlock threads, dyn bytes of dynamic LDS) on the current device;
+// asked of the runtime once per kernel and size.
+static int resident_blocks(const void *fn, size_t dyn) {
+    static std::mutex mu;
+    static std::map<std::tuple<int, const void *, size_t>, int> known;
+    int dev = 0;
+    (void)hipGetDevice(&dev);
+    std::lock_guard<std::mutex> g(mu);
+    const auto key = std::make_tuple(dev, fn, dyn);
+    const auto it = known.find(key);
+    if (it != known.end()) return it->second;
+    int n = 0;
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, kBlock, dyn);
+    if (e != hipSuccess || n < 1) return 4;
+    if (known.size() >= 4096) known.clear();   // (sizes follow the grids)
+    known[key] = n;
+    return n;
+}
+
 template <bool SCALED, bool PACKED, int B, bool E>
 static int blocks_per_cu_of(size_t dyn) {
     const void *fn = B == 2 ? reinterpret_cast<const void *>(&k_count_stream2<SCALED, PACKED, E, true>)
                             : reinterpret_cast<const void *>(&k_count_stream4<SCALED, PACKED, E, true>);
-    int n = 0;
-    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, kBlock, dyn);
-    return (e == hipSuccess && n > 0) ? n : 4;
+    return resident_blocks(fn, dyn);
 }
 
 template <int B, bool E>
@@ -1536,10 +1556,7 @@ static int blocks_per_cu_b(bool scaled, bool packed, size_t dyn) {
 
 template <int U>
 static int blocks_per_cu_up(size_t dyn) {
-    int n = 0;
-    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &n, reinterpret_cast<const void *>(&k_count_stream_up<U>), kBlock, dyn);
-    return (e == hipSuccess && n > 0) ? n : 4;
+    return resident_blocks(reinterpret_cast<const void *>(&k_count_stream_up<U>), dyn);
 }
 
 int count_stream_blocks_per_cu(bool scaled, bool packed, int batch, bool ends, int up, size_t dyn) {
@@ -1982,10 +1999,7 @@ hipError_t launch_prepare_batched(const StreamSubject *subs, const int64_t *item
 
 template <int B, bool E, int U>
 static int batched_blocks_per_cu_of(size_t dyn) {
-    int n = 0;
-    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &n, reinterpret_cast<const void *>(&k_count_batched<B, E, U>), kBlock, dyn);
-    return (e == hipSuccess && n > 0) ? n : 4;
+    return resident_blocks(reinterpret_cast<const void *>(&k_count_batched<B, E, U>), dyn);
 }
 
 int count_batched_blocks_per_cu(int batch, int coarse_words, BatchedKind kind) {

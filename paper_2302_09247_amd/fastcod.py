@@ -6,6 +6,7 @@ every call raises -- there is no CPU fallback.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import os
 from typing import Optional, Tuple
@@ -162,9 +163,17 @@ def _points_ptr(points: torch.Tensor) -> int:
 
 
 def _stream_ptr(stream) -> Optional[int]:
-    if stream is None:
-        stream = torch.cuda.current_stream()
+    if stream is None:   # (the handle alone: no stream object is made)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return stream.cuda_stream
+
+
+_current = contextlib.nullcontext()
+
+
+def _on(device: torch.device):
+    """torch.cuda.device(device), which sets and restores the device of the thread, only where it is another."""
+    return _current if device.index == torch.cuda.current_device() else torch.cuda.device(device)
 
 
 def _dev(t: torch.Tensor, dtype, name: str, shape=None) -> torch.Tensor:
@@ -182,18 +191,9 @@ def _dev(t: torch.Tensor, dtype, name: str, shape=None) -> torch.Tensor:
 def make_opts(scale: float = 1.0, upsample: int = 1, accumulate: bool = False, validate: bool = False,
               variant: int = VARIANT_AUTO, events: Optional[Tuple[int, int]] = None, batch: int = 0,
               blocks_per_cu: int = 0, mode: int = MODE_PASSTHROUGH, pair_capacity: int = 0) -> Opts:
-    o = load().fastcod_default_opts()
-    o.scale = float(scale)
-    o.upsample = int(upsample)
-    o.flags = (ACCUMULATE if accumulate else 0) | (VALIDATE if validate else 0)
-    o.variant = int(variant)
-    if events is not None:
-        o.event_begin, o.event_end = events
-    o.batch = int(batch)
-    o.blocks_per_cu = int(blocks_per_cu)
-    o.mode = int(mode)
-    o.pair_capacity = int(pair_capacity)
-    return o
+    begin, end = events if events is not None else (None, None)
+    return Opts(float(scale), int(upsample), (ACCUMULATE if accumulate else 0) | (VALIDATE if validate else 0), int(variant),
+                begin, end, int(batch), int(blocks_per_cu), int(mode), int(pair_capacity))
 
 
 def count(points: torch.Tensor, offsets: torch.Tensor, roi: torch.Tensor, lab: torch.Tensor, N: int, M: int, *,
@@ -220,7 +220,7 @@ def count(points: torch.Tensor, offsets: torch.Tensor, roi: torch.Tensor, lab: t
     dims = (ctypes.c_int32 * 3)(int(roi.shape[2]), int(roi.shape[1]), int(roi.shape[0]))
     o = make_opts(scale, upsample, accumulate, validate, variant, events, batch, blocks_per_cu, mode, pair_capacity)
     S = int(offsets.shape[0]) - 1
-    with torch.cuda.device(points.device):
+    with _on(points.device):
         _check(lib.fastcod_count_ex(_points_ptr(points), offsets.data_ptr(), S, roi.data_ptr(), lab.data_ptr(),
                                     dims, int(N), int(M), out.data_ptr(), ctypes.byref(o), _stream_ptr(stream)))
     return out
@@ -273,7 +273,7 @@ class Volume:
         o = make_opts(scale, upsample, accumulate, False, VARIANT_STREAM, events, batch, blocks_per_cu, mode,
                       pair_capacity)
         fn = lib.fastcod_volume_count_noalloc if noalloc else lib.fastcod_volume_count
-        with torch.cuda.device(points.device):
+        with _on(points.device):
             _check(fn(self._h, _points_ptr(points), offsets.data_ptr(), int(offsets.shape[0]) - 1, out.data_ptr(),
                       ctypes.byref(o), _stream_ptr(stream)))
         return out
@@ -304,7 +304,7 @@ def parcellate(C: torch.Tensor, labels: bool = True, fractions: bool = True, sum
     frac = torch.empty((N, M), dtype=torch.float32, device=C.device) if fractions else None
     sm = torch.empty(N, dtype=torch.int64, device=C.device) if sums else None
     ptr = lambda t: t.data_ptr() if t is not None and t.numel() else None   # noqa: E731
-    with torch.cuda.device(C.device):
+    with _on(C.device):
         st = _stream_ptr(stream)
         hip = None
         if events is not None:
@@ -377,7 +377,7 @@ class Plan:
         self.device = dev
 
     def launch(self, stream=None) -> None:
-        with torch.cuda.device(self.device):
+        with _on(self.device):
             _check(load().fastcod_plan_launch(self._h, _stream_ptr(stream)))
 
     @property
@@ -526,7 +526,7 @@ def _sink(device):
 def probe_stream(points: torch.Tensor, stream=None) -> None:
     """Reads every point once (12 bytes each) with the counting kernel's access pattern."""
     _dev(points, torch.float32, "points", (3,))
-    with torch.cuda.device(points.device):
+    with _on(points.device):
         _check(load().fastcod_probe_stream(_points_ptr(points), int(points.shape[0]), _sink(points.device),
                                            _stream_ptr(stream)))
 
@@ -544,6 +544,6 @@ def probe_atomics(target: torch.Tensor, idx: torch.Tensor, stream=None) -> None:
 def probe_lookup(vol: "Volume", points: torch.Tensor, scale: float = 1.0, stream=None) -> None:
     """The point stream plus every point's lookups in the resident volume (no de-duplication, no C)."""
     _dev(points, torch.float32, "points", (3,))
-    with torch.cuda.device(points.device):
+    with _on(points.device):
         _check(load().fastcod_probe_lookup(vol.handle, _points_ptr(points), int(points.shape[0]), float(scale),
                                            _sink(points.device), _stream_ptr(stream)))
