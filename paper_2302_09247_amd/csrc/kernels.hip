@@ -1818,26 +1818,55 @@ __global__ void __launch_bounds__(kBlock) k_fallback_batched(const StreamSubject
 // Alg. 1's seed-to-endpoint count
 // ---------------------------------------------------------------------------------------------
 
-// C(row of the first point, label of the last point) += 1 per streamline (the seed is the first
-// point).  One thread per streamline.
+// C(row of the first point, label of the last point) += 1 for streamlines [sb, S) (the seed is the first
+// point).  A wavefront takes 63 streamlines at a time: lane k reads offset k of the 64 around them and
+// the two points beside it, the last of one streamline and the first of the next (24 bytes, mostly of
+// one line), and passes the last one to the lane before it; the label is looked up only where the row
+// was found.  Bound by the scattered reads: one thread per streamline with both points and both lookups
+// of its own took 46 us for a million streamlines.
+template <typename Lookup, bool SCALED>
+__device__ __forceinline__ void seed_end_streamlines(const float *__restrict__ pts, const int64_t *__restrict__ offsets,
+                                                     int64_t sb, int64_t S, float scale, const Grid &g, const Lookup &lk,
+                                                     int32_t *__restrict__ C, uint32_t si, uint32_t sm) {
+    constexpr int kLines = kWave - 1;
+    const int lane = lane_id();
+    const auto offs = gview(offsets);
+    const int64_t Ptot = offs[S] > 0 ? offs[S] : 0;
+    const int64_t waves = (int64_t)gridDim.x * (blockDim.x / kWave);
+    const int64_t wave = (int64_t)blockIdx.x * (blockDim.x / kWave) + (threadIdx.x >> 6);
+    for (int64_t s0 = sb + wave * kLines; s0 < S; s0 += waves * kLines) {   // (uniform over the wavefront)
+        const int64_t s = s0 + lane;
+        const int64_t o = clamp64(offs[min(s, S)], 0, Ptot);
+        // points o - 1 and o, where they exist
+        float e[3] = {NAN, NAN, NAN}, f[3] = {NAN, NAN, NAN};
+        const auto p = gview(pts) + 3 * o;
+        if (o > 0) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) e[k] = p[k - 3];
+        }
+        if (o < Ptot) {
+#pragma unroll
+            for (int k = 0; k < 3; ++k) f[k] = p[k];
+        }
+        // streamline s = [o, next): its last point is the next lane's e
+        const int64_t next = __shfl_down(o, 1);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) e[k] = __shfl_down(e[k], 1);
+        int r = -1, m = -1, none;
+        if (lane < kLines && s < S && next > o) lookup_point<Lookup, SCALED>(f, scale, g, lk, r, none);
+        if (r >= 0) lookup_point<Lookup, SCALED>(e, scale, g, lk, none, m);
+        if (m >= 0) add_one(C + ((uint32_t)r * si + (uint32_t)m * sm));
+    }
+}
+
 template <typename Lookup, bool SCALED>
 __global__ void k_count_seed_end(CountArgs a, Lookup lk) {
-    const int64_t Ptot = a.offsets[a.S] > 0 ? a.offsets[a.S] : 0;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < a.S; s += stride) {
-        const int64_t b0 = clamp64(a.offsets[s], 0, Ptot);
-        const int64_t b1 = clamp64(a.offsets[s + 1], b0, Ptot);
-        if (b1 <= b0) continue;
-        int r, m, r2, m2;
-        lookup_point<Lookup, SCALED>(a.pts + 3 * b0, a.scale, a.g, lk, r, m);
-        lookup_point<Lookup, SCALED>(a.pts + 3 * (b1 - 1), a.scale, a.g, lk, r2, m2);
-        if (r >= 0 && m2 >= 0) atomicAdd(a.C + (uint32_t)r * a.si + (uint32_t)m2 * a.sm, 1);
-    }
+    seed_end_streamlines<Lookup, SCALED>(a.pts, a.offsets, 0, a.S, a.scale, a.g, lk, a.C, a.si, a.sm);
 }
 
 template <typename Lookup>
 static void launch_seed_end_l(const CountArgs &a, const Lookup &lk, int cus, hipStream_t st) {
-    const unsigned blocks = fill_blocks(a.S, cus);
+    const unsigned blocks = fill_blocks(a.S / (kWave - 1) * kWave + kWave, cus);
     if (a.scale != 1.0f) k_count_seed_end<Lookup, true><<<blocks, kBlock, 0, st>>>(a, lk);
     else k_count_seed_end<Lookup, false><<<blocks, kBlock, 0, st>>>(a, lk);
 }
@@ -2037,23 +2066,11 @@ hipError_t launch_count_batched(const StreamSubject *subs, int32_t nsub, const i
     return hipGetLastError();
 }
 
-// Alg. 1's count for table entries [lo, lo + gridDim.y): C(row of the first point, label of the last
-// point) += 1 for streamlines [s_begin, S) of each, as k_count_seed_end for one subject.
+// Alg. 1's count for table entries [lo, lo + gridDim.y): streamlines [s_begin, S) of each.
 __global__ void k_count_seed_end_batched(const StreamSubject *__restrict__ subs, int32_t lo) {
     const StreamSubject &sub = subs[lo + blockIdx.y];
-    const int64_t Ptot = sub.offsets[sub.S] > 0 ? sub.offsets[sub.S] : 0;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const CompactLookup lk{sub.cv};
-    for (int64_t s = clamp64(sub.s_begin, 0, sub.S) + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < sub.S;
-         s += stride) {
-        const int64_t b0 = clamp64(sub.offsets[s], 0, Ptot);
-        const int64_t b1 = clamp64(sub.offsets[s + 1], b0, Ptot);
-        if (b1 <= b0) continue;
-        int r, m, r2, m2;
-        lookup_point<CompactLookup, true>(sub.pts + 3 * b0, sub.scale, sub.g, lk, r, m);
-        lookup_point<CompactLookup, true>(sub.pts + 3 * (b1 - 1), sub.scale, sub.g, lk, r2, m2);
-        if (r >= 0 && m2 >= 0) atomicAdd(sub.C + (uint32_t)r * sub.si + (uint32_t)m2 * sub.sm, 1);
-    }
+    seed_end_streamlines<CompactLookup, true>(sub.pts, sub.offsets, clamp64(sub.s_begin, 0, sub.S), sub.S, sub.scale, sub.g,
+                                              CompactLookup{sub.cv}, sub.C, sub.si, sub.sm);
 }
 
 hipError_t launch_count_seed_end_batched(const StreamSubject *subs, int32_t lo, int32_t n, int cus, hipStream_t st) {

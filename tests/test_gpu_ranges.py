@@ -105,3 +105,24 @@ def test_batched_items(fc, sizes):
         torch.cuda.synchronize()
         for k, s in enumerate(subs):
             np.testing.assert_array_equal(s["C"].cpu().numpy().astype(np.int64), exps[k], err_msg=f"subject {k}")
+
+
+@pytest.mark.parametrize("S", [1, 62, 63, 64, 65, 126, 127, 5000])
+def test_seed_end_lines(fc, S):
+    # a wavefront counts 63 streamlines at a time; one-point and empty ones, also at the ends
+    pts, off, vols = _case(S, False, 500 + S)
+    off = np.concatenate([off[:1], off]) if S % 2 else off
+    if off[-1] == 0:
+        off[-1] = 1
+    pts = pts[: int(off[-1])] if len(pts) >= off[-1] else np.full((int(off[-1]), 3), 20, np.float32)
+    exp = oracle.count(pts, off, vols.roi, vols.lab, vols.N, vols.M, mode=3)
+    dev = [torch.from_numpy(a).cuda() for a in (pts, off, vols.roi, vols.lab)]
+    print(f"seed end S={S}", flush=True)
+    C = torch.empty((vols.N, vols.M), dtype=torch.int32, device="cuda")
+    plan = fc.Plan([dict(points=dev[0], offsets=dev[1], roi=dev[2], lab=dev[3], N=vols.N, M=vols.M, C=C, mode=3)])
+    plan.launch()
+    for variant in (1, 2):
+        got = fc.count(*dev, vols.N, vols.M, mode=3, variant=variant)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(got.cpu().numpy().astype(np.int64), exp, err_msg=f"variant {variant}")
+    np.testing.assert_array_equal(C.cpu().numpy().astype(np.int64), exp, err_msg="plan")
