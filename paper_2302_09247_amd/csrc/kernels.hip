@@ -5,7 +5,7 @@
 // (loc2region applied to its points) are formed, and every (row, label) pair of the two sets adds
 // one to C.  The stages here:
 //   * compact volume build: one pass over both volumes -> occupancy bits + packed codes;
-//   * partition: chunks of whole streamlines, equal or tapering (a binary search per chunk); the same
+//   * partition: tapering ranges of whole streamlines (one pass over the offsets); the same
 //     launch zeroes the call's per-call state;
 //   * count kernels (wave-per-streamline over raster volumes, or flat point stream over the
 //     compact volume): voxelise each point, look it up, de-duplicate the hits of each streamline
@@ -1463,8 +1463,8 @@ __global__ void __launch_bounds__(kBlock) k_count_stream_up(StreamSubject sub, O
     sink.drain(po, wave);
 }
 
-// Batched form: work items (subject, first streamline) from every subject, handed out by one
-// counter; each wavefront keeps the coarse map of the subject it last worked on in its own LDS.
+// Batched form: work items (subject, first streamline) from every subject, handed out by the
+// queues; each wavefront keeps the coarse map of the subject it last worked on in its own LDS.
 // The scale is always applied (multiplying by 1.0f is exact), the code width is read per subject.
 // One instantiation per kind of subject: pass-through (kEnds false, kUp 1), the endpoint modes
 // (kEnds: end labels at each close), and upsampled pass-through (kUp 2 or 4, with
