@@ -161,6 +161,29 @@ hipError_t launch_fill_u64(unsigned long long *p, int64_t n, int cus, hipStream_
 hipError_t launch_compact_build(const int32_t *roi, const int32_t *lab, Grid g, CompactVol cv, uint2 *mb, void *codes,
                                 uint32_t *coarse, uint32_t *ncodes, hipStream_t st);
 
+// The 4 voxels x .. x + 3 of a row of X that one lane of the build reads: it loads elements xs .. xs + 3
+// (kWide: rows of at least 4 voxels, the last 4 where x .. x + 3 pass the end), `mine` are those inside its
+// 4 voxels and the row, and element d of the load is voxel x.  d <= 3 also in lanes past the end of the row,
+// whose `mine` is empty: they shift by it all the same.
+struct RowLane {
+    int32_t xs;
+    int d;
+    uint32_t mine;
+};
+template <bool kWide>
+__host__ __device__ inline RowLane row_lane(int32_t x, int32_t X) {
+    RowLane r{x, 0, 0u};
+    if (kWide) {
+        if (r.xs > X - 4) r.xs = X - 4;
+        r.d = x - r.xs < 3 ? x - r.xs : 3;
+        if (x < X) r.mine = (0xFu << r.d) & 0xFu;
+    } else {
+        if (r.xs > X - 1) r.xs = X - 1;
+        if (x < X) r.mine = 0xFu >> (x + 4 > X ? x + 4 - X : 0);
+    }
+    return r;
+}
+
 // Per-call state zeroed by the partition launch, so that it needs no launches of its own: C when
 // it is not accumulated into, a fixed scratch area's fallback bit maps, the coarse map of a volume built by the same call, the overflow and range counters.  Each
 // range may be empty.

@@ -542,11 +542,10 @@ k_compact_build(const int32_t *__restrict__ roi, const int32_t *__restrict__ lab
     const int32_t xc = 2 * xg + (wv & 1);
     const int q = lane & 15, rr = lane >> 4;
     const int32_t x = xc * 64 + 4 * q;
-    const int32_t xs = kWide ? min(x, g.X - 4) : min(x, g.X - 1);
-    const int d = kWide ? x - xs : 0;   // elements below d belong to other lanes
-    uint32_t mine;                      // this lane's elements inside the row
-    if (x >= g.X) mine = 0u;
-    else mine = kWide ? (0xFu << d) & 0xFu : 0xFu >> max(0, x + 4 - g.X);
+    const RowLane rl = row_lane<kWide>(x, g.X);
+    const int32_t xs = rl.xs;
+    const int d = rl.d;
+    const uint32_t mine = rl.mine;
     // codes in registers: packed (c0), or row and label (c0, c1)
     uint32_t c0[kSteps][4], c1[PACKED ? 1 : kSteps][4];
     uint32_t word[kSteps];
