@@ -864,20 +864,21 @@ struct fastcod_volume {
 };
 
 namespace {
-// Orders st after the volume's build.  Once the build is complete there is nothing to wait for (a wait
-// enqueued on each call took about 1.5 us); a stream under capture is left to the wait, whose outcome it
-// decides.
+// Orders st after the volume's build.  Once the build has been seen complete an eager call has nothing to wait
+// for (a wait enqueued on each call took about 1.5 us).  A stream under capture is left to the wait in every
+// case, so that what capture makes of it does not depend on the calls before it; and an error that the
+// caller left in the runtime stays there, for the launches' own checks.
 hipError_t after_build(const fastcod_volume *cvol, hipStream_t st) {
     fastcod_volume *vol = const_cast<fastcod_volume *>(cvol);
-    if (vol->built.load(std::memory_order_acquire)) return hipSuccess;
+    const bool clean = hipPeekAtLastError() == hipSuccess;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone) {
-        if (hipEventQuery(vol->ready) == hipSuccess) {
-            vol->built.store(true, std::memory_order_release);
-            return hipSuccess;
-        }
+    const bool eager = hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
+    if (eager && vol->built.load(std::memory_order_acquire)) return hipSuccess;
+    if (eager && clean && hipEventQuery(vol->ready) == hipSuccess) {
+        vol->built.store(true, std::memory_order_release);
+        return hipSuccess;
     }
-    (void)hipGetLastError();
+    if (clean) (void)hipGetLastError();   // "not ready", from the query
     return hipStreamWaitEvent(st, vol->ready, 0);
 }
 }  // namespace
