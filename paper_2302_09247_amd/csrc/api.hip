@@ -870,10 +870,12 @@ namespace {
 // caller left in the runtime stays there, for the launches' own checks.
 hipError_t after_build(const fastcod_volume *cvol, hipStream_t st) {
     fastcod_volume *vol = const_cast<fastcod_volume *>(cvol);
+    const bool built = vol->built.load(std::memory_order_acquire);
+    if (built && !st) return hipSuccess;   // the null stream cannot be captured
     const bool clean = hipPeekAtLastError() == hipSuccess;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    const bool eager = hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone;
-    if (eager && vol->built.load(std::memory_order_acquire)) return hipSuccess;
+    const bool eager = !st || (hipStreamIsCapturing(st, &cs) == hipSuccess && cs == hipStreamCaptureStatusNone);
+    if (eager && built) return hipSuccess;
     if (eager && clean && hipEventQuery(vol->ready) == hipSuccess) {
         vol->built.store(true, std::memory_order_release);
         return hipSuccess;
