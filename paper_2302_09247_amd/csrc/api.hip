@@ -242,7 +242,7 @@ int make_count_plan(int64_t S, int32_t N, int32_t M, const fc::CompactVol *cv, c
     // wavefront's point ranges are long enough to amortise their deeper pipeline start
     const bool long_ranges = S >= kLongRangesFrom;
     cp.batch = o.batch != 0 ? o.batch : (long_ranges ? 4 : 2);
-    int per_cu = fc::count_stream_blocks_per_cu(o.scale != 1.0f, cv->packed != 0, cp.batch, cp.ends, o.upsample,
+    int per_cu = fc::count_stream_blocks_per_cu(o.scale != 1.0f, cp.batch, cp.ends, o.upsample,
                                                 fc::coarse_lds_bytes(cv->ncoarse_words));
     if (o.blocks_per_cu > 0 && o.blocks_per_cu < per_cu) per_cu = o.blocks_per_cu;
     cp.blocks = (int64_t)cus * per_cu;

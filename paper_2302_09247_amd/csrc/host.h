@@ -109,7 +109,6 @@ struct CompactLayout {
     int32_t SBX, SBY, SBZ;
     int64_t W;        // words
     int64_t nvox;
-    bool packed;
     int32_t rbits;
     int32_t csx, csyz, CBX, CBY, CBZ, ncoarse_words;
     int64_t ncodes;   // capacity of the code array (every voxel unless sized by compact_layout_fit)
@@ -126,11 +125,13 @@ inline bool compact_layout(const int32_t dims[3], int32_t N, int32_t M, CompactL
     // word indices are uint32 and padding must stay modest (thin grids use raster lookups)
     if (L.W >= (int64_t(1) << 31) || L.W * 32 > 8 * L.nvox + (int64_t(1) << 22)) return false;
     if ((int64_t)L.SBX * L.SBY >= (int64_t(1) << 31)) return false;
+    // one 32-bit code holds a row and a label, and in each field a value that is none: N >= 2^(rb - 1) and
+    // M >= 2^(lb - 1), so N*M < 2^31 (check_volume_args) gives rb + lb - 2 <= 30
     const int rb = bit_width((uint32_t)N), lb = bit_width((uint32_t)M);
-    L.packed = rb + lb <= 32;
+    if (rb + lb > 32) return false;
     L.rbits = rb;
     // buffer-resource offsets are 32-bit: occupancy pairs and codes must stay below 4 GB
-    if (8 * L.W >= (int64_t(1) << 32) || (L.packed ? 4 : 8) * L.nvox >= (int64_t(1) << 32)) return false;
+    if (8 * L.W >= (int64_t(1) << 32) || 4 * L.nvox >= (int64_t(1) << 32)) return false;
     // coarse occupancy (kept in LDS by the counting kernel): one bit per 16x8x8 super-brick when
     // brick_coarse is asked for and the map fits max_coarse_words (the kernel then reuses the
     // super-brick index), else the smallest cube side 8, 16 or 32 whose map fits
@@ -152,7 +153,7 @@ inline bool compact_layout(const int32_t dims[3], int32_t N, int32_t M, CompactL
     L.off_coarse = align(L.off_mb + 8 * (size_t)L.W);
     L.off_codes = align(L.off_coarse + 4 * (size_t)(kCoarseHead + L.ncoarse_words));
     L.ncodes = L.nvox;
-    L.bytes = L.off_codes + (L.packed ? 4 : 8) * (size_t)L.nvox;   // at most every voxel occupied
+    L.bytes = L.off_codes + 4 * (size_t)L.nvox;   // at most every voxel occupied
     // the counting kernel reads pairs and codes through one buffer resource with 32-bit offsets
     if (L.bytes >= (size_t(1) << 32) - 16) return false;
     return true;
@@ -162,7 +163,7 @@ inline bool compact_layout(const int32_t dims[3], int32_t N, int32_t M, CompactL
 // 0 <= lab < M, the test the build uses to set occupancy bits (counted by the caller).
 inline void compact_layout_fit(CompactLayout &L, int64_t occupied) {
     L.ncodes = occupied;
-    L.bytes = L.off_codes + (L.packed ? 4 : 8) * (size_t)(occupied > 0 ? occupied : 1);
+    L.bytes = L.off_codes + 4 * (size_t)(occupied > 0 ? occupied : 1);
 }
 
 inline fc::CompactVol compact_view(void *buf, const CompactLayout &L, int32_t N, int32_t M) {
@@ -175,19 +176,17 @@ inline fc::CompactVol compact_view(void *buf, const CompactLayout &L, int32_t N,
     cv.CBX = L.CBX;
     cv.CBXY = L.CBX * L.CBY;
     cv.ncoarse_words = L.ncoarse_words;
-    cv.codes32 = reinterpret_cast<const uint32_t *>(b + L.off_codes);
-    cv.codes64 = reinterpret_cast<const int2 *>(b + L.off_codes);
+    cv.codes = reinterpret_cast<const uint32_t *>(b + L.off_codes);
     cv.SBX = L.SBX;
     cv.SBXY = L.SBX * L.SBY;
     cv.rbits = L.rbits;
-    cv.rmask = L.rbits >= 32 ? 0xFFFFFFFFu : ((1u << L.rbits) - 1u);
+    cv.rmask = (1u << L.rbits) - 1u;   // (the label field has at least one bit)
     cv.N = N;
     cv.M = M;
-    cv.packed = L.packed ? 1 : 0;
     cv.W = L.W;
     cv.ncodes = L.ncodes;
     cv.codes_off = (uint32_t)L.off_codes;
-    cv.span = (uint32_t)(L.off_codes + (L.packed ? 4 : 8) * (size_t)L.ncodes);
+    cv.span = (uint32_t)(L.off_codes + 4 * (size_t)L.ncodes);
     return cv;
 }
 
@@ -222,7 +221,7 @@ inline hipError_t enqueue_compact_build(const int32_t *roi, const int32_t *lab, 
         if (e != hipSuccess) return e;
     }
     return fc::launch_compact_build(roi, lab, make_grid(dims), cv, reinterpret_cast<uint2 *>(b + L.off_mb),
-                                    b + L.off_codes, reinterpret_cast<uint32_t *>(zero) + kCoarseHead,
+                                    reinterpret_cast<uint32_t *>(b + L.off_codes), reinterpret_cast<uint32_t *>(zero) + kCoarseHead,
                                     reinterpret_cast<uint32_t *>(zero), st);
 }
 

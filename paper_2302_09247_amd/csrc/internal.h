@@ -36,13 +36,11 @@ struct CompactVol {
                               // 4,3 (one 16x8x8 super-brick per block, coarse index = super-brick index)
     int32_t CBX, CBXY;        // coarse blocks along x, and per z-slab
     int32_t ncoarse_words;    // words of `coarse` (a multiple of 2)
-    const uint32_t *codes32;  // packed (row | label << rbits), if packed
-    const int2 *codes64;      // (row, label) pairs, if not packed
+    const uint32_t *codes;    // row | label << rbits; all ones in a field: none
     int32_t SBX, SBXY;        // super-bricks along x, and per z-slab
-    int32_t rbits;            // bits of the row field in a packed code
+    int32_t rbits;            // bits of the row field in a code (at most 31)
     uint32_t rmask;           // (1 << rbits) - 1
     int32_t N, M;
-    int32_t packed;
     int64_t W;                // occupancy words
     int64_t ncodes;           // capacity of the code array (bounds of every code read)
     uint32_t codes_off;       // byte offset of the code array from mb (one allocation)
@@ -158,7 +156,7 @@ hipError_t launch_fill_u64(unsigned long long *p, int64_t n, int cus, hipStream_
 
 // compact volume build: cv's layout and sizes, written through mb (W {word, base} pairs), codes and
 // coarse (ncoarse_words, zero on entry); ncodes: the number of codes written (zero on entry)
-hipError_t launch_compact_build(const int32_t *roi, const int32_t *lab, Grid g, CompactVol cv, uint2 *mb, void *codes,
+hipError_t launch_compact_build(const int32_t *roi, const int32_t *lab, Grid g, CompactVol cv, uint2 *mb, uint32_t *codes,
                                 uint32_t *coarse, uint32_t *ncodes, hipStream_t st);
 
 // The 4 voxels x .. x + 3 of a row of X that one lane of the build reads: it loads elements xs .. xs + 3
@@ -208,7 +206,7 @@ struct Ranges {
 // LDS of a workgroup's copy of a coarse map, stored 16 bytes at a time
 inline size_t coarse_lds_bytes(int32_t words) { return 4 * (size_t)((words + 3) & ~3); }
 // resident 256-thread workgroups per CU of the flat-stream kernel
-int count_stream_blocks_per_cu(bool scaled, bool packed, int batch, bool ends, int up, size_t dyn_lds);
+int count_stream_blocks_per_cu(bool scaled, int batch, bool ends, int up, size_t dyn_lds);
 
 hipError_t launch_count_wave(const CountArgs &a, const RasterVol &rv, int blocks, hipStream_t st);
 // parcellation outputs of C [N][M]: label [N], frac [N][M], sums [N] (each may be null)

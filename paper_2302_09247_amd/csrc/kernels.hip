@@ -108,16 +108,10 @@ __device__ __forceinline__ void compact_get(const CompactVol &c, int ix, int iy,
     m = -1;
     if (!((e.x >> bit) & 1u)) return;
     const uint32_t rank = e.y + __popc(e.x & ((1u << bit) - 1u));
-    if (c.packed) {
-        const uint32_t code = c.codes32[rank];
-        const uint32_t rv = code & c.rmask, mv = code >> c.rbits;
-        r = rv < (uint32_t)c.N ? (int)rv : -1;
-        m = mv < (uint32_t)c.M ? (int)mv : -1;
-    } else {
-        const int2 code = c.codes64[rank];
-        r = code.x;
-        m = code.y;
-    }
+    const uint32_t code = c.codes[rank];
+    const uint32_t rv = code & c.rmask, mv = code >> c.rbits;
+    r = rv < (uint32_t)c.N ? (int)rv : -1;
+    m = mv < (uint32_t)c.M ? (int)mv : -1;
 }
 
 struct RasterLookup {
@@ -524,10 +518,10 @@ constexpr int kBuildSteps = 4;                   // steps of a wavefront: two a 
 constexpr int kBuildParts = 16 / kBuildSteps;    // wavefronts per super-brick along z
 constexpr int kBuildWaves = 2 * kBuildParts;     // two 64-voxel chunks along x
 constexpr int64_t kBuildCachedVoxels = int64_t(1) << 23;   // 64 MB of volumes
-template <bool PACKED, bool kWide, bool kNt>
+template <bool kWide, bool kNt>
 __global__ void __launch_bounds__(kBuildWaves *kWave)
 k_compact_build(const int32_t *__restrict__ roi, const int32_t *__restrict__ lab, Grid g, CompactVol cv, int32_t SBY,
-                uint2 *__restrict__ mb, void *__restrict__ codes, uint32_t *__restrict__ coarse,
+                uint2 *__restrict__ mb, uint32_t *__restrict__ codes, uint32_t *__restrict__ coarse,
                 uint32_t *__restrict__ ncodes) {
     __shared__ uint32_t s_cnt[8 * kBuildParts];   // codes of (super-brick, part)
     __shared__ uint32_t s_any[kBuildWaves];       // occupied 8-voxel halves of a wavefront's super-bricks
@@ -546,8 +540,7 @@ k_compact_build(const int32_t *__restrict__ roi, const int32_t *__restrict__ lab
     const int32_t xs = rl.xs;
     const int d = rl.d;
     const uint32_t mine = rl.mine;
-    // codes in registers: packed (c0), or row and label (c0, c1)
-    uint32_t c0[kSteps][4], c1[PACKED ? 1 : kSteps][4];
+    uint32_t code[kSteps][4];
     uint32_t word[kSteps];
     uint32_t occ = 0u;   // 4 bits a step: this lane's occupied elements
     const int at_bit = 4 * (q & 3) + 16 * (rr & 1);
@@ -579,15 +572,9 @@ k_compact_build(const int32_t *__restrict__ roi, const int32_t *__restrict__ lab
         for (int i = 0; i < 4; ++i) {
             const bool rv = (unsigned)r[i] < (unsigned)cv.N, mv = (unsigned)m[i] < (unsigned)cv.M;
             // (all ones: neither a row nor a label, as both fields hold a value that is none)
-            if (PACKED) {
-                c0[st][i] = (rv ? (uint32_t)r[i] : cv.rmask) |
-                            ((mv ? (uint32_t)m[i] : (0xFFFFFFFFu >> cv.rbits)) << cv.rbits);
-                o |= min(~c0[st][i], 1u) << i;
-            } else {
-                c0[st][i] = rv ? (uint32_t)r[i] : 0xFFFFFFFFu;
-                c1[st][i] = mv ? (uint32_t)m[i] : 0xFFFFFFFFu;
-                o |= min(~(c0[st][i] & c1[st][i]), 1u) << i;
-            }
+            code[st][i] = (rv ? (uint32_t)r[i] : cv.rmask) |
+                          ((mv ? (uint32_t)m[i] : (0xFFFFFFFFu >> cv.rbits)) << cv.rbits);
+            o |= min(~code[st][i], 1u) << i;
         }
         o &= (y < g.Y && z < g.Z) ? mine : 0u;
         occ |= o << (4 * st);
@@ -665,28 +652,21 @@ k_compact_build(const int32_t *__restrict__ roi, const int32_t *__restrict__ lab
         uint32_t at = bases[st] + (uint32_t)__popc(word[st] & ((1u << at_bit) - 1u));
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            if ((o >> i) & 1u) {
-                if (PACKED) static_cast<uint32_t *>(codes)[at] = c0[st][i];
-                else static_cast<int2 *>(codes)[at] = make_int2((int)c0[st][i], (int)c1[PACKED ? 0 : st][i]);
-                ++at;
-            }
+            if ((o >> i) & 1u) codes[at++] = code[st][i];
     }
 }
 
-hipError_t launch_compact_build(const int32_t *roi, const int32_t *lab, Grid g, CompactVol cv, uint2 *mb, void *codes,
+hipError_t launch_compact_build(const int32_t *roi, const int32_t *lab, Grid g, CompactVol cv, uint2 *mb, uint32_t *codes,
                                 uint32_t *coarse, uint32_t *ncodes, hipStream_t st) {
     const int32_t SBY = cv.SBXY / cv.SBX;
     const int64_t SBZ = cv.W / 32 / cv.SBXY;
     const unsigned blocks = (unsigned)((int64_t)((cv.SBX + 7) / 8) * SBY * SBZ);
     const bool wide = g.X >= 4, nt = (int64_t)g.X * g.Y * g.Z > kBuildCachedVoxels;
-#define FC_BUILD(P_, W_, T_) \
-    k_compact_build<P_, W_, T_><<<blocks, kBuildWaves * kWave, 0, st>>>(roi, lab, g, cv, SBY, mb, codes, coarse, ncodes)
-    if (cv.packed && wide && nt) FC_BUILD(true, true, true);
-    else if (cv.packed && wide) FC_BUILD(true, true, false);
-    else if (cv.packed) FC_BUILD(true, false, false);
-    else if (wide && nt) FC_BUILD(false, true, true);
-    else if (wide) FC_BUILD(false, true, false);
-    else FC_BUILD(false, false, false);
+#define FC_BUILD(W_, T_) \
+    k_compact_build<W_, T_><<<blocks, kBuildWaves * kWave, 0, st>>>(roi, lab, g, cv, SBY, mb, codes, coarse, ncodes)
+    if (wide && nt) FC_BUILD(true, true);
+    else if (wide) FC_BUILD(true, false);
+    else FC_BUILD(false, false);
 #undef FC_BUILD
     return hipGetLastError();
 }
@@ -974,9 +954,9 @@ __device__ __forceinline__ RangeBounds range_bounds(const int64_t *offsets, int6
 }
 
 // Counts streamlines [s0, s1) of one subject (whole streamlines only) into sub.C through `sink`.
-// `coarse` is the subject's coarse occupancy map in LDS.  PACKED: 0/1 = code width known at compile
-// time, 2 = read from cv.packed.
-template <bool SCALED, int PACKED, int kBatch, bool kEnds, int kUp, bool kBrick, typename Sink>
+// `coarse` is the subject's coarse occupancy map in LDS.  kCodesFirst: a batch's codes are awaited before the
+// next batch's pair gathers are issued (see the pipeline below).
+template <bool SCALED, int kBatch, bool kEnds, int kUp, bool kBrick, bool kCodesFirst, typename Sink>
 __device__ void stream_range(const StreamSubject &sub, const uint32_t *coarse, const RangeBounds &rb, int32_t subject,
                              const Overflow &ovf, StreamSet &set, Sink &sink) {
     constexpr int kV = kBatch * kUp;   // lookups per batch: kUp sub-points of each of kBatch windows
@@ -1286,7 +1266,10 @@ __device__ void stream_range(const StreamSubject &sub, const uint32_t *coarse, c
     // codes return and its tail runs.  Vector-memory loads complete in issue order, so each
     // iteration issues: the codes of k, the pairs of k + 1, the points of k + 2; batch k's decode
     // then waits for its codes only, and the next iteration's flags for the pairs of k + 1 only.
-    const bool packed = PACKED == 1 || (PACKED == 2 && cv.packed);
+    // kCodesFirst (the batched pass-through kernel) waits for the codes of k before the pairs of k + 1: its
+    // updates are atomics, and where they are the bound it gains more from fewer loads beside them than
+    // it loses by the wait.  A plan of 12 subjects of 200M points and 75M entries of C takes 1094 us a
+    // launch with and 1112 without it, one of 4 subjects of 87M points and 14M entries 299 and 294.
     const uint32_t code_oob = kOutOfRange - (uint32_t)codes_off;   // with the code offset: past the resource
     uint32_t bix[kV], mw[kV], rank[kV];
     {
@@ -1304,19 +1287,11 @@ __device__ void stream_range(const StreamSubject &sub, const uint32_t *coarse, c
         bool flag[kV];
 #pragma unroll
         for (int v = 0; v < kV; ++v) flag[v] = __builtin_amdgcn_ubfe(mw[v], bix[v], 1) != 0u;
-        uint32_t c0[kV], c1[kV];
+        uint32_t code[kV];
 #pragma unroll
         for (int v = 0; v < kV; ++v) {
             const uint32_t at = rank[v] + __popc(__builtin_amdgcn_ubfe(mw[v], 0, bix[v]));
-            if (packed) {
-                c0[v] = __builtin_amdgcn_raw_buffer_load_b32(rvol, flag[v] ? at << 2 : code_oob, codes_off, kAuxCached);
-                c1[v] = 0u;
-            } else {
-                const auto c2 = __builtin_amdgcn_raw_buffer_load_b64(rvol, flag[v] ? at << 3 : code_oob, codes_off,
-                                                                     kAuxCached);
-                c0[v] = c2[0];
-                c1[v] = c2[1];
-            }
+            code[v] = __builtin_amdgcn_raw_buffer_load_b32(rvol, flag[v] ? at << 2 : code_oob, codes_off, kAuxCached);
         }
         __builtin_amdgcn_sched_barrier(0);
         // lookups and pair gathers of batch k + 1 (its points arrived during the last iteration),
@@ -1325,6 +1300,8 @@ __device__ void stream_range(const StreamSubject &sub, const uint32_t *coarse, c
         {
             uint32_t addr[kV];
             lookup(w0 + BW, addr, bix2);
+            __builtin_amdgcn_sched_barrier(0);
+            if (kCodesFirst) __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
             __builtin_amdgcn_sched_barrier(0);
             gather_pairs(addr, mw2, rank2);
         }
@@ -1335,14 +1312,9 @@ __device__ void stream_range(const StreamSubject &sub, const uint32_t *coarse, c
         int r[kV], m[kV];
 #pragma unroll
         for (int v = 0; v < kV; ++v) {
-            if (packed) {
-                const uint32_t rv = c0[v] & cv.rmask, mv = c0[v] >> cv.rbits;
-                r[v] = (flag[v] && rv < (uint32_t)cv.N) ? (int)rv : -1;
-                m[v] = (flag[v] && mv < (uint32_t)cv.M) ? (int)mv : -1;
-            } else {
-                r[v] = flag[v] ? (int)c0[v] : -1;
-                m[v] = flag[v] ? (int)c1[v] : -1;
-            }
+            const uint32_t rv = code[v] & cv.rmask, mv = code[v] >> cv.rbits;
+            r[v] = (flag[v] && rv < (uint32_t)cv.N) ? (int)rv : -1;
+            m[v] = (flag[v] && mv < (uint32_t)cv.M) ? (int)mv : -1;
         }
         tail(w0, r, m, flag);
 #pragma unroll
@@ -1396,7 +1368,7 @@ __device__ __forceinline__ void for_each_range(const Ranges &rg, const StreamSub
 }
 
 // The flat-stream kernel's body: the wavefront's ranges, pair updates through its append sink.
-template <bool SCALED, bool PACKED, int kBatch, bool kEnds, bool kBrick>
+template <bool SCALED, int kBatch, bool kEnds, bool kBrick>
 __device__ __forceinline__ void count_stream_body(const StreamSubject &sub, const Overflow &ovf,
                                                   const Ranges &rg, const PairOut &po) {
     // 4-window batches run 6 wavefronts per SIMD (their scalar registers), so they can afford the
@@ -1416,7 +1388,7 @@ __device__ __forceinline__ void count_stream_body(const StreamSubject &sub, cons
     AppendSink<kSinkCap> sink;
     sink.init(s_pend + wv * kSinkCap, sub.C, po, wave);
     for_each_range(rg, sub, ovf, wave, rb, [&](const RangeBounds &r) {
-        stream_range<SCALED, PACKED ? 1 : 0, kBatch, kEnds, 1, kBrick>(sub, s_coarse, r, 0, ovf, set, sink);
+        stream_range<SCALED, kBatch, kEnds, 1, kBrick, false>(sub, s_coarse, r, 0, ovf, set, sink);
     });
     sink.drain(po, wave);
 }
@@ -1424,20 +1396,20 @@ __device__ __forceinline__ void count_stream_body(const StreamSubject &sub, cons
 // Two-window batches (the short-call schedule) need few vector registers; with at most 80 scalar
 // registers a SIMD holds 8 of these wavefronts.  (Each wavefront's scalar allocation is its count
 // rounded up to 16, plus 16 more: 800 / (96 + 16) = 7 wavefronts at 81..96 registers, 6 above that.)
-template <bool SCALED, bool PACKED, bool kEnds, bool kBrick>
+template <bool SCALED, bool kEnds, bool kBrick>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_num_sgpr(80)))
 k_count_stream2(StreamSubject sub, Overflow ovf, Ranges rg, PairOut po) {
-    count_stream_body<SCALED, PACKED, 2, kEnds, kBrick>(sub, ovf, rg, po);
+    count_stream_body<SCALED, 2, kEnds, kBrick>(sub, ovf, rg, po);
 }
 
-template <bool SCALED, bool PACKED, bool kEnds, bool kBrick>
+template <bool SCALED, bool kEnds, bool kBrick>
 __global__ void __launch_bounds__(kBlock)
 k_count_stream4(StreamSubject sub, Overflow ovf, Ranges rg, PairOut po) {
-    count_stream_body<SCALED, PACKED, 4, kEnds, kBrick>(sub, ovf, rg, po);
+    count_stream_body<SCALED, 4, kEnds, kBrick>(sub, ovf, rg, po);
 }
 
 // Upsampled pass-through (up = 2 .. kUp): the scale is always applied (multiplying by 1.0f is
-// exact) and the code width is read from the volume, so two instantiations cover every case.
+// exact), so two instantiations cover every case.
 template <int kUp>
 __global__ void __launch_bounds__(kBlock) k_count_stream_up(StreamSubject sub, Overflow ovf, Ranges rg,
                                                             PairOut po) {
@@ -1457,14 +1429,14 @@ __global__ void __launch_bounds__(kBlock) k_count_stream_up(StreamSubject sub, O
     AppendSink<kSinkCap> sink;
     sink.init(s_pend + wv * kSinkCap, sub.C, po, wave);
     for_each_range(rg, sub, ovf, wave, rb, [&](const RangeBounds &r) {
-        stream_range<true, 2, kB, false, kUp, false>(sub, s_coarse, r, 0, ovf, set, sink);
+        stream_range<true, kB, false, kUp, false, false>(sub, s_coarse, r, 0, ovf, set, sink);
     });
     sink.drain(po, wave);
 }
 
 // Batched form: work items (subject, first streamline) from every subject, handed out by the
 // queues; each wavefront keeps the coarse map of the subject it last worked on in its own LDS.
-// The scale is always applied (multiplying by 1.0f is exact), the code width is read per subject.
+// The scale is always applied (multiplying by 1.0f is exact).
 // One instantiation per kind of subject: pass-through (kEnds false, kUp 1), the endpoint modes
 // (kEnds: end labels at each close), and upsampled pass-through (kUp 2 or 4, with
 // sub.up <= kUp); a launch takes the items of subjects of one kind only.
@@ -1516,7 +1488,7 @@ __global__ void __launch_bounds__(kBlock) k_count_batched(const StreamSubject *_
             loaded = subject;
         }
         sink.C = sub.C;
-        stream_range<true, 2, kBatch, kEnds, kUp, false>(sub, coarse, rb, subject, ovf, set, sink);
+        stream_range<true, kBatch, kEnds, kUp, false, kUp == 1 && !kEnds>(sub, coarse, rb, subject, ovf, set, sink);
         sink.drain();   // the next item may belong to another subject's C
     }
 }
@@ -1540,17 +1512,16 @@ static int resident_blocks(const void *fn, size_t dyn) {
     return n;
 }
 
-template <bool SCALED, bool PACKED, int B, bool E>
+template <bool SCALED, int B, bool E>
 static int blocks_per_cu_of(size_t dyn) {
-    const void *fn = B == 2 ? reinterpret_cast<const void *>(&k_count_stream2<SCALED, PACKED, E, true>)
-                            : reinterpret_cast<const void *>(&k_count_stream4<SCALED, PACKED, E, true>);
+    const void *fn = B == 2 ? reinterpret_cast<const void *>(&k_count_stream2<SCALED, E, true>)
+                            : reinterpret_cast<const void *>(&k_count_stream4<SCALED, E, true>);
     return resident_blocks(fn, dyn);
 }
 
 template <int B, bool E>
-static int blocks_per_cu_b(bool scaled, bool packed, size_t dyn) {
-    if (scaled) return packed ? blocks_per_cu_of<true, true, B, E>(dyn) : blocks_per_cu_of<true, false, B, E>(dyn);
-    return packed ? blocks_per_cu_of<false, true, B, E>(dyn) : blocks_per_cu_of<false, false, B, E>(dyn);
+static int blocks_per_cu_b(bool scaled, size_t dyn) {
+    return scaled ? blocks_per_cu_of<true, B, E>(dyn) : blocks_per_cu_of<false, B, E>(dyn);
 }
 
 template <int U>
@@ -1558,10 +1529,10 @@ static int blocks_per_cu_up(size_t dyn) {
     return resident_blocks(reinterpret_cast<const void *>(&k_count_stream_up<U>), dyn);
 }
 
-int count_stream_blocks_per_cu(bool scaled, bool packed, int batch, bool ends, int up, size_t dyn) {
+int count_stream_blocks_per_cu(bool scaled, int batch, bool ends, int up, size_t dyn) {
     if (up > 1) return up == 2 ? blocks_per_cu_up<2>(dyn) : blocks_per_cu_up<4>(dyn);
-    if (ends) return batch == 2 ? blocks_per_cu_b<2, true>(scaled, packed, dyn) : blocks_per_cu_b<4, true>(scaled, packed, dyn);
-    return batch == 2 ? blocks_per_cu_b<2, false>(scaled, packed, dyn) : blocks_per_cu_b<4, false>(scaled, packed, dyn);
+    if (ends) return batch == 2 ? blocks_per_cu_b<2, true>(scaled, dyn) : blocks_per_cu_b<4, true>(scaled, dyn);
+    return batch == 2 ? blocks_per_cu_b<2, false>(scaled, dyn) : blocks_per_cu_b<4, false>(scaled, dyn);
 }
 
 static StreamSubject stream_subject(const CountArgs &a, const CompactVol &cv) {
@@ -1587,15 +1558,13 @@ static void launch_stream_bk(const CountArgs &a, const CompactVol &cv, const Ran
     const bool scaled = a.scale != 1.0f;
     const size_t dyn = coarse_lds_bytes(cv.ncoarse_words);
     const StreamSubject sub = stream_subject(a, cv);
-#define FC_LAUNCH_STREAM(S_, P_)                                                                               \
-    do {                                                                                                       \
-        if (B == 2) k_count_stream2<S_, P_, E, K><<<blocks, kBlock, dyn, st>>>(sub, a.ovf, rg, po); \
-        else k_count_stream4<S_, P_, E, K><<<blocks, kBlock, dyn, st>>>(sub, a.ovf, rg, po);       \
+#define FC_LAUNCH_STREAM(S_)                                                                        \
+    do {                                                                                            \
+        if (B == 2) k_count_stream2<S_, E, K><<<blocks, kBlock, dyn, st>>>(sub, a.ovf, rg, po);     \
+        else k_count_stream4<S_, E, K><<<blocks, kBlock, dyn, st>>>(sub, a.ovf, rg, po);            \
     } while (0)
-    if (scaled && cv.packed) FC_LAUNCH_STREAM(true, true);
-    else if (scaled) FC_LAUNCH_STREAM(true, false);
-    else if (cv.packed) FC_LAUNCH_STREAM(false, true);
-    else FC_LAUNCH_STREAM(false, false);
+    if (scaled) FC_LAUNCH_STREAM(true);
+    else FC_LAUNCH_STREAM(false);
 #undef FC_LAUNCH_STREAM
 }
 
@@ -2621,7 +2590,7 @@ __global__ void __launch_bounds__(kBlock) k_probe_lookup(StreamSubject sub, int6
         for (int b = 0; b < kBatch; ++b) {
             flag[b] = __builtin_amdgcn_ubfe(mw[b], bix[b], 1) != 0u;
             const uint32_t at = base[b] + __popc(__builtin_amdgcn_ubfe(mw[b], 0, bix[b]));
-            const uint32_t off = flag[b] ? (cv.packed ? at << 2 : at << 3) : code_oob;
+            const uint32_t off = flag[b] ? at << 2 : code_oob;
             c[b] = __builtin_amdgcn_raw_buffer_load_b32(rvol, off, codes_off, kAuxCached);
         }
         __builtin_amdgcn_sched_barrier(0);

@@ -1,5 +1,6 @@
 // Host build of the arithmetic that the kernels share with the host (csrc/internal.h), for
 // tests/test_host_math.py.
+#include "host.h"
 #include "internal.h"
 
 extern "C" {
@@ -10,6 +11,18 @@ void row_lane(int wide, int32_t x, int32_t X, int32_t out[3]) {
     out[0] = r.xs;
     out[1] = r.d;
     out[2] = (int32_t)r.mine;
+}
+
+// compact layout of a grid: 1 and {row bits, row mask, bytes, offset of the codes}, or 0 if it is refused
+int layout(const int32_t dims[3], int32_t N, int32_t M, int64_t out[4]) {
+    fch::CompactLayout L;
+    if (!fch::compact_layout(dims, N, M, L, fch::kMaxCoarseWords, true)) return 0;
+    const fc::CompactVol cv = fch::compact_view(nullptr, L, N, M);
+    out[0] = cv.rbits;
+    out[1] = cv.rmask;
+    out[2] = (int64_t)L.bytes;
+    out[3] = cv.codes_off;
+    return 1;
 }
 
 }

@@ -1,5 +1,6 @@
 """Host tests of arithmetic that the kernels share with the host (csrc/internal.h), built here for the CPU
-(tests/native/host_math.hip): which voxels of a row a lane of the compact build reads and owns."""
+(tests/native/host_math.hip): which voxels of a row a lane of the compact build reads and owns;
+that one 32-bit code holds every row and label that the argument checks let in."""
 import ctypes
 import os
 import subprocess
@@ -38,3 +39,26 @@ def test_build_lanes_own_every_voxel_of_a_row_once(lib, wide):
                     assert xs + i == x + i - d and i >= d
                     owners[xs + i] += 1
         assert (owners == 1).all(), X
+
+
+def _shapes():
+    for rb in range(1, 32):
+        for n in (1 << (rb - 1), (1 << rb) - 1):
+            most = ((1 << 31) - 1) // n                     # N * M < 2^31
+            for m in {1, 2, most // 2, most - 1, most, 1 << (most.bit_length() - 1)}:
+                if 1 <= m <= most:
+                    yield n, m
+
+
+def test_a_code_of_32_bits_holds_every_row_and_label(lib):
+    out = (ctypes.c_int64 * 4)()
+    dims = (ctypes.c_int32 * 3)(30, 20, 10)
+    for N, M in _shapes():
+        assert lib.layout(dims, N, M, out) == 1, (N, M)
+        rbits, rmask = out[0], out[1]
+        assert out[2] == out[3] + 4 * 30 * 20 * 10          # 4 bytes a code
+        none = 0xFFFFFFFF
+        # "none" in either field is no row and no label, and the largest of both come back as they went in
+        assert none & rmask >= N and none >> rbits >= M
+        code = (N - 1) | ((M - 1) << rbits)
+        assert code < 1 << 32 and code & rmask == N - 1 and code >> rbits == M - 1, (N, M)
