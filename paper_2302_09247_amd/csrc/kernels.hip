@@ -1371,8 +1371,9 @@ __device__ __forceinline__ void for_each_range(const Ranges &rg, const StreamSub
 template <bool SCALED, int kBatch, bool kEnds, bool kBrick>
 __device__ __forceinline__ void count_stream_body(const StreamSubject &sub, const Overflow &ovf,
                                                   const Ranges &rg, const PairOut &po) {
-    // 4-window batches run 6 wavefronts per SIMD (their scalar registers), so they can afford the
-    // LDS of 512 buffered updates; 2-window batches keep 8 per SIMD with 256
+    // 4-window batches run 5 wavefronts per SIMD (81 to 84 vector registers), so they can afford the LDS of
+    // 512 buffered updates; 2-window batches keep 8 per SIMD with 256.  (Held to the 80 registers of a sixth,
+    // the 4-window kernel measured no faster: 2601 against 2594 us for 5M streamlines.)
     constexpr int kSinkCap = kBatch == 4 ? 8 * kWave : 4 * kWave;
     __shared__ uint32_t s_set[kWavesPerBlock * kSetWords];
     __shared__ __align__(16) uint32_t s_pend[kWavesPerBlock * kSinkCap];
@@ -1409,10 +1410,12 @@ k_count_stream4(StreamSubject sub, Overflow ovf, Ranges rg, PairOut po) {
 }
 
 // Upsampled pass-through (up = 2 .. kUp): the scale is always applied (multiplying by 1.0f is
-// exact), so two instantiations cover every case.
+// exact), so two instantiations cover every case.  Six wavefronts per SIMD (at most 80 vector registers):
+// left to itself the compiler takes 81 for kUp 2, which is five, and 300k streamlines upsampled by 2 take
+// 217 instead of 212 us.
 template <int kUp>
-__global__ void __launch_bounds__(kBlock) k_count_stream_up(StreamSubject sub, Overflow ovf, Ranges rg,
-                                                            PairOut po) {
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6)))
+k_count_stream_up(StreamSubject sub, Overflow ovf, Ranges rg, PairOut po) {
     constexpr int kB = kUp == 2 ? 2 : 1;   // kB * kUp lookups per batch, as the plain kernel's 4
     constexpr int kSinkCap = 4 * kWave;
     __shared__ uint32_t s_set[kWavesPerBlock * kSetWords];
