@@ -2338,7 +2338,11 @@ k_pair_sort(PairOut po, int32_t nwaves, int32_t ntiles, int32_t tile_log2, int32
 // lanes read a run together, kRuns runs of a group in flight.  C's entries are loaded behind the first
 // updates: loads complete in order, so ahead of them they would hold the updates up.  (Reading whole
 // tiles from one sorted array took 20 us for 2M updates in 35 tiles, 14 us for 1M in 503 and 19 us for
-// 11M; this takes 11, 15 and 35 us, in exchange for the passes above.)
+// 11M; this takes 11, 15 and 35 us, in exchange for the passes above.)  A wavefront one of whose runs has 72
+// updates or more takes the long ones 64 at a time, equal neighbours added together: a small C, or one
+// whose updates gather in a few tiles, is bound by the hot tile's LDS atomics.  Eight at a time, one
+// tile of 2032 entries took 89 us for 1M streamlines' updates, now 47; four hot entries 250 us for 100k
+// streamlines', now 88.
 template <int kLog2>
 __global__ void __launch_bounds__(512) k_pair_tile_add(const uint16_t *__restrict__ sorted, const uint16_t *__restrict__ off,
                                                        const uint2 *__restrict__ blk, int32_t nblk, int32_t ntiles,
@@ -2362,7 +2366,7 @@ __global__ void __launch_bounds__(512) k_pair_tile_add(const uint16_t *__restric
     }
 #pragma unroll
     for (int j = 0; j < kSteps; ++j) reinterpret_cast<uint4 *>(h)[threadIdx.x + j * 512] = make_uint4(0u, 0u, 0u, 0u);
-    uint32_t s[kRuns], e[kRuns];
+    uint32_t s[kRuns], e[kRuns], longest = 0u;
     auto bounds = [&](uint32_t j) {   // of the groups' runs in round j
         uint32_t a0[kRuns], a1[kRuns];
 #pragma unroll
@@ -2379,6 +2383,7 @@ __global__ void __launch_bounds__(512) k_pair_tile_add(const uint16_t *__restric
             const uint32_t at = run[k].y + j * (uint32_t)kPairRound;
             s[k] = at + a0[k] + l8;
             e[k] = at + a1[k];
+            longest = max(longest, a1[k] - a0[k]);
         }
     };
     uint32_t v[kRuns];
@@ -2398,28 +2403,81 @@ __global__ void __launch_bounds__(512) k_pair_tile_add(const uint16_t *__restric
         for (int k = 0; k < kRuns; ++k)
             if (v[k] != kNoEntry) atomicAdd(&h[v[k]], 1u);
     };
+    // Runs with 64 updates or more to go (a tile that holds many of a workgroup's updates): 16 bytes a lane,
+    // from the 16-byte boundary at or below the group's next update.  Such a step ends within the run.
+    auto add_long = [&]() {
+        for (;;) {
+            uint4 w[kRuns];
+            uint32_t from[kRuns];   // the group's next update, or kNoEntry
+            bool any = false;
+#pragma unroll
+            for (int k = 0; k < kRuns; ++k) {
+                from[k] = s[k] - l8;
+                if (from[k] + 64u > e[k]) from[k] = kNoEntry;
+                w[k] = make_uint4(0u, 0u, 0u, 0u);
+                if (from[k] != kNoEntry) w[k] = reinterpret_cast<const uint4 *>(sorted)[(from[k] >> 3) + l8];
+                any |= from[k] != kNoEntry;
+            }
+            if (!__any(any)) return;
+#pragma unroll
+            for (int k = 0; k < kRuns; ++k)
+                if (from[k] != kNoEntry) {
+                    const uint32_t at = (from[k] & ~7u) + 8u * l8;
+                    const uint32_t q[4] = {w[k].x, w[k].y, w[k].z, w[k].w};
+                    uint32_t cnt = 0u;   // equal neighbours are added together
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const uint32_t u = i & 1 ? q[i >> 1] >> 16 : q[i >> 1] & 0xFFFFu;
+                        cnt += at + i >= from[k] ? 1u : 0u;
+                        if (i == 7 || (i & 1 ? q[(i + 1) >> 1 & 3] & 0xFFFFu : q[i >> 1] >> 16) != u) {
+                            if (cnt) atomicAdd(&h[u], cnt);
+                            cnt = 0u;
+                        }
+                    }
+                    s[k] = (from[k] & ~7u) + 64u + l8;
+                }
+        }
+    };
     bounds(0u);
     bool more = load();
     __builtin_amdgcn_sched_barrier(0);
+    const bool any_long = __any(longest >= 8u + 64u);   // (8 updates of each run are under way)
     int4 c[kSteps];
-    if (whole) {
+    auto load_c = [&]() {
 #pragma unroll
         for (int j = 0; j < kSteps; ++j) c[j] = reinterpret_cast<const int4 *>(C)[threadIdx.x + j * 512];
-    }
+    };
+    if (whole && !any_long) load_c();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int k = 0; k < kRuns; ++k) most = max(most, run[k].x);
     __syncthreads();   // h is zero
-    for (uint32_t j = 0;;) {
+    if (any_long) {
+        // (a loop of its own: with the long steps inside the other one, a C of 14M entries took 2% longer a call)
         add();
-        if (more) {
-            more = load();
-            continue;
+        for (uint32_t j = 0;;) {
+            add_long();
+            do {
+                more = load();
+                add();
+            } while (more);
+            ++j;
+            if (!__any(j < most)) break;
+            bounds(j);
         }
-        ++j;
-        if (!__any(j < most)) break;
-        bounds(j);
-        more = load();
+        if (whole) load_c();
+    } else {
+        for (uint32_t j = 0;;) {
+            add();
+            if (more) {
+                more = load();
+                continue;
+            }
+            ++j;
+            if (!__any(j < most)) break;
+            bounds(j);
+            more = load();
+        }
     }
     __syncthreads();
     if (whole) {
