@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 namespace fc {
@@ -181,6 +182,32 @@ __host__ __device__ inline RowLane row_lane(int32_t x, int32_t X) {
     }
     return r;
 }
+
+// Range that a streamline starting at point p belongs to: floor(n * h(p / P)), h the inverse of
+// g(x) = 1.5 x - 0.5 x^2, so the ranges shrink linearly from 1.5x to 0.5x the mean in the order they
+// are handed out and the last ones to start end close together.  p counts to 24 bits (exact as a
+// float); each step, IEEE square root included, is monotone in p, as the table needs.
+struct RangeOf {
+    int sh;
+    float inv_P, n;
+    int64_t P;
+    int32_t last;
+    __host__ __device__ RangeOf(int64_t points, int64_t nparts) : n((float)nparts), last((int32_t)nparts - 1) {
+        P = points > 0 ? points : 0;
+        sh = P >> 24 ? 40 - __builtin_clzll((unsigned long long)P) : 0;
+        inv_P = P > 0 ? 1.0f / (float)(uint32_t)(P >> sh) : 0.0f;
+    }
+    __host__ __device__ int32_t operator()(int64_t p) const {
+        const float u = fminf((float)(uint32_t)((p < 0 ? 0 : (p > P ? P : p)) >> sh) * inv_P, 1.0f);
+        const int32_t i = (int32_t)(n * (1.5f - sqrtf(2.25f - 2.0f * u)));
+        return i < 0 ? 0 : (i > last ? last : i);
+    }
+    // the same for ranges of equal size
+    __host__ __device__ int32_t equal(int64_t p) const {
+        const int32_t i = (int32_t)(n * fminf((float)(uint32_t)((p < 0 ? 0 : (p > P ? P : p)) >> sh) * inv_P, 1.0f));
+        return i < 0 ? 0 : (i > last ? last : i);
+    }
+};
 
 // Per-call state zeroed by the partition launch, so that it needs no launches of its own: C when
 // it is not accumulated into, a fixed scratch area's fallback bit maps, the coarse map of a volume built by the same call, the overflow and range counters.  Each

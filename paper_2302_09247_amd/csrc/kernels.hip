@@ -676,31 +676,9 @@ hipError_t launch_compact_build(const int32_t *roi, const int32_t *lab, Grid g, 
 // P = offsets[S] read on the device (launches stay asynchronous)
 // ---------------------------------------------------------------------------------------------
 
-// Range that a streamline starting at point p belongs to: floor(n * h(p / P)), h the inverse of
-// g(x) = 1.5 x - 0.5 x^2, so the ranges shrink linearly from 1.5x to 0.5x the mean in the order they
-// are handed out and the last ones to start end close together.  p counts to 24 bits (exact as a
-// float); each step, IEEE square root included, is monotone in p, as the table needs.
-struct RangeOf {
-    int sh;
-    float inv_P, n;
-    int64_t P;
-    int32_t last;
-    __device__ RangeOf(int64_t points, int64_t nparts) : n((float)nparts), last((int32_t)nparts - 1) {
-        P = points > 0 ? points : 0;
-        sh = P >> 24 ? 40 - __clzll(P) : 0;
-        inv_P = P > 0 ? 1.0f / (float)(uint32_t)(P >> sh) : 0.0f;
-    }
-    __device__ int32_t operator()(int64_t p) const {
-        const float u = fminf((float)(uint32_t)(clamp64(p, 0, P) >> sh) * inv_P, 1.0f);
-        const int32_t i = (int32_t)(n * (1.5f - sqrtf(2.25f - 2.0f * u)));
-        return i < 0 ? 0 : (i > last ? last : i);
-    }
-    // the same for ranges of equal size
-    __device__ int32_t equal(int64_t p) const {
-        const int32_t i = (int32_t)(n * fminf((float)(uint32_t)(clamp64(p, 0, P) >> sh) * inv_P, 1.0f));
-        return i < 0 ? 0 : (i > last ? last : i);
-    }
-};
+// Streamlines from which a thread of the partition launch takes four of them: up to there one each makes no
+// more wavefronts than the device holds at once, and a wavefront's ranges are written sooner.
+constexpr int64_t kPartitionUnrollFrom = int64_t(1) << 20;
 
 // p[0 .. n) = 0 by the whole grid, 16 bytes a store
 __device__ __forceinline__ void grid_zero(int32_t *p, int64_t n, int64_t t0, int64_t stride) {
@@ -715,11 +693,15 @@ __device__ __forceinline__ void grid_zero(int32_t *p, int64_t n, int64_t t0, int
 // Bound by latency (and by the zero fill of C on large ones), so the offsets are read once, in order:
 // the thread of streamline s knows the ranges that begin with it, those in (range(s - 1), range(s)].
 // A binary search per range, 13 to 20 dependent loads, took 6.4 us on 1k-10k streamlines and 12 us on
-// 1M.  A streamline that begins more than kShort ranges (a giant one before it) is written by its
-// whole wavefront.  first == nullptr: only the zero fills.
+// 1M.  Streamlines that begin up to kOwn ranges write them side by side, one that begins more (a giant one
+// before it) has its whole wavefront write them: with a whole wavefront for every streamline that begins more
+// than two, one after another, and four streamlines a thread, long streamlines in a row held a few wavefronts
+// up (57,400 streamlines, 4000 of them ten times as long, took 75 us a call, now 56, the search 59; 33,000
+// ordinary ones 49, now 38, the search 40).  first == nullptr: only the zero fills.
+template <int kUnroll>
 __global__ void k_partition(const int64_t *__restrict__ offsets, int64_t S, int64_t nparts, int32_t *__restrict__ first,
                             ZeroRanges z) {
-    constexpr int kShort = 2, kUnroll = 4;
+    constexpr int kShort = 2, kOwn = 8;
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int lane = lane_id();
@@ -739,12 +721,16 @@ __global__ void k_partition(const int64_t *__restrict__ offsets, int64_t S, int6
 #pragma unroll
             for (int k = 0; k < kShort; ++k)
                 if (mine && lo + k <= hi) first[lo + k] = (int32_t)s;
-            uint64_t rest = __ballot(mine && lo + kShort <= hi);
+            if (!__ballot(mine && lo + kShort <= hi)) continue;
+#pragma unroll 1
+            for (int k = kShort; k < kOwn; ++k)
+                if (mine && lo + k <= hi) first[lo + k] = (int32_t)s;
+            uint64_t rest = __ballot(mine && lo + kOwn <= hi);
             while (rest) {
                 const int k = __builtin_ctzll(rest);
                 rest &= rest - 1ull;
                 const int32_t l = __builtin_amdgcn_readlane(lo, k), h = __builtin_amdgcn_readlane(hi, k);
-                for (int32_t i = l + kShort + lane; i <= h; i += kWave) first[i] = (int32_t)(b0 + j * kWave + k);
+                for (int32_t i = l + kOwn + lane; i <= h; i += kWave) first[i] = (int32_t)(b0 + j * kWave + k);
             }
         }
     }
@@ -756,9 +742,11 @@ __global__ void k_partition(const int64_t *__restrict__ offsets, int64_t S, int6
 
 hipError_t launch_partition(const int64_t *offsets, int64_t S, int64_t nparts, int32_t *first, const ZeroRanges &z,
                             int cus, hipStream_t st) {
-    int64_t n = std::max(first ? (S + 4) / 4 : int64_t(1), z.n64);
+    const int unroll = S < kPartitionUnrollFrom ? 1 : 4;
+    int64_t n = std::max(first ? (S + unroll) / unroll : int64_t(1), z.n64);
     for (int64_t k : z.n32) n = std::max(n, (k + 3) / 4);
-    k_partition<<<fill_blocks(n, cus), kBlock, 0, st>>>(offsets, S, nparts, first, z);
+    if (unroll == 1) k_partition<1><<<fill_blocks(n, cus), kBlock, 0, st>>>(offsets, S, nparts, first, z);
+    else k_partition<4><<<fill_blocks(n, cus), kBlock, 0, st>>>(offsets, S, nparts, first, z);
     return hipGetLastError();
 }
 

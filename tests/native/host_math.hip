@@ -25,4 +25,10 @@ int layout(const int32_t dims[3], int32_t N, int32_t M, int64_t out[4]) {
     return 1;
 }
 
+// ranges of n point positions, of nparts tapering or (equal) equal ranges over P points
+void range_of(int64_t P, int64_t nparts, int equal, const int64_t *p, int64_t n, int32_t *out) {
+    const fc::RangeOf r(P, nparts);
+    for (int64_t k = 0; k < n; ++k) out[k] = equal ? r.equal(p[k]) : r(p[k]);
+}
+
 }

@@ -1,6 +1,7 @@
 """Host tests of arithmetic that the kernels share with the host (csrc/internal.h), built here for the CPU
 (tests/native/host_math.hip): which voxels of a row a lane of the compact build reads and owns;
-that one 32-bit code holds every row and label that the argument checks let in."""
+that one 32-bit code holds every row and label that the argument checks let in; which range of the points
+a streamline belongs to, of which the table of ranges needs that it never decreases."""
 import ctypes
 import os
 import subprocess
@@ -62,3 +63,95 @@ def test_a_code_of_32_bits_holds_every_row_and_label(lib):
         assert none & rmask >= N and none >> rbits >= M
         code = (N - 1) | ((M - 1) << rbits)
         assert code < 1 << 32 and code & rmask == N - 1 and code >> rbits == M - 1, (N, M)
+
+
+def _ranges(lib, P, nparts, equal, p):
+    p = np.ascontiguousarray(p, np.int64)
+    out = np.empty(p.size, np.int32)
+    lib.range_of(ctypes.c_int64(P), ctypes.c_int64(nparts), equal, p.ctypes.data_as(ctypes.c_void_p), ctypes.c_int64(p.size),
+                 out.ctypes.data_as(ctypes.c_void_p))
+    return out.astype(np.int64)
+
+
+POINTS = [0, 1, 2, 5, 999, (1 << 24) - 1, 1 << 24, (1 << 24) + 1, (1 << 25) - 1, 1 << 25, 3 * (1 << 24) + 7, 112_532_461,
+          1_097_713_418, (1 << 32) - 1, 1 << 32, (1 << 32) + 1, (1 << 36) + 12345, (1 << 40) - 1, 1 << 40]
+
+
+@pytest.mark.parametrize("equal", [0, 1])
+@pytest.mark.parametrize("P", POINTS)
+def test_ranges_never_decrease(lib, P, equal):
+    rng = np.random.default_rng(P % 1000 + equal)
+    p = rng.integers(0, P + 1, 200_000) if P > 200_000 else np.arange(P + 1)
+    step = max(1, P >> 24)
+    edges = np.concatenate([[0, P], (rng.integers(0, P + 1, 2000) // step * step)[:, None].repeat(3, 1).ravel() + np.tile([-1, 0, 1], 2000)])
+    p = np.sort(np.concatenate([p, np.clip(edges, 0, P), [-5, P + 5]]))
+    for nparts in (1, 2, 3, 7, 64, 1000, 6144, 28_672, 49_152, 50_001):
+        r = _ranges(lib, P, nparts, equal, p)
+        assert (np.diff(r) >= 0).all(), nparts
+        assert r[0] == 0 and r.max() < nparts
+        if P > 1 << 20:   # range i holds about the share of the points it should (24-bit positions: to 1 in 300)
+            i = np.arange(nparts + 1) / nparts
+            want = P * (i if equal else 1.5 * i - 0.5 * i * i)
+            got = p[np.searchsorted(r, np.arange(nparts))]
+            spread = P / 200_000 * 30 + P / nparts
+            assert np.abs(got - want[:-1]).max() < spread
+            assert r[-1] == nparts - 1
+
+
+@pytest.mark.parametrize("seed", range(6))
+def test_one_pass_writes_every_range_once(lib, seed):
+    # the table's rule: streamline s writes the ranges in (range(s - 1), range(s)], the end of the last
+    # streamline those that are left, nparts included; a plan's items: the last streamline takes the rest
+    rng = np.random.default_rng(seed)
+    S = int(rng.choice([1, 2, 63, 64, 65, 5000, 40_000]))
+    lens = rng.integers(0, 200, S)
+    lens[rng.random(S) < 0.3] = 0
+    lens[: S // 7] = 0
+    lens[S - S // 7:] = 0
+    if seed % 2:
+        lens[S // 2] = 1 + 1000 * S
+        lens[S // 3: S // 3 + 40] *= 300
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64) * (1 if seed < 4 else 70_001)
+    for nparts in (1, 2, 5, 64, 6144, 28_672):
+        r = _ranges(lib, int(off[-1]), nparts, 0, off[:-1])
+        hi = np.append(r, nparts)
+        lo = np.append(-1, r) + 1
+        first = np.full(nparts + 1, -1)
+        writes = np.zeros(nparts + 1, np.int64)
+        for s in range(S + 1):
+            first[lo[s]:hi[s] + 1] = s
+            writes[lo[s]:hi[s] + 1] += 1
+        assert (writes == 1).all() and first[0] == 0 and first[-1] == S and (np.diff(first) >= 0).all()
+        # every streamline is in the range it belongs to
+        for i in rng.integers(0, nparts, 50):
+            assert (r[first[i]:first[i + 1]] == i).all()
+        e = _ranges(lib, int(off[-1]), nparts, 1, off[:-1])
+        hi = e.copy()
+        hi[-1] = nparts - 1
+        lo = np.append(-1, e[:-1]) + 1
+        writes = np.zeros(nparts, np.int64)
+        for s in range(S):
+            writes[lo[s]:hi[s] + 1] += 1
+        assert (writes == 1).all()
+
+
+@pytest.mark.parametrize("width", [256, 1024])
+@pytest.mark.parametrize("seed", range(4))
+def test_count_search_of_either_workgroup_size(width, seed):
+    # the overflow queue's search for a point's streamline runs in workgroups of 256 threads, and of 1024
+    # beside the sorting of the pair buffer: `width` evenly spaced offsets a round
+    rng = np.random.default_rng(100 * width + seed)
+    S = int(rng.choice([1, 2, width - 1, width, width + 1, 70_000, 3_000_000]))
+    lens = rng.integers(0, 400, S)
+    lens[rng.random(S) < 0.2] = 0
+    off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+    if off[-1] == 0:
+        return
+    for p in rng.integers(0, off[-1], 100):
+        lo, hi = 0, S
+        while hi - lo > 1:
+            step = (hi - lo + width - 1) // width
+            at = lo + np.arange(1, width, dtype=np.int64) * step
+            lo += int((off[at[at < hi]] <= p).sum()) * step
+            hi = min(hi, lo + step)
+        assert lo == int(np.searchsorted(off, p, side="right")) - 1 and off[lo] <= p < off[lo + 1]
