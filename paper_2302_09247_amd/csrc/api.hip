@@ -125,10 +125,15 @@ constexpr int kBlocksPerCU = 8;            // resident 256-thread workgroups per
 // queues, their sizes falling linearly from 1.5x to 0.5x the mean, so that the wavefronts finish
 // together.  Each range start costs a few dependent loads and a pipeline fill.
 constexpr int kRangesPerWave = 6;
-// Calls of at most this many streamlines per wavefront of a full launch give every wavefront one
-// range of (nearly) equally many streamlines instead, without a table: with a handful of streamlines a
-// wavefront, finding, fetching and starting six ranges takes longer than counting them.
-constexpr int kStaticRangeStreamlines = 4;
+// Calls of at most kOwnRangeStreamlines streamlines per wavefront of a full launch (262,144 on 256 CUs) give
+// every wavefront one range instead, without a table, which it finds itself: fetching and starting six ranges
+// takes longer than it evens out.  A call takes, table against own ranges, at 33,000 streamlines 38 and 28 us, at
+// 130,000 75 and 66, at 262,000 106 and 105, at 400,000 141 and 148.
+// Up to kEqualRangeStreamlines a wavefront, its range is simply its share of the streamlines, whatever their
+// lengths: 16,000 take 19.7 us, 21.3 with the search; with long ones in a row (13,120, 900 of them ten times as
+// long) 32.5 and 24 us, 35.5 in a table.  Beyond it such a row outweighs the search: 19,680 take 46 and 25 us.
+constexpr int kOwnRangeStreamlines = 32;
+constexpr int kEqualRangeStreamlines = 2;
 constexpr int64_t kLongRangesFrom = int64_t(1) << 21;   // 4-window batches from this many streamlines
 constexpr int64_t kDirectMaxStreamlines = int64_t(1) << 17;   // calls below this many streamlines ...
 constexpr int64_t kDirectMaxEntries = int64_t(1) << 20;       // ... on a C of at most this many entries
@@ -179,6 +184,7 @@ struct CountPlan {
     bool zero_c = false;       // C overwritten (zeroed first)
     bool fused_zero = false;   // the partition launch does the zeroing
     bool ends = false;         // an endpoint mode
+    bool equal_ranges = false; // without a table: every wavefront gets its share of the streamlines
     int64_t NM = 0;
     fc::PairTiles tiles;
     int batch = 2;
@@ -246,7 +252,8 @@ int make_count_plan(int64_t S, int32_t N, int32_t M, const fc::CompactVol *cv, c
                                                 fc::coarse_lds_bytes(cv->ncoarse_words));
     if (o.blocks_per_cu > 0 && o.blocks_per_cu < per_cu) per_cu = o.blocks_per_cu;
     cp.blocks = (int64_t)cus * per_cu;
-    if (S <= cp.blocks * fc::kWavesPerBlock * kStaticRangeStreamlines) {
+    if (S <= cp.blocks * fc::kWavesPerBlock * kOwnRangeStreamlines) {
+        cp.equal_ranges = S <= cp.blocks * fc::kWavesPerBlock * kEqualRangeStreamlines;
         cp.nparts = std::min<int64_t>(cp.blocks * fc::kWavesPerBlock, S);
         cp.blocks = (cp.nparts + fc::kWavesPerBlock - 1) / fc::kWavesPerBlock;
     } else {
@@ -362,8 +369,10 @@ int enqueue_count(const CountPlan &cp, const CountScratch &sc, int dev, const Vo
         fc::Ranges rg;
         rg.first = cp.first_bytes ? sc.first : nullptr;
         rg.nparts = cp.nparts;
-        rg.per = (uint32_t)(S / cp.nparts);
-        rg.extra = (uint32_t)(S % cp.nparts);
+        rg.per = cp.equal_ranges ? (uint32_t)(S / cp.nparts) : 0u;
+        rg.extra = cp.equal_ranges ? (uint32_t)(S % cp.nparts) : 0u;
+        rg.inv_nparts = 1.0 / (double)cp.nparts;
+        rg.inv_S = 1.0 / (double)S;
         FC_HIP(fc::launch_partition(offsets, S, cp.nparts, cp.first_bytes ? sc.first : nullptr, z, cus, st));
         if (build_late) FC_HIP(build(true));
         if (o.event_begin) FC_HIP(hipEventRecord((hipEvent_t)o.event_begin, st));

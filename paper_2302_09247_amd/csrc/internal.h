@@ -224,11 +224,13 @@ struct ZeroRanges {
 hipError_t launch_partition(const int64_t *offsets, int64_t S, int64_t nparts, int32_t *first, const ZeroRanges &z,
                             int cus, hipStream_t st);
 // Streamline ranges of a flat-stream launch: a table of nparts ranges handed out by the queues, or
-// (first == nullptr) one range per wavefront, `per` streamlines each and one more in the first `extra`.
+// (first == nullptr) one range per wavefront: `per` streamlines each and one more in the first `extra`, or
+// (per == 0) ranges of about equally many points and streamlines that the wavefronts find themselves.
 struct Ranges {
     const int32_t *first;
     int64_t nparts;
     uint32_t per, extra;
+    double inv_nparts, inv_S;   // (per == 0)
 };
 // LDS of a workgroup's copy of a coarse map, stored 16 bytes at a time
 inline size_t coarse_lds_bytes(int32_t words) { return 4 * (size_t)((words + 3) & ~3); }

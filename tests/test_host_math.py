@@ -1,7 +1,8 @@
 """Host tests of arithmetic that the kernels share with the host (csrc/internal.h), built here for the CPU
 (tests/native/host_math.hip): which voxels of a row a lane of the compact build reads and owns;
 that one 32-bit code holds every row and label that the argument checks let in; which range of the points
-a streamline belongs to, of which the table of ranges needs that it never decreases."""
+a streamline belongs to, of which the table of ranges needs that it never decreases; that the ranges which
+wavefronts find for themselves cover every streamline once."""
 import ctypes
 import os
 import subprocess
@@ -155,3 +156,77 @@ def test_count_search_of_either_workgroup_size(width, seed):
             lo += int((off[at[at < hi]] <= p).sum()) * step
             hi = min(hi, lo + step)
         assert lo == int(np.searchsorted(off, p, side="right")) - 1 and off[lo] <= p < off[lo + 1]
+
+
+def _own_ranges(off, nparts):
+    """numpy model of the ranges that wavefronts find for themselves (one per wavefront, no table)."""
+    S = off.size - 1
+    P = max(int(off[-1]), 0)
+    ln = int(np.float64(P) * (1.0 / np.float64(S))) + 1
+    inv = 1.0 / np.float64(nparts)
+
+    def target(w):
+        return int(np.float64(P + ln * S) * (np.float64(w) * inv))
+
+    def first_at(w):
+        lo, hi, t, rounds = 0, S, target(w), 0
+        while lo < hi:
+            step = (hi - lo + 63) // 64
+            at = lo + np.arange(64, dtype=np.int64) * step
+            at = at[at < hi]
+            n = int((off[at] + ln * at < t).sum())
+            hi = min(hi, lo + n * step) if n else lo
+            lo = lo + (n - 1) * step + 1 if n else lo
+            rounds += 1
+            assert 0 <= lo <= hi <= S and rounds <= 6
+        return lo
+
+    out = []
+    for w in range(nparts):
+        s0 = 0 if w == 0 else first_at(w)
+        s1 = S
+        if w + 1 < nparts:
+            at = np.arange(s0, s0 + 64)
+            at = at[at < S]
+            n = int((off[at] + ln * at < target(w + 1)).sum())
+            s1 = s0 + n if n < 64 else max(s0, first_at(w + 1))
+        out.append((s0, s1))
+    return out, ln
+
+
+@pytest.mark.parametrize("order", ["drawn", "sorted", "falling", "long in a row", "empty runs", "giant"])
+@pytest.mark.parametrize("S,nparts", [(3, 1), (200, 64), (2049, 1024), (5000, 1024), (32_768, 1024), (20_000, 8192)])
+def test_own_ranges_cover_every_streamline_once(order, S, nparts):
+    rng = np.random.default_rng(S + len(order))
+    lens = np.clip(np.round(150 * np.exp(0.5 * rng.standard_normal(S))), 20, 600).astype(np.int64)
+    if order == "sorted":
+        lens.sort()
+    if order == "falling":
+        lens = np.sort(lens)[::-1].copy()
+    if order == "long in a row":
+        lens[: S // 20] *= 10
+    if order == "empty runs":
+        lens[: S // 4] = 0
+        lens[S - S // 4:] = 0
+        lens[rng.random(S) < 0.3] = 0
+    if order == "giant":
+        lens[S // 2] = 1 << 40
+    off = np.concatenate([[0], np.cumsum(lens)])
+    ranges, ln = _own_ranges(off, nparts)
+    assert ranges[0][0] == 0 and ranges[-1][1] == S
+    assert all(a[1] == b[0] for a, b in zip(ranges, ranges[1:]))
+    # at most twice the mean of the streamlines, and of the points but for the last one's length
+    per = np.array([b - a for a, b in ranges])
+    assert per.max() <= 2 * S / nparts + 2
+    begun = np.array([off[b - 1] - off[a] if b > a else 0 for a, b in ranges])
+    assert begun.max() <= 2 * (off[-1] + S) / nparts + 2
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_own_ranges_of_decreasing_offsets_stay_in_bounds(seed):
+    # malformed offsets give wrong counts, but every range lies in [0, S] and the search ends
+    rng = np.random.default_rng(seed)
+    S = 4000
+    off = rng.integers(-1000 if seed % 2 else 0, 300_000, S + 1)
+    for s0, s1 in _own_ranges(off, 512)[0]:
+        assert 0 <= s0 <= s1 <= S
