@@ -486,6 +486,8 @@ struct fastcod_plan {
     int64_t transpose_tiles = 0;
     DevBuf d_transposed;                        // device copy of `transposed`
     DevBuf d_subs, d_sizes, d_item_base, d_items, d_ovf, d_fallback;
+    fc::PrepareGrid prepare;                    // workgroups of the preparation launch
+    DevBuf d_block_base;                        // its table
     fc::FallbackScratch fs{};
     fc::Overflow ovf{};
     PlanSched sched;
@@ -542,15 +544,11 @@ int plan_enqueue(fastcod_plan &pl, int cus, hipStream_t st) {
     const auto *subs = static_cast<const fc::StreamSubject *>(pl.d_subs.p);
     // one launch zeroes every C, the overflow count and every kind's queues, and writes the work items
     const int64_t header_words = (int64_t)(fc::overflow_header_bytes(fc::kBatchedKinds) / 8);
-    int64_t most_s = 0, most_entries = 0;
-    for (int32_t k = 0; k < pl.n; ++k) {
-        most_s = std::max(most_s, pl.subs[k].S);
-        most_entries = std::max(most_entries, pl.sizes[k]);
-    }
     FC_HIP(fc::launch_prepare_batched(subs, static_cast<const int64_t *>(pl.d_item_base.p),
-                                      static_cast<const int64_t *>(pl.d_sizes.p), pl.n, most_s, most_entries,
+                                      static_cast<const int64_t *>(pl.d_sizes.p), pl.n, pl.prepare,
+                                      static_cast<const int64_t *>(pl.d_block_base.p),
                                       pl.nitems > 0 ? static_cast<int2 *>(pl.d_items.p) : nullptr, pl.ovf.count,
-                                      header_words, cus, st));
+                                      header_words, st));
     const int32_t *kl = pl.kind_lo;
     const int seed = (int)fc::BatchedKind::kSeedEnd;
     if (pl.nitems > 0) {
@@ -601,6 +599,7 @@ void plan_free(fastcod_plan *pl) {
     pl->d_ovf.release();
     pl->d_fallback.release();
     pl->d_transposed.release();
+    pl->d_block_base.release();
     delete pl;
 }
 
@@ -757,6 +756,16 @@ int plan_build(const fastcod_subject *subjects, int32_t n, uint32_t flags, const
     FC_HIP(hipMemcpyAsync(pl->d_subs.p, pl->subs.data(), sizeof(fc::StreamSubject) * (size_t)n, hipMemcpyHostToDevice, st));
     FC_HIP(hipMemcpyAsync(pl->d_sizes.p, pl->sizes.data(), 8 * (size_t)n, hipMemcpyHostToDevice, st));
     const size_t header = fc::overflow_header_bytes(fc::kBatchedKinds);
+    std::vector<int64_t> work(n), block_base(n + 1, 0);
+    for (int32_t k = 0; k < n; ++k)
+        work[k] = std::max((pl->sizes[k] + 3) / 4,
+                           k < pl->kind_lo[(int)fc::BatchedKind::kSeedEnd] ? fc::kPrepareStreamlineWork * pl->subs[k].S : 0);
+    pl->prepare = fc::prepare_grid(work.data(), n, (int64_t)(header / 8), cus, block_base.data());
+    if (pl->prepare.table) {
+        FC_HIP(pl->d_block_base.ensure(8 * (size_t)(n + 1), false));
+        FC_HIP(hipMemcpyAsync(pl->d_block_base.p, block_base.data(), 8 * (size_t)(n + 1), hipMemcpyHostToDevice, st));
+        FC_HIP(hipStreamSynchronize(st));
+    }
     FC_HIP(pl->d_ovf.ensure(header + 8 * (size_t)std::max<int64_t>(total_s, 1), false));
     pl->ovf.count = static_cast<unsigned long long *>(pl->d_ovf.p);
     pl->ovf.work = pl->ovf.count + fc::kQueueWords;

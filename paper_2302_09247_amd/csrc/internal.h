@@ -274,12 +274,49 @@ struct TransposeJob {
 hipError_t launch_transpose_many(const TransposeJob *jobs, int32_t njobs, int64_t ntiles, int cus, hipStream_t st);
 
 // batched form
+// Workgroups of a preparation launch: `blocks` for every subject, or (table) `blocks` in all, subject k's from
+// base[k] to base[k + 1].
+struct PrepareGrid {
+    int64_t blocks = 1;
+    bool table = false;
+};
+// Up to 16 workgroups per CU in all, one thread per unit of work[k] at most: a unit zeroes four entries of C; a
+// streamline, whose offset is waited for, counts as kPrepareStreamlineWork.  Equally many each while that gives the largest subject all it can use or half of its share of the
+// work; in proportion otherwise, one at least where there is work (base: n + 1 entries, written then).
+// (A plan of one subject of 3M streamlines and 255 of 100 takes 1054 us a launch, 1828 with equally many.)
+constexpr int64_t kPrepareStreamlineWork = 4;
+inline PrepareGrid prepare_grid(const int64_t *work, int32_t n, int64_t nzero, int cus, int64_t *base) {
+    const int64_t cap = (int64_t)cus * 16;
+    int64_t most = 0, sum = 0;
+    for (int32_t k = 0; k < n; ++k) {
+        most = most > work[k] ? most : work[k];
+        sum += work[k];
+    }
+    auto blocks_of = [](int64_t w) { return (w + kBlock - 1) / kBlock; };
+    PrepareGrid g;
+    const int64_t all = blocks_of(most), each = cap / n > 1 ? cap / n : 1;
+    g.table = each < all && most * n > 2 * sum;
+    if (!g.table) {
+        const int64_t want = blocks_of(most > nzero ? most : nzero);
+        g.blocks = want < 1 ? 1 : (want < each ? want : each);
+        return g;
+    }
+    base[0] = 0;
+    for (int32_t k = 0; k < n; ++k) {
+        int64_t b = (int64_t)((double)cap * ((double)work[k] / (double)sum));
+        if (b < 1) b = 1;
+        if (b > blocks_of(work[k])) b = blocks_of(work[k]);
+        base[k + 1] = base[k] + b;
+    }
+    g.blocks = base[n];
+    return g;
+}
 // zeroes every subject's C (sizes: entries; nullptr: none), writes the work items (items == nullptr: none)
 // and zeroes zero[0 .. nzero) (the counting launches' overflow count and range queues);
-// most_streamlines, most_entries: the largest subject's streamlines and entries of C to zero
+// block_base: device copy of the grid's table (grid.table)
 hipError_t launch_prepare_batched(const StreamSubject *subs, const int64_t *item_base, const int64_t *sizes, int32_t nsub,
-                                  int64_t most_streamlines, int64_t most_entries, int2 *items, unsigned long long *zero,
-                                  int64_t nzero, int cus, hipStream_t st);
+                                  const PrepareGrid &grid, const int64_t *block_base, int2 *items, unsigned long long *zero,
+                                  int64_t nzero, hipStream_t st);
 // Points a work item holds at least, on average: smaller launches get fewer items, and with at most one
 // per wavefront nothing is drawn from a queue.  (24 little subjects of 3.4M points in all: 45.1 us a
 // launch at 512, 41.4 at 256, 58.6 at 1024, 58 with 28,672 items whatever the points.)

@@ -2005,19 +2005,36 @@ hipError_t launch_parcellate(const int32_t *C, int32_t N, int32_t M, int32_t *la
 // batched form: work items, zero fill of every C, launchers
 // ---------------------------------------------------------------------------------------------
 
-// Prepares a launch; blockIdx.y is the subject.  Its C is zeroed (sizes: entries of each subject's C;
+// Prepares a launch; blockIdx.y is the subject, or (block_base) the one whose workgroups blockIdx.x falls
+// into.  Its C is zeroed (sizes: entries of each subject's C;
 // nullptr: not here), and its work items item_base[s] .. item_base[s + 1] are written: item j = (subject,
 // first streamline of [s_begin, S) whose start lies in the j-th of the n_s equal parts of the points
 // offsets[s_begin] .. offsets[S]).  The offsets are read once, in order, as in k_partition: a binary
 // search per item took 8.5 us on little subjects and 16 us on large ones, after a launch for the zero
-// fill of its own.  Also zeroes zero[0 .. nzero): the counting launches' overflow count and queues.
+// fill of its own; with a small share of the workgroups for one large subject, its pass took 4 ms of 3M
+// streamlines beside 999 of 100.  Also zeroes zero[0 .. nzero): the counting launches' overflow count and queues.
 __global__ void k_prepare_batched(const StreamSubject *__restrict__ subs, const int64_t *__restrict__ item_base,
-                                  const int64_t *__restrict__ sizes, int2 *__restrict__ items,
+                                  const int64_t *__restrict__ sizes, int32_t nsub,
+                                  const int64_t *__restrict__ block_base, int2 *__restrict__ items,
                                   unsigned long long *__restrict__ zero, int64_t nzero) {
-    constexpr int kShort = 2;
-    const int32_t k = (int32_t)blockIdx.y;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    constexpr int kShort = 2, kOwn = 8;
+    int32_t k = (int32_t)blockIdx.y;
+    int64_t block = blockIdx.x, blocks = gridDim.x;
+    if (block_base) {
+        // the last subject whose base is at or below this workgroup: 64 bases a round
+        int32_t lo = 0, hi = nsub;   // block_base[lo] <= block, and the answer in [lo, hi)
+        while (hi - lo > 1) {
+            const int32_t step = (hi - lo + kWave - 1) / kWave, at = lo + lane_id() * step;
+            const uint64_t le = __ballot(at < hi && block_base[at < hi ? at : lo] <= block);
+            lo += (__popcll(le) - 1) * step;   // (lane 0's is)
+            hi = min(hi, lo + step);
+        }
+        k = lo;
+        block -= block_base[k];
+        blocks = block_base[k + 1] - block_base[k];
+    }
+    const int64_t stride = blocks * blockDim.x;
+    const int64_t t0 = block * blockDim.x + threadIdx.x;
     const StreamSubject &sub = subs[k];
     const int64_t i0 = item_base[k], S = sub.S, sb = clamp64(sub.s_begin, 0, S);
     const int32_t ns = items ? (int32_t)(item_base[k + 1] - i0) : 0;
@@ -2035,30 +2052,33 @@ __global__ void k_prepare_batched(const StreamSubject *__restrict__ subs, const 
 #pragma unroll
         for (int q = 0; q < kShort; ++q)
             if (mine && lo + q <= hi) items[i0 + lo + q] = make_int2(k, (int)(lo + q <= in ? s : S));
-        uint64_t rest = __ballot(mine && lo + kShort <= hi);
+        if (!__ballot(mine && lo + kShort <= hi)) continue;
+#pragma unroll 1
+        for (int q = kShort; q < kOwn; ++q)
+            if (mine && lo + q <= hi) items[i0 + lo + q] = make_int2(k, (int)(lo + q <= in ? s : S));
+        uint64_t rest = __ballot(mine && lo + kOwn <= hi);
         while (rest) {
             const int q = __builtin_ctzll(rest);
             rest &= rest - 1ull;
             const int32_t l = __builtin_amdgcn_readlane(lo, q), h = __builtin_amdgcn_readlane(hi, q),
                           n = __builtin_amdgcn_readlane(in, q);
             const int64_t sq = sb + b0 + q;
-            for (int32_t i = l + kShort + lane; i <= h; i += kWave) items[i0 + i] = make_int2(k, (int)(i <= n ? sq : S));
+            for (int32_t i = l + kOwn + lane; i <= h; i += kWave) items[i0 + i] = make_int2(k, (int)(i <= n ? sq : S));
         }
     }
     // (the zero fills come last: a wait for a load also waits for the stores before it)
     if (sizes) grid_zero(sub.C, sizes[k], t0, stride);
-    if (k == 0)
-        for (int64_t i = t0; i < nzero; i += stride) zero[i] = 0ull;
+    if (block_base || k == 0) {
+        const int64_t threads = (int64_t)gridDim.x * blockDim.x;
+        for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nzero; i += threads) zero[i] = 0ull;
+    }
 }
 
 hipError_t launch_prepare_batched(const StreamSubject *subs, const int64_t *item_base, const int64_t *sizes, int32_t nsub,
-                                  int64_t most_streamlines, int64_t most_entries, int2 *items, unsigned long long *zero,
-                                  int64_t nzero, int cus, hipStream_t st) {
-    // one streamline or four entries of C per thread and step, up to 16 workgroups per CU in all
-    const int64_t n = std::max(std::max(most_streamlines, (most_entries + 3) / 4), nzero);
-    int64_t blocks = std::min((n + kBlock - 1) / kBlock, std::max<int64_t>((int64_t)cus * 16 / nsub, 1));
-    k_prepare_batched<<<dim3((unsigned)std::max<int64_t>(blocks, 1), (unsigned)nsub), kBlock, 0, st>>>(subs, item_base, sizes,
-                                                                                                     items, zero, nzero);
+                                  const PrepareGrid &grid, const int64_t *block_base, int2 *items, unsigned long long *zero,
+                                  int64_t nzero, hipStream_t st) {
+    k_prepare_batched<<<dim3((unsigned)grid.blocks, grid.table ? 1u : (unsigned)nsub), kBlock, 0, st>>>(
+        subs, item_base, sizes, nsub, grid.table ? block_base : nullptr, items, zero, nzero);
     return hipGetLastError();
 }
 

@@ -49,9 +49,11 @@ class HipExecutor final : public fcs::Executor {
         FC_HIP(hipStreamCreateWithFlags(&copy_, hipStreamNonBlocking));
         FC_HIP(hipStreamCreateWithFlags(&out_, hipStreamNonBlocking));
         const int64_t nsub = cfg.max_active;
-        // the subject table and the item bases in one block (host and device alike): one upload a launch
+        // the subject table, the item bases and the preparation launch's table in one block (host and device
+        // alike): one upload a launch
         desc_base_off_ = (sizeof(fc::StreamSubject) * (size_t)nsub + 255) & ~size_t(255);
-        const size_t desc_bytes = desc_base_off_ + 8 * (size_t)(nsub + 1);
+        const size_t desc_bytes = desc_base_off_ + 16 * (size_t)(nsub + 1);
+        work_.resize((size_t)nsub);
         for (Slot &s : slots_) {
             FC_HIP(hipHostMalloc(reinterpret_cast<void **>(&s.h_desc), desc_bytes, hipHostMallocDefault));
             s.h_subs = reinterpret_cast<fc::StreamSubject *>(s.h_desc);
@@ -212,22 +214,23 @@ class HipExecutor final : public fcs::Executor {
             }
             s.h_base[k + 1] = s.h_base[k] + ni;
         }
+        for (int32_t k = 0; k < n; ++k) work_[k] = k < kind_lo[seed] ? fc::kPrepareStreamlineWork * (chunks[k].s1 - chunks[k].s0) : 0;
+        const int64_t header_words = (int64_t)(fc::overflow_header_bytes(fc::kBatchedKinds) / 8);
+        const fc::PrepareGrid prepare = fc::prepare_grid(work_.data(), n, header_words, cus_, s.h_base + n + 1);
         const int64_t nitems = s.h_base[n];
         if (nitems + 1 > (int64_t)(s.d_items.n / 8)) return err(FASTCOD_EINVAL, "work item table overflow");
         const auto *subs = static_cast<const fc::StreamSubject *>(s.d_desc.p);
         const auto *d_base = reinterpret_cast<const int64_t *>(static_cast<const char *>(s.d_desc.p) + desc_base_off_);
         const int2 *items = static_cast<const int2 *>(s.d_items.p);
         // the counters and range queues are reset by the launch that writes the items (by a fill without items)
-        const int64_t header_words = (int64_t)(fc::overflow_header_bytes(fc::kBatchedKinds) / 8);
-        if (hip(hipMemcpyAsync(s.d_desc.p, s.h_desc, desc_base_off_ + 8 * (size_t)(n + 1), hipMemcpyHostToDevice, comp_),
+        if (hip(hipMemcpyAsync(s.d_desc.p, s.h_desc, desc_base_off_ + (prepare.table ? 16 : 8) * (size_t)(n + 1),
+                               hipMemcpyHostToDevice, comp_),
                 "descriptor upload") ||
             (nitems == 0 && hip(fc::launch_fill_u64(ovf_.count, header_words, cus_, comp_), "counter reset")))
             return FASTCOD_EHIP;
         if (nitems > 0) {
-            int64_t most_s = 0;
-            for (const fcs::Chunk &c : chunks) most_s = std::max(most_s, c.s1 - c.s0);
-            if (hip(fc::launch_prepare_batched(subs, d_base, nullptr, n, most_s, 0, static_cast<int2 *>(s.d_items.p),
-                                               ovf_.count, header_words, cus_, comp_),
+            if (hip(fc::launch_prepare_batched(subs, d_base, nullptr, n, prepare, d_base + n + 1,
+                                               static_cast<int2 *>(s.d_items.p), ovf_.count, header_words, comp_),
                     "work items"))
                 return FASTCOD_EHIP;
             for (int k = 0; k < seed; ++k) {
@@ -280,7 +283,7 @@ class HipExecutor final : public fcs::Executor {
         hipEvent_t ev = nullptr, link = nullptr;
     };
     struct Slot {
-        char *h_desc = nullptr;                 // pinned: subject table, then (at desc_base_off_) item bases
+        char *h_desc = nullptr;                 // pinned: subject table, then (at desc_base_off_) item and block bases
         fc::StreamSubject *h_subs = nullptr;
         int64_t *h_base = nullptr;
         DevBuf d_desc, d_items;                 // d_desc: the same layout as h_desc
@@ -391,6 +394,7 @@ class HipExecutor final : public fcs::Executor {
     std::vector<int> free_flags_;
     std::map<uint64_t, int> flag_of_;     // request id -> flag slot
     size_t desc_base_off_ = 0;   // offset of the item bases in a slot's descriptor block
+    std::vector<int64_t> work_;  // of a launch's requests, for its preparation
     uint64_t next_slot_ = 0;
     std::vector<TokenRec> toks_;
     std::vector<fcs::Token> free_toks_;

@@ -31,4 +31,11 @@ void range_of(int64_t P, int64_t nparts, int equal, const int64_t *p, int64_t n,
     for (int64_t k = 0; k < n; ++k) out[k] = equal ? r.equal(p[k]) : r(p[k]);
 }
 
+// workgroups of a preparation launch: 1 with base[0 .. n] if they go by the table, else 0 and base[0] = those of each subject
+int prepare_grid(const int64_t *work, int32_t n, int64_t nzero, int cus, int64_t *base) {
+    const fc::PrepareGrid g = fc::prepare_grid(work, n, nzero, cus, base);
+    if (!g.table) base[0] = g.blocks;
+    return g.table && g.blocks == base[n] ? 1 : (g.table ? -1 : 0);
+}
+
 }

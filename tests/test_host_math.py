@@ -2,7 +2,8 @@
 (tests/native/host_math.hip): which voxels of a row a lane of the compact build reads and owns;
 that one 32-bit code holds every row and label that the argument checks let in; which range of the points
 a streamline belongs to, of which the table of ranges needs that it never decreases; that the ranges which
-wavefronts find for themselves cover every streamline once."""
+wavefronts find for themselves cover every streamline once; that a plan's preparation gives every subject
+workgroups in proportion to its work."""
 import ctypes
 import os
 import subprocess
@@ -230,3 +231,43 @@ def test_own_ranges_of_decreasing_offsets_stay_in_bounds(seed):
     off = rng.integers(-1000 if seed % 2 else 0, 300_000, S + 1)
     for s0, s1 in _own_ranges(off, 512)[0]:
         assert 0 <= s0 <= s1 <= S
+
+
+def _grid(lib, work, nzero=5200, cus=256):
+    w = np.asarray(work, np.int64)
+    base = np.zeros(w.size + 1, np.int64)
+    vp = ctypes.c_void_p
+    t = lib.prepare_grid(w.ctypes.data_as(vp), ctypes.c_int32(w.size), ctypes.c_int64(nzero), ctypes.c_int(cus), base.ctypes.data_as(vp))
+    assert t >= 0
+    return (np.diff(base) if t else np.full(w.size, base[0])), base, bool(t)
+
+
+@pytest.mark.parametrize("small", [0, 1, 100, 3000])
+@pytest.mark.parametrize("n", [1, 2, 16, 64, 256, 1000, 5000])
+@pytest.mark.parametrize("big", [100, 20_000, 3_000_000, 20_000_000])
+def test_preparation_workgroups_follow_the_work(lib, small, n, big):
+    for at in {0, n // 2, n - 1}:
+        work = np.full(n, small, np.int64)
+        work[at] = big
+        blocks, base, table = _grid(lib, work)
+        assert ((blocks >= 1) | (work == 0)).all()
+        assert blocks.sum() <= 4096 + n or not table
+        # no subject needs more than about twice the steps of an even split over the whole launch
+        steps = np.ceil(work / np.maximum(blocks, 1) / 256)
+        even = np.ceil(work.sum() / (4096 * 256))
+        assert steps.max() <= 2 * even + 2, (steps.max(), even, table)
+        if table:   # every workgroup finds its subject (64 bases a round)
+            for b in np.unique(np.concatenate([[0, base[n] - 1], base[:-1][blocks > 0], base[1:][blocks > 0] - 1])):
+                lo, hi = 0, n
+                while hi - lo > 1:
+                    step = (hi - lo + 63) // 64
+                    idx = lo + np.arange(64) * step
+                    lo += (int((base[idx[idx < hi]] <= b).sum()) - 1) * step
+                    hi = min(hi, lo + step)
+                assert base[lo] <= b < base[lo + 1], (b, lo)
+
+
+def test_balanced_plans_keep_equal_shares(lib):
+    rng = np.random.default_rng(5)
+    for n in (1, 12, 24, 100):
+        assert not _grid(lib, rng.integers(100_000, 300_000, n))[2]
