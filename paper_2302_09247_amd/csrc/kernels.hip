@@ -1405,9 +1405,8 @@ __device__ __forceinline__ void for_each_range(const Ranges &rg, const StreamSub
 template <bool SCALED, int kBatch, bool kEnds, bool kBrick, bool kSearch>
 __device__ __forceinline__ void count_stream_body(const StreamSubject &sub, const Overflow &ovf,
                                                   const Ranges &rg, const PairOut &po) {
-    // 4-window batches run 5 wavefronts per SIMD (81 to 84 vector registers), so they can afford the LDS of
-    // 512 buffered updates; 2-window batches keep 8 per SIMD with 256.  (Held to the 80 registers of a sixth,
-    // the 4-window kernel measured no faster: 2601 against 2594 us for 5M streamlines.)
+    // 4-window batches run 6 wavefronts per SIMD (their vector registers), so they can afford the LDS of 512
+    // buffered updates; 2-window batches keep 8 per SIMD with 256
     constexpr int kSinkCap = kBatch == 4 ? 8 * kWave : 4 * kWave;
     __shared__ uint32_t s_set[kWavesPerBlock * kSetWords];
     __shared__ __align__(16) uint32_t s_pend[kWavesPerBlock * kSinkCap];
@@ -1439,8 +1438,11 @@ k_count_stream2(StreamSubject sub, Overflow ovf, Ranges rg, PairOut po) {
 
 // (kSearch: wavefronts find their ranges themselves.  Two instantiations: with the search before it the loop
 // keeps other scalars in registers, and 5M streamlines, which come in a table, take 2613 instead of 2592 us.)
+// Six wavefronts per SIMD (at most 80 vector registers): left to itself the compiler takes 81 to 84, which is
+// five, and 5M streamlines of 150 points on a 210x240x200 grid take 1727 instead of 1616 us, on 145x174x145 1791
+// instead of 1669, on 260x311x260 1702 instead of 1667; 5M of 220 points there take 2600 either way.
 template <bool SCALED, bool kEnds, bool kBrick, bool kSearch>
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(6)))
 k_count_stream4(StreamSubject sub, Overflow ovf, Ranges rg, PairOut po) {
     count_stream_body<SCALED, 4, kEnds, kBrick, kSearch>(sub, ovf, rg, po);
 }

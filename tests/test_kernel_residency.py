@@ -66,7 +66,7 @@ def _waves(k):
     return min(8, 512 // vgprs, 800 // sgprs)
 
 
-@pytest.mark.parametrize("part,waves", [("k_count_stream_up", 6), ("k_count_stream2", 8), ("k_count_stream4", 5),
+@pytest.mark.parametrize("part,waves", [("k_count_stream_up", 6), ("k_count_stream2", 8), ("k_count_stream4", 6),
                                         ("k_count_batched", 6), ("k_pair_sort", 8)])
 def test_wavefronts_per_simd(kernels, part, waves):
     found = [k for name, k in kernels.items() if part in name]
