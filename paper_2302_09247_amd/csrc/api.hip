@@ -294,7 +294,7 @@ int enqueue_count(const CountPlan &cp, const CountScratch &sc, int dev, const Vo
                   const fc::CompactVol *cv, int32_t *C, const fastcod_opts &o, hipStream_t st) {
     const int cus = cu_count(dev);
     auto build = [&](bool zeroed) {
-        return enqueue_compact_build(vb->roi, vb->lab, vb->dims, N, M, *vb->L, vb->buf, cus, st, zeroed);
+        return enqueue_compact_build(vb->roi, vb->lab, vb->dims, N, M, *vb->L, vb->buf, cus, st, zeroed, S);
     };
     // the partition launch zeroes what the build needs, so the build follows it
     const bool build_late = vb && !cp.seed_end && S > 0;

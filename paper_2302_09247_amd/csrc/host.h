@@ -208,10 +208,11 @@ inline int32_t *compact_zero_words(void *buf, const CompactLayout &L, int64_t *n
 }
 
 // Builds the compact volume of (roi, lab) into `buf` (L.bytes, laid out by compact_layout) on `st`;
-// zeroed: compact_zero_words are zero already (by an earlier launch on `st`).
+// zeroed: compact_zero_words are zero already (by an earlier launch on `st`); S: streamlines of the call
+// that builds it (0: built to be kept).
 inline hipError_t enqueue_compact_build(const int32_t *roi, const int32_t *lab, const int32_t dims[3], int32_t N,
                                         int32_t M, const CompactLayout &L, void *buf, int cus, hipStream_t st,
-                                        bool zeroed = false) {
+                                        bool zeroed = false, int64_t S = 0) {
     const fc::CompactVol cv = compact_view(buf, L, N, M);
     char *b = static_cast<char *>(buf);
     int64_t nz = 0;
@@ -222,7 +223,7 @@ inline hipError_t enqueue_compact_build(const int32_t *roi, const int32_t *lab, 
     }
     return fc::launch_compact_build(roi, lab, make_grid(dims), cv, reinterpret_cast<uint2 *>(b + L.off_mb),
                                     reinterpret_cast<uint32_t *>(b + L.off_codes), reinterpret_cast<uint32_t *>(zero) + kCoarseHead,
-                                    reinterpret_cast<uint32_t *>(zero), st);
+                                    reinterpret_cast<uint32_t *>(zero), S, st);
 }
 
 inline int check_volume_args(const int32_t *roi, const int32_t *lab, const int32_t dims[3], int32_t N, int32_t M) {

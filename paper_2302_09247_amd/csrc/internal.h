@@ -156,9 +156,10 @@ hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, int cus, hipStream_
 hipError_t launch_fill_u64(unsigned long long *p, int64_t n, int cus, hipStream_t st);
 
 // compact volume build: cv's layout and sizes, written through mb (W {word, base} pairs), codes and
-// coarse (ncoarse_words, zero on entry); ncodes: the number of codes written (zero on entry)
+// coarse (ncoarse_words, zero on entry); ncodes: the number of codes written (zero on entry); S: streamlines
+// of the call that builds it (0: built to be kept)
 hipError_t launch_compact_build(const int32_t *roi, const int32_t *lab, Grid g, CompactVol cv, uint2 *mb, uint32_t *codes,
-                                uint32_t *coarse, uint32_t *ncodes, hipStream_t st);
+                                uint32_t *coarse, uint32_t *ncodes, int64_t S, hipStream_t st);
 
 // The 4 voxels x .. x + 3 of a row of X that one lane of the build reads: it loads elements xs .. xs + 3
 // (kWide: rows of at least 4 voxels, the last 4 where x .. x + 3 pass the end), `mine` are those inside its

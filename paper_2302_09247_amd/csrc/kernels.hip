@@ -508,16 +508,17 @@ hipError_t launch_fill_u64(unsigned long long *p, int64_t n, int cus, hipStream_
 // for every wavefront took 75, 27 and 11 us: atomics on one line are served one after another.
 // kWide: rows of at least 4 voxels; a lane whose voxels pass the end of the row then takes its last 4
 // (16-byte loads need only the 4-byte alignment of the elements).
-// kNt: non-temporal loads, for volumes of more than kBuildCachedVoxels.  Cached, 168 MB of volumes
-// (260x311x260) displace the offsets and the zeroed C from the last-level cache, and the counting
-// kernel and the tile pass read them from memory: the build takes 35 instead of 42 us, the whole call
-// 2700 instead of 2644.  Small ones leave room: cached, 145x174x145 (29 MB) takes 395 instead of 397
-// us a call, and 64^3 20.5 instead of 21.0.
+// kNt: non-temporal loads, for more than kBuildCachedVoxels in a call of at least kBuildCachedStreamlines.
+// Cached, 168 MB of volumes (260x311x260) displace the offsets and the zeroed C of a large call from the
+// last-level cache: the build takes 36 instead of 42 us, but 5M streamlines of 220 points take 2609 instead
+// of 2594 a call.  Smaller calls leave room for both: cached, 100,000 streamlines on that grid take 117 instead of
+// 125 us, 1M 414 and 424, 3M 1052 and 1060, 5M of 150 points 1698 and 1702; 100,000 on 210x240x200 98 and 103.
 // coarse[] and *ncodes are zero on entry.
 constexpr int kBuildSteps = 4;                   // steps of a wavefront: two a slice
 constexpr int kBuildParts = 16 / kBuildSteps;    // wavefronts per super-brick along z
 constexpr int kBuildWaves = 2 * kBuildParts;     // two 64-voxel chunks along x
 constexpr int64_t kBuildCachedVoxels = int64_t(1) << 23;   // 64 MB of volumes
+constexpr int64_t kBuildCachedStreamlines = int64_t(1) << 22;
 template <bool kWide, bool kNt>
 __global__ void __launch_bounds__(kBuildWaves *kWave)
 k_compact_build(const int32_t *__restrict__ roi, const int32_t *__restrict__ lab, Grid g, CompactVol cv, int32_t SBY,
@@ -657,11 +658,12 @@ k_compact_build(const int32_t *__restrict__ roi, const int32_t *__restrict__ lab
 }
 
 hipError_t launch_compact_build(const int32_t *roi, const int32_t *lab, Grid g, CompactVol cv, uint2 *mb, uint32_t *codes,
-                                uint32_t *coarse, uint32_t *ncodes, hipStream_t st) {
+                                uint32_t *coarse, uint32_t *ncodes, int64_t S, hipStream_t st) {
     const int32_t SBY = cv.SBXY / cv.SBX;
     const int64_t SBZ = cv.W / 32 / cv.SBXY;
     const unsigned blocks = (unsigned)((int64_t)((cv.SBX + 7) / 8) * SBY * SBZ);
-    const bool wide = g.X >= 4, nt = (int64_t)g.X * g.Y * g.Z > kBuildCachedVoxels;
+    const bool wide = g.X >= 4;
+    const bool nt = S >= kBuildCachedStreamlines && (int64_t)g.X * g.Y * g.Z > kBuildCachedVoxels;
 #define FC_BUILD(W_, T_) \
     k_compact_build<W_, T_><<<blocks, kBuildWaves * kWave, 0, st>>>(roi, lab, g, cv, SBY, mb, codes, coarse, ncodes)
     if (wide && nt) FC_BUILD(true, true);
