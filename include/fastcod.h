@@ -86,8 +86,9 @@ typedef struct fastcod_opts {
     int32_t batch;      /* flat-stream schedule: 64-point windows per pipelined batch, 2 or 4; 0 = 4 for
                            n_streamlines >= 2^21 (ranges long enough to fill the deeper pipeline), else 2 */
     int32_t blocks_per_cu; /* flat-stream schedule: resident workgroups per CU, 0 = occupancy limit */
-    int32_t mode;       /* FASTCOD_MODE_*; the batched and served forms count FASTCOD_MODE_PASSTHROUGH */
-    int64_t pair_capacity; /* flat-stream path: workspace entries (4 bytes each, held twice) for the   */
+    int32_t mode;       /* FASTCOD_MODE_* (subjects of a plan and served requests carry their own)        */
+    int64_t pair_capacity; /* flat-stream path: workspace entries (4 bytes each, 2 more for a sorted   */
+                        /* copy, and a table of the copy's runs) for the                            */
                         /* C updates it appends and later adds into C tile by tile; 0 = 8 per       */
                         /* streamline, clamped to [2^20, 2^28]; values above INT32_MAX are clamped.  */
                         /* Updates that find their wavefront's share full go to C as atomics: the   */
@@ -156,17 +157,17 @@ int fastcod_volume_destroy(fastcod_volume *vol);
  * transposed copy), and N and M whose overflow bit maps exceed 4 MiB fail with ENOMEM -- every
  * such check happens before anything is enqueued.  Calls on one device share the area: calls
  * that overlap in time on one device (two streams, or two threads) race and give wrong counts,
- * so serialise them (one stream).  The area keeps the last call's contents; each call clears what
- * it needs zeroed with a kernel of its own (no memset node under capture).
+ * so serialise them (one stream).  The area keeps the last call's contents; each call's first kernel
+ * clears what it needs zeroed (no memset node under capture).
  */
 int fastcod_volume_count_noalloc(const fastcod_volume *vol, const float *points, const int64_t *offsets,
                                  int64_t n_streamlines, int32_t *C_out, const fastcod_opts *opts, void *stream);
 
 /*
  * Batched form: many subjects (each its own streamlines, volumes, N, M, scale, mode, upsampling and
- * C) counted by persistent kernels that take (subject, point range) work items from a counter, the
- * whole sequence (zero every C, end labels, partition, count, overflow fallback, transposes) captured
- * once in a hipGraph and replayed by every launch.  Subjects of one kind share one launch: all the
+ * C) counted by persistent kernels that take (subject, point range) work items from queues, the
+ * whole sequence (one preparation kernel: every C zeroed, the work items written; count, overflow
+ * fallback, transposes) captured once in a hipGraph and replayed by every launch.  Subjects of one kind share one launch: all the
  * pass-through subjects (the usual case) one, the endpoint-mode subjects (Alg. 2 as printed,
  * Section 2) another, upsampled ones (Section 3) a third, Alg. 1's seed-to-end subjects a fourth.
  * Each subject's C is identical to what fastcod_count_ex gives for it with the same scale, mode and
@@ -203,10 +204,11 @@ typedef struct fastcod_plan fastcod_plan;
 /*
  * Builds a plan (synchronous on `stream`): compact volumes of every distinct volume pair (built
  * once, kept by the plan; the source volumes may be freed afterwards), work-item tables, scratch,
- * and the captured graph.  A subject with streamlines, N >= 64, M >= 2 and a C_out that no other
- * subject of the plan writes is counted into a plan-owned transposed copy [M][N] (4*N*M bytes),
- * transposed into C_out at the end of each launch; the others count into C_out directly.  Points, offsets and C_out are read/written by every launch, so their
- * contents may change between launches but their addresses and sizes may not.
+ * and the captured graph.  In plans of more than 2^24 points, a subject with streamlines, N >= 64,
+ * M >= 2 and a C_out that no other subject of the plan writes is counted into a plan-owned transposed
+ * copy [M][N] (4*N*M bytes), transposed into C_out at the end of each launch; the others count into
+ * C_out directly.  Points, offsets and C_out are read/written by every launch, so their contents may
+ * change between launches but their addresses and sizes may not.
  * tune_cache: optional HOST path of a text file of tuned schedules (read, and appended to when
  * FASTCOD_PLAN_TUNE times a new kind of batch); NULL = no file.
  * Errors: EINVAL (bad subject, or a grid too thin for the compact volume), ENOMEM, EHIP.

@@ -33,7 +33,7 @@ struct Workspace {
     DevBuf fallback;    // fallback scratch (all-zero between launches)
     DevBuf flags;       // validation flags
     DevBuf ct;          // transposed accumulation copy of C (C beyond the histogram's tiles)
-    DevBuf pairs;       // appended C updates: slice lengths, run table, slices, sorted copy
+    DevBuf pairs;       // appended C updates: slice lengths, run table, slices, sorted copy (16-bit)
     void free_buffers() {
         for (DevBuf *b : {&compact, &first, &ovf, &fallback, &flags, &ct, &pairs}) b->release();
     }
@@ -139,9 +139,13 @@ constexpr int64_t kDirectMaxStreamlines = int64_t(1) << 17;   // calls below thi
 constexpr int64_t kDirectMaxEntries = int64_t(1) << 20;       // ... on a C of at most this many entries
                                                               // add their updates to C as atomics
 
-// Plans of more pass-through points than this count into transposed copies of C.  The copies save about a
-// quarter of the atomic requests and cost a launch and a pass over C: 12 subjects of 200M points take
-// 1090 us a launch with and 1151 without them, 24 little subjects of 3.4M points 53.3 with and 41.8 without.
+// Plans of more points than this (all subjects') count into transposed copies of C.  The copies save up to a
+// quarter of the atomic requests, where a streamline's updates fall into neighbouring rows, and cost a launch and
+// a pass over C.  Which is more hangs on the updates a point makes, which nobody knows when the plan is built;
+// so the line only keeps the copies from plans whose passes over C they would dominate.  A launch takes,
+// with copies and without: 24 subjects of 3.4M points and 5M entries in all 48 and 38 us, 12 of 8M and 5M 82 and 66, of
+// 30M and 5M 156 and 141, of 150M and 39M 684 and 606, of 149M and 157M 1292 and 965; and of 200M and 75M, with
+// more updates a point, 1094 and 1173.
 constexpr int64_t kTransposeMinPoints = int64_t(1) << 24;
 
 // Fallback scratch layout for a C of N rows and M labels: per workgroup an N-bit map, an M-bit map
@@ -222,9 +226,11 @@ int make_count_plan(int64_t S, int32_t N, int32_t M, const fc::CompactVol *cv, c
     // transposed workspace copy CT[M][N] instead: the rows of one streamline are neighbouring ROI
     // indices, so its pair updates share memory lines there.
     // Small calls (fewer than 2^17 streamlines) on a small C add their updates to C as atomics
-    // instead: there the histogram's three launches cost more than the atomics they replace (10k
-    // streamlines on a 64^3 grid: 41 against 62 us a call).  At 1M streamlines the pair buffer still
-    // keeps the counting kernel 5-8% shorter; the whole call is then within a few percent either way.
+    // instead: there the histogram's launches cost more than the atomics they replace (2272 x 8 entries:
+    // 10,000 streamlines 16 against 28 us a call, 131,000 61 against 86; 7944 x 70: 66 against 77).  Spread
+    // updates would gain up to about 300,000 (262,000: 108 against 147 and 114 against 128 us; 400,000: 171 against
+    // 196 and 172 against 170), but updates that gather in a few entries are served one after another
+    // (131,000 streamlines on four entries: 1765 against 218 us), so the line lies below.
     // An explicit pair_capacity keeps the pair buffer.
     cp.NM = (int64_t)N * M;
     const bool direct = o.pair_capacity == 0 && S < kDirectMaxStreamlines && cp.NM <= kDirectMaxEntries;

@@ -48,8 +48,6 @@ struct CompactVol {
     uint32_t span;            // bytes from mb to the end of the code array (< 2^32 - 16)
 };
 
-// Streamlines whose distinct (row, label) keys outgrow the per-wave LDS set are handed to a
-// fallback kernel through this queue of point indices (one point inside each such streamline).
 // Per-wavefront slices of appended C updates (flat-stream kernel, plain path): wavefront w writes
 // its entries to pairs[w * cap ...] and their number to counts[w]; cap 0 = every update is an atomic.
 struct PairOut {
@@ -88,6 +86,8 @@ inline PairTiles pair_tiles(int64_t NM, int64_t S, int64_t nwaves, int64_t cap) 
     return pt;
 }
 
+// Streamlines whose distinct (row, label) keys outgrow the per-wave LDS set are handed to a
+// fallback kernel through this queue of point indices (one point inside each such streamline).
 struct Overflow {
     unsigned long long *count;
     int64_t *list;
@@ -211,8 +211,8 @@ struct RangeOf {
 };
 
 // Per-call state zeroed by the partition launch, so that it needs no launches of its own: C when
-// it is not accumulated into, a fixed scratch area's fallback bit maps, the coarse map of a volume built by the same call, the overflow and range counters.  Each
-// range may be empty.
+// it is not accumulated into, a fixed scratch area's fallback bit maps, the coarse map of a volume built by
+// the same call, the overflow and range counters.  Each range may be empty.
 constexpr int kZeroRanges = 3;
 struct ZeroRanges {
     int32_t *w32[kZeroRanges] = {};

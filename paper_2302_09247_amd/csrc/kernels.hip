@@ -5,8 +5,8 @@
 // (loc2region applied to its points) are formed, and every (row, label) pair of the two sets adds
 // one to C.  The stages here:
 //   * compact volume build: one pass over both volumes -> occupancy bits + packed codes;
-//   * partition: tapering ranges of whole streamlines (one pass over the offsets); the same
-//     launch zeroes the call's per-call state;
+//   * partition: tapering ranges of whole streamlines (one pass over the offsets; smaller calls' wavefronts
+//     find a range each themselves); the same launch zeroes the call's per-call state;
 //   * count kernels (wave-per-streamline over raster volumes, or flat point stream over the
 //     compact volume): voxelise each point, look it up, de-duplicate the hits of each streamline
 //     in a per-wavefront LDS hash set, and emit its |I| x |M| pair updates: the flat-stream
@@ -273,7 +273,7 @@ struct AppendSink {
         buf = b;
         n = 0;
         C = c;
-        out = po.pairs + (size_t)wave * po.cap;   // (po.cap is a multiple of 4)
+        out = po.pairs + (size_t)wave * po.cap;   // (po.cap is a multiple of 8)
         room = po.cap;
     }
     __device__ void emit(int cnt) {   // the first cnt (<= kSinkCap) entries of buf
@@ -877,9 +877,8 @@ hipError_t launch_count_wave(const CountArgs &a, const RasterVol &rv, int blocks
 // count, variant 2: flat point stream over ranges of whole streamlines
 // ---------------------------------------------------------------------------------------------
 //
-// Wavefront w owns the streamlines [first[w], first[w+1]): one contiguous range of about P/W
-// points.  It walks the range in batches of kBatch 64-point windows regardless of streamline
-// boundaries.  Per batch: voxelise, occupancy-bit gathers (a 2-3 MB structure that stays in L2),
+// A wavefront takes contiguous ranges of whole streamlines, from the table or one of its own.  It walks a
+// range in batches of kBatch 64-point windows regardless of streamline boundaries.  Per batch: voxelise, occupancy-bit gathers (a 2-3 MB structure that stays in L2),
 // and for the few flagged lanes the rank and code gathers; only then are the next batch's
 // streaming loads issued (vector loads return in issue order, so no gather wait of this batch
 // covers them), and the windows are folded into the open streamline's LDS set while they are in
